@@ -95,7 +95,7 @@ typedef struct {
 /*
  * The same operator on strided tensors and on other head dimensions (the paper's evaluation spans
  * models with less common head sizes, Section 7.1): D any multiple of 8 up to 256 -- a head runs on
- * the next of the 64-, 128- and 256-wide kernels with the missing columns of Q read as zero.  `st` gives
+ * the next of the 64-, 80-, 96-, 128-, 192- and 256-wide kernels with the missing columns of Q read as zero.  `st` gives
  * element strides as above (NULL = contiguous [B][H][S][D]); q/k/v strides must be non-negative
  * multiples of 8 (16 bytes; 0 broadcasts a tensor along that axis), o strides positive multiples of 4,
  * every sequence stride at least D and at most 2^23.  lse stays contiguous [B][Hq][S].  Everything else

@@ -9,12 +9,14 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 _CSRC = os.path.join(_HERE, "csrc")
 # (source, extra defines, object name).  The prefill kernels are instantiated in naut_attn_inst.hip, compiled
-# once per (input type, output type) pair so that the four pairs build in parallel.
+# once per (input type, output type) pair and group of head widths so that they build in parallel.
 _DT = {"bf16": 0, "f16": 1, "f32": 2}  # naut_dtype
 JOBS = [(os.path.join(_CSRC, n), [], n + ".o") for n in ("naut_attn.hip", "naut_decode.hip", "naut_fp8.hip", "naut_probe.hip")]
-JOBS += [(os.path.join(_CSRC, "naut_attn_inst.hip"), ["-DNAUT_INST_IN=%d" % _DT[i], "-DNAUT_INST_OUT=%d" % _DT[o]],
-          "naut_attn_inst_%s_%s.o" % (i, o))
-         for i, o in (("bf16", "bf16"), ("bf16", "f32"), ("f16", "f16"), ("f16", "f32"))]
+JOBS = [(os.path.join(_CSRC, "naut_attn_inst.hip"),
+         ["-DNAUT_INST_IN=%d" % _DT[i], "-DNAUT_INST_OUT=%d" % _DT[o], "-DNAUT_INST_W=%d" % w],
+         "naut_attn_inst_%s_%s_%d.o" % (i, o, w))
+        for w in (128, 96, 256, 64)  # the longest compiles first
+        for i, o in (("bf16", "bf16"), ("bf16", "f32"), ("f16", "f16"), ("f16", "f32"))] + JOBS
 SRCS = sorted({j[0] for j in JOBS})
 LIB = os.path.join(_HERE, "libnaut_attn.so")
 # The same sources with every hand-made synchronisation replaced by its most conservative form (-DNAUT_SAFE_SYNC=1,

@@ -25,18 +25,18 @@ int fail_launch(hipError_t e)
 namespace naut_k {
 
 // defined in naut_attn_inst.hip
-extern template int launch<64, NAUT_BF16, NAUT_BF16>(const Params&, int, hipStream_t);
-extern template int launch<128, NAUT_BF16, NAUT_BF16>(const Params&, int, hipStream_t);
-extern template int launch<256, NAUT_BF16, NAUT_BF16>(const Params&, int, hipStream_t);
-extern template int launch<64, NAUT_BF16, NAUT_F32>(const Params&, int, hipStream_t);
-extern template int launch<128, NAUT_BF16, NAUT_F32>(const Params&, int, hipStream_t);
-extern template int launch<256, NAUT_BF16, NAUT_F32>(const Params&, int, hipStream_t);
-extern template int launch<64, NAUT_F16, NAUT_F16>(const Params&, int, hipStream_t);
-extern template int launch<128, NAUT_F16, NAUT_F16>(const Params&, int, hipStream_t);
-extern template int launch<256, NAUT_F16, NAUT_F16>(const Params&, int, hipStream_t);
-extern template int launch<64, NAUT_F16, NAUT_F32>(const Params&, int, hipStream_t);
-extern template int launch<128, NAUT_F16, NAUT_F32>(const Params&, int, hipStream_t);
-extern template int launch<256, NAUT_F16, NAUT_F32>(const Params&, int, hipStream_t);
+#define NAUT_EXTERN(IN, OUT)                                                      \
+    extern template int launch<64, IN, OUT>(const Params&, int, hipStream_t);   \
+    extern template int launch<80, IN, OUT>(const Params&, int, hipStream_t);   \
+    extern template int launch<96, IN, OUT>(const Params&, int, hipStream_t);   \
+    extern template int launch<128, IN, OUT>(const Params&, int, hipStream_t);  \
+    extern template int launch<192, IN, OUT>(const Params&, int, hipStream_t);  \
+    extern template int launch<256, IN, OUT>(const Params&, int, hipStream_t);
+NAUT_EXTERN(NAUT_BF16, NAUT_BF16)
+NAUT_EXTERN(NAUT_BF16, NAUT_F32)
+NAUT_EXTERN(NAUT_F16, NAUT_F16)
+NAUT_EXTERN(NAUT_F16, NAUT_F32)
+#undef NAUT_EXTERN
 
 }  // namespace naut_k
 
@@ -134,23 +134,22 @@ int naut_attn_fwd_strided(const void* q, const void* k, const void* v, void* o, 
     // is kept to two heads at a time (measured: +2..5 % over all of its heads at once; no gain for D <= 128)
     p.hao = D > 128 ? 2 : 0;
     hipStream_t st_ = (hipStream_t)stream;
-    const int DK = D <= 64 ? 64 : D <= 128 ? 128 : 256;  // width the kernel is compiled for
+    const int DK = compiled_width(D);
 
-#define NAUT_DISPATCH(DD, IN, OUT)                         \
-    if (DK == DD && in_dtype == IN && out_dtype == OUT)   \
-        return launch<DD, IN, OUT>(p, causal, st_);
-    NAUT_DISPATCH(128, NAUT_BF16, NAUT_BF16)
-    NAUT_DISPATCH(64, NAUT_BF16, NAUT_BF16)
-    NAUT_DISPATCH(128, NAUT_BF16, NAUT_F32)
-    NAUT_DISPATCH(64, NAUT_BF16, NAUT_F32)
-    NAUT_DISPATCH(128, NAUT_F16, NAUT_F16)
-    NAUT_DISPATCH(64, NAUT_F16, NAUT_F16)
-    NAUT_DISPATCH(128, NAUT_F16, NAUT_F32)
-    NAUT_DISPATCH(64, NAUT_F16, NAUT_F32)
-    NAUT_DISPATCH(256, NAUT_BF16, NAUT_BF16)
-    NAUT_DISPATCH(256, NAUT_BF16, NAUT_F32)
-    NAUT_DISPATCH(256, NAUT_F16, NAUT_F16)
-    NAUT_DISPATCH(256, NAUT_F16, NAUT_F32)
+#define NAUT_DISPATCH(IN, OUT)                                \
+    if (in_dtype == IN && out_dtype == OUT)                   \
+        switch (DK) {                                         \
+        case 64: return launch<64, IN, OUT>(p, causal, st_);  \
+        case 80: return launch<80, IN, OUT>(p, causal, st_);  \
+        case 96: return launch<96, IN, OUT>(p, causal, st_);  \
+        case 128: return launch<128, IN, OUT>(p, causal, st_); \
+        case 192: return launch<192, IN, OUT>(p, causal, st_); \
+        default: return launch<256, IN, OUT>(p, causal, st_); \
+        }
+    NAUT_DISPATCH(NAUT_BF16, NAUT_BF16)
+    NAUT_DISPATCH(NAUT_BF16, NAUT_F32)
+    NAUT_DISPATCH(NAUT_F16, NAUT_F16)
+    NAUT_DISPATCH(NAUT_F16, NAUT_F32)
 #undef NAUT_DISPATCH
     return fail(NAUT_ERR_UNSUPPORTED, "no kernel for this (D, dtype) combination");
 }

@@ -66,6 +66,15 @@ constexpr int NTHREADS = NWAVES * 64;
 constexpr float RESCALE_TAU = 6.0f;  // log2 units
 constexpr float P_LIMIT = 1024.0f;   // a block's per-lane row sum above this moves the reference maximum
 
+// The kernels are compiled for head dimensions 64, 80, 96, 128, 192 and 256; a head in between runs on the next
+// wider one.  In LDS a row of K or V always takes 64, 128 or 256 values, so that the swizzles (which need a power
+// of two) are those of the wide head; a narrower head leaves the rest of the row out of its MFMAs and fragment
+// reads.  At D = 80 that is 11 MFMAs for every 16 of the 128-wide head, at 96 it is 12, at 192 24 for 32.  Measured
+// against the next wider kernel: 4x16 heads, S = 1777, D = 80 108 -> 88 us; 4x64/8 heads, S = 3835, D = 192, causal
+// 2.67 -> 2.28 ms (outputs bit-identical).
+constexpr int layout_width(int D) { return D <= 64 ? 64 : D <= 128 ? 128 : 256; }
+constexpr int compiled_width(int D) { return D <= 64 ? 64 : D <= 80 ? 80 : D <= 96 ? 96 : D <= 128 ? 128 : D <= 192 ? 192 : 256; }
+
 struct Params {
     const void* q;
     const void* k;
@@ -77,7 +86,7 @@ struct Params {
     int nqt2;      // number of 256-query tiles
     float c;       // scale * log2(e), > 0
     // Byte strides of batch, head and sequence position (the D axis is contiguous).  The kernels are
-    // compiled for D = 64 or 128; a smaller head dimension runs on the next wider one: cpr 16-byte
+    // compiled for a few head dimensions; others run on the next wider one: cpr 16-byte
     // chunks of every row are real, the chunks of Q beyond them read as zero, those of K and V repeat
     // a real chunk (they meet zeros of Q, or end in columns of O that are not stored).
     long long q_bs, q_hs, k_bs, k_hs, v_bs, v_hs, o_bs, o_hs;
@@ -133,11 +142,12 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
 {
     using T = In<DT_IN>;
     constexpr int BN = D > 128 ? 32 : 64;    // keys per step (hides the file-scope value used by kernel 2)
-    constexpr int ROWB = D * 2;              // bytes per K/V row
+    constexpr int W = layout_width(D);       // row width of the LDS layouts
+    constexpr int ROWB = W * 2;              // bytes per K/V row in LDS
     constexpr int TILEB = BN * ROWB;         // bytes per K or V tile
-    constexpr int CPR = D / 8;               // 16-byte chunks per row
+    constexpr int CPR = W / 8;               // 16-byte chunks per row
     constexpr int KS = D / 16;               // MFMA k-steps of Q.K^T
-    constexpr int DB = D / 32;               // 32-row blocks of O^T
+    constexpr int DB = (D + 31) / 32;        // 32-row blocks of O^T
     constexpr int KB = BN / 32;              // 32-key blocks of S^T
 
     // Tiles are filled by direct global->LDS loads, each wavefront its share of every tile.  D = 256: four K
@@ -242,7 +252,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
             krow = off / ROWB;
             kc = off % ROWB / 16;
             vrow = P / CPR;                                              // the inverse of v_off
-            vc = D == 128 ? (P % CPR) ^ ((vrow & 3) << 2) : (P % CPR) ^ (((vrow >> 1) & 1) << 2);
+            vc = W == 128 ? (P % CPR) ^ ((vrow & 3) << 2) : (P % CPR) ^ (((vrow >> 1) & 1) << 2);
         }
         kcol = (kc < cpr ? kc : cpr - 1) * 16;
         vcol = (vc < cpr ? vc : cpr - 1) * 16;
@@ -314,7 +324,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     int rd_k[KS], rd_v[DB];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-        rd_k[ks] = (int)smem_base + k_off<D>(l32, ks * 2 + h);
+        rd_k[ks] = (int)smem_base + k_off<W>(l32, ks * 2 + h);
         asm volatile("" : "+v"(rd_k[ks]));
     }
     {
@@ -323,7 +333,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const int d = 32 * db + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
-            rd_v[db] = (int)smem_base + v_off<D>(key, d >> 3) + (d & 7) * 2;
+            rd_v[db] = (int)smem_base + v_off<W>(key, d >> 3) + (d & 7) * 2;
             asm volatile("" : "+v"(rd_v[db]));
         }
     }
@@ -552,7 +562,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         // different rows per store instruction); after the exchange D/8 lanes write one row with 16 bytes
         // each.  The tiles are dead after the loop's last barrier (every tile load has landed, every
         // fragment has been consumed); each wavefront stages its 32 rows in its own part of them.
-        constexpr int CPRO = D / 8, R256 = ROWB >= 256 ? 1 : 256 / ROWB;
+        constexpr int CPRO = CPR, R256 = ROWB >= 256 ? 1 : 256 / ROWB;
         static_assert(NWAVES * 32 * ROWB <= (int)sizeof(smem), "staging rows must fit the tile buffers");
         // Every address below derives from this copy of the lane id, which exists only from here on: nothing
         // of the epilogue can be computed before the key loop and held in registers across it.
@@ -689,12 +699,13 @@ __global__ __launch_bounds__(NWV * 64, 1) void naut_fwd_kernel_v2(const Params p
     using XM = XMfma<DT_IN>;
     using PC = Pieces<QH>;
     static_assert(QH * NWV * 32 == BM2, "a work-group owns 256 queries");
-    constexpr int ROWB = D * 2;
+    constexpr int W = layout_width(D);         // row width of the LDS layouts
+    constexpr int ROWB = W * 2;
     constexpr int TILEB = BN * ROWB;           // one 64-key K or V tile
     constexpr int KS = D / 16;
-    constexpr int DB = D / 32;
+    constexpr int DB = (D + 31) / 32;
     constexpr int LD_PER_W = TILEB / 1024 / NWV;  // direct loads per wavefront per tile (1 KB each)
-    constexpr int NF = 2 * KS;                 // fragments per stage: even = V^T (Y), odd = K (X)
+    constexpr int NF = 2 * DB + KS;            // fragments per stage: even = V^T (Y), odd = K (X)
     constexpr int NS = NF * QH;                // slots (MFMAs) per stage
     constexpr int WQ = 32 * QH;                // queries per wavefront
     constexpr bool ALLV = QH == 1;  // everything fits the ordinary vector registers: no accumulation registers at all
@@ -705,7 +716,7 @@ __global__ __launch_bounds__(NWV * 64, 1) void naut_fwd_kernel_v2(const Params p
             asm volatile("" : "+a"(x));
     };
     constexpr int PREFETCH = NAUT_PF < NF ? NAUT_PF : NF - 1;  // LDS fragments in flight ahead of their MFMAs
-    static_assert(2 * DB == KS, "Y and X fragments must pair up");
+    static_assert(2 * DB == KS || 2 * DB == KS + 1, "Y and X fragments alternate, Y first");
     static_assert(LD_PER_W >= 1, "every wavefront must take part in the tile loads");
 
     __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * NBUF * TILEB];  // K tiles, then V tiles
@@ -792,11 +803,11 @@ __global__ __launch_bounds__(NWV * 64, 1) void naut_fwd_kernel_v2(const Params p
         {
             const int line = P >> 4, pos = P & 15;
             const int L = (line << 4) + (pos ^ (line & 15));
-            const int krow = L / (D / 8), kch = L % (D / 8);  // logical chunk L = row krow, chunk kch
+            const int krow = L / (W / 8), kch = L % (W / 8);  // logical chunk L = row krow, chunk kch
             k_goff[i] = krow * p.k_rs + (kch < cpr ? kch : cpr - 1) * 16;
             k_grow[i] = krow;
         }
-        if constexpr (D == 128) {
+        if constexpr (W == 128) {
             const int row = P >> 4, cc = P & 15;
             const int lc = cc ^ ((row & 3) << 2);
             v_goff[i] = row * p.v_rs + (lc < cpr ? lc : cpr - 1) * 16;
@@ -854,14 +865,14 @@ __global__ __launch_bounds__(NWV * 64, 1) void naut_fwd_kernel_v2(const Params p
     int k_lane[KS], v_lane[DB];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-        k_lane[ks] = k_off<D>(l32, ks * 2 + h);
+        k_lane[ks] = k_off<W>(l32, ks * 2 + h);
     {
         const int i16 = lane & 15;
         const int key = 4 * h + (i16 >> 2);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const int d = 32 * db + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
-            v_lane[db] = v_off<D>(key, d >> 3) + (d & 7) * 2;
+            v_lane[db] = v_off<W>(key, d >> 3) + (d & 7) * 2;
         }
     }
     // LDS byte addresses of the fragments in buffer 0 of K and of V; they stay as they are for the whole
@@ -1274,7 +1285,7 @@ __global__ __launch_bounds__(NWV * 64, 1) void naut_fwd_kernel_v2(const Params p
         // wavefront's own part of the first four tile buffers (where only its own tile loads land,
         // and those are complete), so no barrier is needed: the other wavefronts have consumed every
         // tile by the time this one is past the last barrier.
-        constexpr int CPRO = D / 8;           // 16-byte chunks per staged row
+        constexpr int CPRO = W / 8;           // 16-byte chunks per staged row
         constexpr int PS = LD_PER_W * 1024;   // this wavefront's part of one tile buffer
         constexpr int RP = PS / ROWB;         // staged rows per part
         constexpr int R256 = ROWB >= 256 ? 1 : 256 / ROWB;  // rows per 256-byte bank line
@@ -1396,30 +1407,30 @@ int launch(const Params& p, int causal, hipStream_t stream)
     if (nblocks > 0x7fffffffLL)
         return fail(NAUT_ERR_UNSUPPORTED, "B*Hq*ceil(S/128) exceeds the 1-D grid limit");
     const dim3 grid((unsigned)nblocks);
-#define NAUT_LAUNCH(KERNEL, THREADS)                                              \
+#define NAUT_LAUNCH(KERNEL, DD, THREADS)                                          \
     do {                                                                          \
         if (causal)                                                               \
-            hipLaunchKernelGGL((KERNEL<D, DT_IN, DT_OUT, true NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p);  \
+            hipLaunchKernelGGL((KERNEL<DD, DT_IN, DT_OUT, true NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p);  \
         else                                                                      \
-            hipLaunchKernelGGL((KERNEL<D, DT_IN, DT_OUT, false NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p); \
+            hipLaunchKernelGGL((KERNEL<DD, DT_IN, DT_OUT, false NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p); \
     } while (0)
     bool launched = false;
     if constexpr (D <= 128) {
         if (variant == V_W8Q32) {
 #define NAUT_TAIL , 1, 8
-            NAUT_LAUNCH(naut_fwd_kernel_v2, 512);
+            NAUT_LAUNCH(naut_fwd_kernel_v2, D, 512);
 #undef NAUT_TAIL
             launched = true;
         } else if (variant == V_W4Q64) {
 #define NAUT_TAIL , 2, 4
-            NAUT_LAUNCH(naut_fwd_kernel_v2, 256);
+            NAUT_LAUNCH(naut_fwd_kernel_v2, layout_width(D), 256);
 #undef NAUT_TAIL
             launched = true;
         }
     }
     if (!launched) {
 #define NAUT_TAIL
-        NAUT_LAUNCH(naut_fwd_kernel_bm128, NTHREADS);
+        NAUT_LAUNCH(naut_fwd_kernel_bm128, D, NTHREADS);
 #undef NAUT_TAIL
     }
 #undef NAUT_LAUNCH

@@ -232,3 +232,29 @@ def test_wide_head_row_stride_beyond_32_bits(D, variant, monkeypatch):
     o, lse = run_strided(qd, kd, vd, od, True, scale)
     o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, True, scale)
     gu.check(o, lse, o_ref, lse_ref, "D=%d %s, row stride 2^23" % (D, variant))
+
+
+@pytest.mark.parametrize("D,variant", [(72, "w8q32"), (80, "w8q32"), (88, "w8q32"), (96, "w8q32"), (104, "w8q32"),
+                                       (72, "bm128"), (88, "bm128"), (96, "bm128"), (104, "bm128"),
+                                       (136, ""), (184, ""), (192, ""), (200, "")])
+@pytest.mark.parametrize("causal,idt,odt,S", [(True, synth.BF16, synth.BF16, 197), (False, synth.F16, synth.F32, 322)])
+def test_compiled_widths(D, variant, causal, idt, odt, S, monkeypatch):
+    """Head dimensions on both sides of every width a kernel is compiled for (80, 96, 128, 192, 256), on rows padded
+    with NaN patterns: the columns between D and the compiled width must come from the padding of Q, never from
+    memory, and nothing may be written there."""
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
+    B, Hq, Hkv = 1, 4, 2
+    P = D + 24
+    q, k, v = make(B, Hq, Hkv, S, D, idt, 9500 + D)
+    scale = 1.0 / math.sqrt(D)
+
+    def padded(a):
+        buf = np.full(a.shape[:3] + (P,), 0x7FC0 if idt == synth.BF16 else 0x7E00, dtype=np.uint16)
+        buf[..., :D] = a
+        return gu.to_device(buf, idt)[..., :D]
+    o_buf = torch.full((B, Hq, S, P), 7.0, dtype=gu.TORCH_DT[odt], device="cuda")
+    print("compiled widths", D, variant, causal, flush=True)
+    o, lse = run_strided(padded(q), padded(k), padded(v), o_buf[..., :D], causal, scale)
+    o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, scale)
+    gu.check(o, lse, o_ref, lse_ref, "D=%d %s" % (D, variant))
+    assert torch.all(o_buf[..., D:] == 7.0).item(), "the gaps between O rows were written"
