@@ -130,9 +130,6 @@ int naut_attn_fwd_strided(const void* q, const void* k, const void* v, void* o, 
     p.o_hs = st->o_h * out_b;
     p.o_rs = (int)(st->o_s * out_b);
     p.cpr = D / 8;
-    // D = 256: the K/V of one head is twice as large and every 128-query work-group streams it, so an XCD
-    // is kept to two heads at a time (measured: +2..5 % over all of its heads at once; no gain for D <= 128)
-    p.hao = D > 128 ? 2 : 0;
     hipStream_t st_ = (hipStream_t)stream;
     const int DK = compiled_width(D);
 
@@ -177,7 +174,7 @@ const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int 
     if (B <= 0 || Hq <= 0 || S <= 0 || (D != 64 && D != 128 && D != 256) || !dtype_pair_ok(in_dtype, out_dtype))
         return nullptr;
     if (D == 256)
-        return "fwd_bm128_w4q32_bn32";
+        return wide_variant(S, (long long)B * Hq, causal) == V_W8Q32 ? "fwd_bm256_w8q32_bn32" : "fwd_bm128_w4q32_bn32";
     const int variant = pick_variant(S, (long long)B * Hq, D, causal);
     return variant < 0 ? nullptr : kVariantName[variant];
 }

@@ -7,7 +7,7 @@
 // One kernel computes O = softmax(scale * Q K^T + causal mask) V for a
 // (batch, head, query tile) per work-group; three variants share the formulation
 // below and are picked per shape (pick_variant): kernel 1 (128 queries per
-// work-group; also the D = 256 instantiation) and kernel 2 (256 queries,
+// work-group; heads wider than 128 run on it too, with 128 or 256 queries) and kernel 2 (256 queries,
 // software-pipelined over 32-key blocks, in two shapes).  The reductions over the key
 // axis (row max, row sum, weighted sum of V) are fused with the rolling-update
 // scheme of Section 4.2/4.3 of the paper: a running maximum m and running sum l
@@ -32,7 +32,7 @@
 // K and V tiles are multi-buffered in LDS, one barrier per tile, and go straight from
 // global memory into LDS (global_load_lds_dwordx4, the swizzle applied to the source
 // address): one tile ahead over two buffers in kernel 1, three tiles ahead over four
-// buffers in kernel 2 and in the D = 256 instantiation.
+// buffers in kernel 2 and for heads wider than 128.
 #ifndef NAUT_ATTN_KERNELS_H
 #define NAUT_ATTN_KERNELS_H
 #include <hip/hip_runtime.h>
@@ -60,7 +60,12 @@ using namespace naut;
 
 
 constexpr int BM = 128;  // queries per work-group
+constexpr int BM2 = 256; // queries per work-group of the eight-wavefront kernels
 constexpr int BN = 64;   // keys per step
+#ifndef NAUT_HAO
+#define NAUT_HAO 8
+#endif
+constexpr int HEADS_AT_ONCE = NAUT_HAO;  // (batch, head) pairs an XCD works on at a time (eight-wavefront kernels)
 constexpr int NWAVES = 4;
 constexpr int NTHREADS = NWAVES * 64;
 constexpr float RESCALE_TAU = 6.0f;  // log2 units
@@ -92,11 +97,10 @@ struct Params {
     long long q_bs, q_hs, k_bs, k_hs, v_bs, v_hs, o_bs, o_hs;
     int q_rs, k_rs, v_rs, o_rs;
     int cpr;       // real 16-byte chunks per row = head dimension / 8
-    int hao;       // kernel 1: (batch, head) pairs an XCD works on at a time (0: all of its share at once)
 };
 
 // S^T MFMAs of the variants that need more than 256 registers per lane (64 queries per wavefront in
-// kernel 2, D = 256 in kernel 1), written as asm so that their accumulator is an ordinary vector
+// kernel 2, wide heads on four wavefronts in kernel 1), written as asm so that their accumulator is an ordinary vector
 // register tuple while O and Q live in the accumulation registers (the compiler's own MFMA form
 // would then put the scores there too and copy each one out for the softmax).  The compiler's hazard handling does not look inside asm, so the wait states the
 // hardware does not interlock are owed by hand:
@@ -132,15 +136,27 @@ struct XMfma<NAUT_F16> {
     }
 };
 
-// ---- kernel 1: 128 queries per work-group, 4 wavefronts x 32 queries ----
-// Two work-groups per CU (four at D = 64) and 64 keys per step for D <= 128.  D = 256 doubles the O accumulator and the
-// Q fragments of a lane (192 registers between them), so it runs one work-group per CU on the full
-// 512-register budget, 32 keys per step (the four tile buffers then still fill 64 KB).
+// ---- kernel 1: 32 queries per wavefront, 4 wavefronts (D > 128: 4 or 8) per work-group ----
+// Two work-groups per CU (four at D = 64) and 64 keys per step for D <= 128.  A wider head doubles the O accumulator
+// and the Q fragments of a lane (192 registers between them at D = 256) and runs one work-group per CU with 32 keys per
+// step (four K and four V buffers of 16 KB), in two shapes:
+//   NWV = 8: two wavefronts per SIMD.  With O and Q, 16 scores that become P in place, and fragment addresses that
+//       share their two halves (k_at, v_at) a lane needs 246 of its 256 registers (D = 192: 218), all ordinary ones, so
+//       the compiler schedules every MFMA; while one wavefront of a SIMD does its softmax or waits for LDS the other's
+//       MFMAs run, and a K/V tile serves 256 queries.
+//   NWV = 4: one wavefront per SIMD on the 512-register budget, O and Q in the accumulation registers and the score
+//       MFMAs in asm.  It is bound by the dependences of its one instruction stream (46 % of the wavefront time is
+//       waiting), but one work-group of it takes 0.8 times as long as one of the other, so it stays for grids that do
+//       not fill the chip (see wide_variant).
+// S = 16384, 32 heads, causal, D = 256: 5281 us (833 TFLOP/s) on four wavefronts, 3920 us (1122) on eight, which is
+// where the clock the chip sustains under matrix load stops the D = 128 kernel too; D = 192, 4x64/8 heads,
+// S = 3835: 2250 -> 1463 us.  Outputs are bit-identical (same tiles, same order).
 
-template <int D, int DT_IN, int DT_OUT, bool CAUSAL>
-__global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm128(const Params p)
+template <int D, int DT_IN, int DT_OUT, bool CAUSAL, int NWV = NWAVES>
+__global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm128(const Params p)
 {
     using T = In<DT_IN>;
+    constexpr int BM = NWV * 32;             // queries per work-group (hides the file-scope value)
     constexpr int BN = D > 128 ? 32 : 64;    // keys per step (hides the file-scope value used by kernel 2)
     constexpr int W = layout_width(D);       // row width of the LDS layouts
     constexpr int ROWB = W * 2;              // bytes per K/V row in LDS
@@ -155,12 +171,15 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     // hide the load latency behind).  D <= 128: K0 V0 K1 V1 ..., a ring of NB2 buffers filled NB2 - 1 steps
     // ahead (the key loop is unrolled over the ring, so a tile's LDS offsets are instruction immediates).
     constexpr bool WIDE = D > 128;
+    constexpr bool ACC = WIDE && NWV == 4;         // O and Q live in the accumulation registers
+    constexpr bool PAIR = WIDE && NWV == 8;        // two wavefronts per SIMD on 256 ordinary registers each
+    static_assert(NWV == 4 || WIDE, "eight wavefronts: wide heads only");
     constexpr int NB = 4;                          // buffers per operand (wide)
     constexpr int NB2 = NAUT_K1_NBUF;              // buffers per operand (D <= 128)
-    constexpr int LDW = TILEB / 1024 / NWAVES;     // direct loads (1 KB each) per wavefront per tile
+    constexpr int LDW = TILEB / 1024 / NWV;        // direct loads (1 KB each) per wavefront per tile
     static_assert(LDW >= 1 && (NB2 - 1) * 2 * LDW < 64, "every wavefront loads; vmcnt field");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[(WIDE ? 2 * NB : 2 * NB2) * TILEB];
-    __shared__ float dl_lds[NTHREADS];
+    __shared__ float dl_lds[NWV * 64];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -171,21 +190,20 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     // Tile scheduler: heaviest (last) query tiles first; consecutive block ids walk the
     // (batch, head) axis so that each XCD (block id mod 8) keeps to a fixed subset of heads.
     const int nbh = p.B * p.Hq;
+    const int nqt = NWV == 4 ? p.nqt : p.nqt2;
     const int bid = blockIdx.x;
     int qt, bh;
-    if (p.hao > 0 && (nbh & 7) == 0) {
-        // Long key ranges: an XCD takes a contiguous run of heads and works on p.hao of them at a
-        // time, so that the K/V tiles its work-groups stream stay in its L2.
+    if (NWV == 8 && (nbh & 7) == 0) {  // as in kernel 2: an XCD's run of heads, a few at a time
         const int xcd = bid & 7, s = bid >> 3;
         const int hpx = nbh >> 3;
-        const int G = hpx < p.hao ? hpx : p.hao;
-        const int per_group = p.nqt * G;
+        const int G = hpx < HEADS_AT_ONCE ? hpx : HEADS_AT_ONCE;
+        const int per_group = nqt * G;
         const int g = s / per_group, sg = s % per_group;
         const int ng = hpx - g * G < G ? hpx - g * G : G;
         bh = xcd * hpx + g * G + sg % ng;
-        qt = p.nqt - 1 - sg / ng;
+        qt = nqt - 1 - sg / ng;
     } else {
-        qt = p.nqt - 1 - bid / nbh;
+        qt = nqt - 1 - bid / nbh;
         bh = bid % nbh;
     }
     const int b = bh / p.Hq;
@@ -215,7 +233,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     // The wide instantiation keeps it, and O, in the accumulation registers.  D <= 128 pins it only
     // after the first tile's loads are out, so that the two share one round trip to memory.
     auto pin_acc = [](f32x16_t& x) {
-        if constexpr (WIDE)
+        if constexpr (ACC)
             asm volatile("" : "+a"(x));
     };
     auto pin_q = [&](int cpr_now) {
@@ -223,7 +241,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         for (int ks = 0; ks < KS; ++ks) {
             if (ks * 2 + h >= cpr_now)
                 qf[ks] = i32x4_t{0, 0, 0, 0};
-            if constexpr (WIDE)
+            if constexpr (ACC)
                 asm volatile("" : "+a"(qf[ks]));
             else
                 asm volatile("" : "+v"(qf[ks]));
@@ -263,7 +281,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
 #pragma unroll
     for (int n = 0; n < LDW; ++n) {
         source_of(n, wk_row[n], wk_col[n], wv_row[n], wv_col[n]);
-        if constexpr (!WIDE) {
+        if constexpr (!ACC) {
             wk_col[n] += wk_row[n] * p.k_rs;
             wv_col[n] += wv_row[n] * p.v_rs;
         }
@@ -274,12 +292,12 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     // sequence re-read its last row.
     // (D <= 128: `buf`, the tile's place in the ring, is a constant at every call)
     auto issue_tile = [&](int tile, int buf = 0) {
-        const unsigned kd = smem_base + (unsigned)((WIDE ? (tile % NB) * TILEB : buf * 2 * TILEB) + wave * LDW * 1024);
+        const unsigned kd = smem_base + (unsigned)((ACC ? (tile % NB) * TILEB : WIDE ? buf * TILEB : buf * 2 * TILEB) + wave * LDW * 1024);
         const unsigned vd = kd + (WIDE ? NB * TILEB : TILEB);
         const unsigned char* const kt = kg + (size_t)tile * BN * p.k_rs;
         const unsigned char* const vt = vg + (size_t)tile * BN * p.v_rs;
         const int last_row = S - 1 - tile * BN;  // of this tile, counted from its first row; >= 0
-        if constexpr (WIDE) {
+        if constexpr (ACC) {
 #pragma unroll
             for (int n = 0; n < LDW; ++n) {
                 const int row = wk_row[n] < last_row ? wk_row[n] : last_row;
@@ -321,9 +339,11 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     // fixed LDS addresses of this lane's fragment reads in buffer 0 (K: per k-step; V: per 32-row block
     // of O^T, first of the two transposed reads); buffer, key-block and key-step offsets are immediates
     // (adding 8, 16 or 32 to a row changes no swizzle key)
-    int rd_k[KS], rd_v[DB];
+    // (wide: the swizzles stay inside 256 bytes, so the second half of a row is the first plus 256)
+    constexpr int NRK = WIDE ? 8 : KS, NRV = WIDE ? 4 : DB;
+    int rd_k[NRK], rd_v[NRV];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
+    for (int ks = 0; ks < NRK; ++ks) {
         rd_k[ks] = (int)smem_base + k_off<W>(l32, ks * 2 + h);
         asm volatile("" : "+v"(rd_k[ks]));
     }
@@ -331,12 +351,14 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         const int i16 = lane & 15;
         const int key = 4 * h + (i16 >> 2);
 #pragma unroll
-        for (int db = 0; db < DB; ++db) {
+        for (int db = 0; db < NRV; ++db) {
             const int d = 32 * db + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
-            rd_v[db] = (int)smem_base + v_off<W>(key, d >> 3) + (d & 7) * 2;
+            rd_v[db] = (int)smem_base + v_off<W>(key, d >> 3) + (d & 7) * 2 + (PAIR ? NB * TILEB : 0);
             asm volatile("" : "+v"(rd_v[db]));
         }
     }
+    auto k_at = [&](int ks) { return rd_k[ks % NRK] + ks / NRK * 256; };
+    auto v_at = [&](int db) { return rd_v[db % NRV] + db / NRV * 256; };
 
     f32x16_t oacc[DB];
 #pragma unroll
@@ -362,8 +384,10 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         // Q must be in its registers before the tile loads start: the compiler's own wait for Q would
         // otherwise also wait for every tile load issued before it.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        for (int t = 0; t < NB - 1 && t < ntiles; ++t)
-            issue_tile(t);
+        static_for<0, NB - 1>([&](auto TC) {
+            if (decltype(TC)::value < ntiles)
+                issue_tile(decltype(TC)::value, decltype(TC)::value);
+        });
         wait_tiles(ntiles - 1);
         tile_barrier();
     } else {
@@ -376,19 +400,19 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         pin_q(cpr_late);                    // Q and the first tiles share one round trip to memory
     }
 
-    // One key tile.  D <= 128: UC = j & 1 as a constant -- the driver loop below is unrolled over the two
-    // LDS buffers, so the tile's LDS offsets are immediates.  D = 256 keeps one copy of its (long) body
-    // and adds the buffer offset at run time.
-    constexpr int NU = WIDE ? 1 : NB2;
+    // One key tile.  UC = j mod the number of buffers as a constant -- the driver loop below is unrolled over
+    // the LDS buffers, so the tile's LDS offsets are immediates.  The four-wavefront wide shape keeps one copy of
+    // its (long) body and adds the buffer offset at run time.
+    constexpr int NU = ACC ? 1 : PAIR ? NB : NB2;
     auto step = [&](auto UC, int j) {
         constexpr int U = decltype(UC)::value;
-        const int KT = WIDE ? (j % NB) * TILEB : U * 2 * TILEB;   // byte offset of this step's K tile
-        const int VT = WIDE ? KT + NB * TILEB : KT + TILEB;
+        const int KT = ACC ? (j % NB) * TILEB : PAIR ? U * TILEB : U * 2 * TILEB;   // byte offset of this step's K tile
+        const int VT = ACC ? KT + NB * TILEB : PAIR ? KT : KT + TILEB;
         const int kv0 = j * BN;
         if constexpr (WIDE) {
             // buffer (j + NB - 1) % NB was last read in step j - 1, which every wavefront has left
             if (j + NB - 1 < ntiles)
-                issue_tile(j + NB - 1);
+                issue_tile(j + NB - 1, PAIR ? (U + NB - 1) % NB : 0);
             if constexpr (SAFE_SYNC)
                 tile_barrier();  // checking build: nothing in flight while the step computes
         } else {
@@ -414,7 +438,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
             f32x16_t sacc[KB];
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
-                if constexpr (WIDE) {
+                if constexpr (ACC) {
                     // The compiler moves nothing across the asm MFMAs, so the fragment reads are put
                     // KPF MFMAs ahead of their use by hand.  Measured at S = 16384: reading each fragment
                     // right before its MFMA exposes the LDS latency 16 times per step (714 TFLOP/s), one
@@ -425,11 +449,11 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
                     i32x4_t kf[KS];
 #pragma unroll
                     for (int ks = 0; ks < KPF; ++ks)
-                        kf[ks] = *(const NAUT_LDS i32x4_t*)(uintptr_t)(rd_k[ks] + KT + kb * 32 * ROWB);
+                        kf[ks] = *(const NAUT_LDS i32x4_t*)(uintptr_t)(k_at(ks) + KT + kb * 32 * ROWB);
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) {
                         if (ks + KPF < KS)
-                            kf[ks + KPF] = *(const NAUT_LDS i32x4_t*)(uintptr_t)(rd_k[ks + KPF] + KT + kb * 32 * ROWB);
+                            kf[ks + KPF] = *(const NAUT_LDS i32x4_t*)(uintptr_t)(k_at(ks + KPF) + KT + kb * 32 * ROWB);
                         if (ks == 0)
                             XMfma<DT_IN>::first(sacc[kb], kf[ks], qf[ks]);
                         else
@@ -442,7 +466,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
                         sacc[kb][r] = 0.f;
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) {
-                        const i32x4_t kf = *(const NAUT_LDS i32x4_t*)(uintptr_t)(rd_k[ks] + KT + kb * 32 * ROWB);
+                        const i32x4_t kf = *(const NAUT_LDS i32x4_t*)(uintptr_t)(k_at(ks) + KT + kb * 32 * ROWB);
                         sacc[kb] = T::mfma(kf, qf[ks], sacc[kb]);
                     }
                 }
@@ -508,7 +532,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
                               T::pack2(sacc[kb][r0 + 4], sacc[kb][r0 + 5]), T::pack2(sacc[kb][r0 + 6], sacc[kb][r0 + 7])};
 #pragma unroll
                 for (int db = 0; db < DB; ++db) {
-                    const int a = rd_v[db] + VT + t * 16 * ROWB;
+                    const int a = v_at(db) + VT + t * 16 * ROWB;
                     const i16x4_t r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((NAUT_LDS i16x4_t*)(uintptr_t)a);
                     const i16x4_t r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((NAUT_LDS i16x4_t*)(uintptr_t)(a + 8 * ROWB));
                     const i32x2_t lo = __builtin_bit_cast(i32x2_t, r0), hi = __builtin_bit_cast(i32x2_t, r1);
@@ -537,6 +561,8 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
             // read of this step has been consumed by its MFMA, and the fence of __syncthreads()
             // would wait for all tile loads in flight.
             wait_tiles(ntiles - 2 - j);
+            if constexpr (PAIR)
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // nothing is left to wait for unless the compiler moved an MFMA
             tile_barrier();
         }
     };
@@ -563,7 +589,7 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         // each.  The tiles are dead after the loop's last barrier (every tile load has landed, every
         // fragment has been consumed); each wavefront stages its 32 rows in its own part of them.
         constexpr int CPRO = CPR, R256 = ROWB >= 256 ? 1 : 256 / ROWB;
-        static_assert(NWAVES * 32 * ROWB <= (int)sizeof(smem), "staging rows must fit the tile buffers");
+        static_assert(NWV * 32 * ROWB <= (int)sizeof(smem), "staging rows must fit the tile buffers");
         // Every address below derives from this copy of the lane id, which exists only from here on: nothing
         // of the epilogue can be computed before the key loop and held in registers across it.
         int ln = lane;
@@ -642,11 +668,6 @@ __global__ __launch_bounds__(NTHREADS, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
 #ifndef NAUT_PF
 #define NAUT_PF 3
 #endif
-#ifndef NAUT_HAO
-#define NAUT_HAO 8
-#endif
-constexpr int HEADS_AT_ONCE = NAUT_HAO;
-constexpr int BM2 = 256;
 constexpr int LA = 3;           // tile loads are issued this many iterations ahead of their use
 constexpr int NBUF = LA + 1;    // LDS buffers per operand
 constexpr float M_INIT = -1.0e30f;  // finite stand-in for "no maximum yet": keeps -inf - (-inf) out
@@ -1363,6 +1384,22 @@ __global__ __launch_bounds__(NWV * 64, 1) void naut_fwd_kernel_v2(const Params p
 enum Variant { V_W8Q32 = 0, V_W4Q64 = 1, V_BM128 = 2 };
 constexpr const char* kVariantName[3] = {"fwd_bm256_w8q32_bn64", "fwd_bm256_w4q64_bn64", "fwd_bm128_w4q32_bn64"};
 
+// D > 128: eight wavefronts per work-group, or four (V_BM128) where all 128-query work-groups run at once, one per CU.
+// With the causal mask the second round's work-groups are short and start as the first ones end: two rounds still
+// count as one.  Measured at D = 256 (us, four / eight wavefronts): one head set of 32, S = 1024, no mask (256 of 128
+// queries) 47.5 / 55.6, S = 1500 (384) 115.8 / 81.0; causal, S = 2048 (512) 92.5 / 100.0, 64 heads, S = 1024 (512)
+// 58.4 / 56.7, S = 1500 (768) 115.8 / 85.8; D = 192 draws the line in the same place.
+inline int wide_variant(int S, long long nbh, int causal)
+{
+    if (const char* e = getenv("NAUT_ATTN_VARIANT")) {  // the names that have no wide form choose nothing here
+        if (!strcmp(e, "w8q32"))
+            return V_W8Q32;
+        if (!strcmp(e, "bm128"))
+            return V_BM128;
+    }
+    return nbh * ((S + BM - 1) / BM) <= (causal ? 512 : 256) ? V_BM128 : V_W8Q32;
+}
+
 inline int pick_variant(int S, long long nbh, int D, int causal)
 {
     if (const char* e = getenv("NAUT_ATTN_VARIANT")) {
@@ -1399,8 +1436,7 @@ template <int D, int DT_IN, int DT_OUT>
 int launch(const Params& p, int causal, hipStream_t stream)
 {
     const long long nbh = (long long)p.B * p.Hq;
-    // The pipelined kernel exists for D <= 128; wider heads always take the 128-query kernel.
-    const int variant = D > 128 ? V_BM128 : pick_variant(p.S, nbh, D, causal);
+    const int variant = D > 128 ? wide_variant(p.S, nbh, causal) : pick_variant(p.S, nbh, D, causal);
     if (variant < 0)
         return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64 or bm128)");
     const long long nblocks = nbh * (variant == V_BM128 ? p.nqt : p.nqt2);
@@ -1424,6 +1460,14 @@ int launch(const Params& p, int causal, hipStream_t stream)
         } else if (variant == V_W4Q64) {
 #define NAUT_TAIL , 2, 4
             NAUT_LAUNCH(naut_fwd_kernel_v2, layout_width(D), 256);
+#undef NAUT_TAIL
+            launched = true;
+        }
+    }
+    if constexpr (D > 128) {
+        if (variant == V_W8Q32) {
+#define NAUT_TAIL , 8
+            NAUT_LAUNCH(naut_fwd_kernel_bm128, D, 512);
 #undef NAUT_TAIL
             launched = true;
         }

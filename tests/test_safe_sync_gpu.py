@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2604_14825_amd import binding as nb
 from paper_2604_14825_amd import synth
 
@@ -107,6 +108,33 @@ def test_wide_head_bit_identical(D, S, causal, idt, odt):
     q, k, v = make(2, 4, 2, S, D, idt, 23000 + S)
     print("safe-sync wide", D, S, causal, flush=True)
     both_prefill(q, k, v, idt, odt, causal, 1.0 / math.sqrt(D), "wide D=%d S=%d" % (D, S))
+
+
+@pytest.mark.parametrize("D,idt,odt", [(256, synth.BF16, synth.BF16), (192, synth.F16, synth.F16), (136, synth.BF16, synth.F32)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_wide_head_eight_wavefronts(D, idt, odt, causal, monkeypatch):
+    """The eight-wavefront shape of the wide heads at every phase of its ring of four 32-key buffers, with and without
+    a ragged tail, on one, two and three 256-query tiles: both builds, the four-wavefront shape (the same tiles in the
+    same order: bit-identical) and the oracle."""
+    for S in [32 * t + e for t in (1, 2, 3, 4, 5) for e in (-1, 0, 1)] + [255, 256, 257, 600]:
+        q, k, v = make(1, 2, 1, S, D, idt, 29000 + S)
+        qd, kd, vd = (gu.to_device(a, idt) for a in (q, k, v))
+        st = [t.stride(a) for t in (qd, kd, vd, qd) for a in (0, 1, 2)]
+        outs = []
+        print("wide, eight wavefronts", D, causal, S, flush=True)
+        for L, variant in ((libs()[0], "w8q32"), (libs()[1], "w8q32"), (libs()[0], "bm128")):
+            monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
+            o = torch.full((1, 2, S, D), float("nan"), dtype=gu.TORCH_DT[odt], device="cuda")
+            lse = torch.full((1, 2, S), float("nan"), dtype=torch.float32, device="cuda")
+            rc = L.naut_attn_fwd_strided(qd.data_ptr(), kd.data_ptr(), vd.data_ptr(), o.data_ptr(), lse.data_ptr(), 1, 2, 1, S, D,
+                                         int(causal), 1.0 / math.sqrt(D), None, idt, odt, nb.NautStrides(*st))
+            assert rc == 0, L.naut_last_error_string()
+            torch.cuda.synchronize()
+            outs.append((o.double().cpu().numpy(), lse.double().cpu().numpy()))
+        for x in outs[1:]:
+            assert np.array_equal(outs[0][0], x[0]) and np.array_equal(outs[0][1], x[1]), "D=%d S=%d" % (D, S)
+        o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, 1.0 / math.sqrt(D))
+        gu.check(outs[0][0], outs[0][1], o_ref, lse_ref, "D=%d S=%d" % (D, S))
 
 
 def test_long_sequence_bit_identical():
