@@ -69,6 +69,7 @@ constexpr int HEADS_AT_ONCE = NAUT_HAO;  // (batch, head) pairs an XCD works on 
 constexpr int NWAVES = 4;
 constexpr int NTHREADS = NWAVES * 64;
 constexpr float RESCALE_TAU = 6.0f;  // log2 units
+constexpr float M_INIT = -1.0e30f;   // finite stand-in for "no maximum yet": keeps -inf - (-inf) out
 constexpr float P_LIMIT = 1024.0f;   // a block's per-lane row sum above this moves the reference maximum
 
 // The kernels are compiled for head dimensions 64, 80, 96, 128, 192 and 256; a head in between runs on the next
@@ -148,12 +149,14 @@ struct XMfma<NAUT_F16> {
 //       MFMAs in asm.  It is bound by the dependences of its one instruction stream (46 % of the wavefront time is
 //       waiting), but one work-group of it takes 0.8 times as long as one of the other, so it stays for grids that do
 //       not fill the chip (see wide_variant).
+// NG key groups of NWV wavefronts (D <= 128; see key_groups): group g takes key tiles g, g + NG, ... through tile
+// buffers of its own, and the partial (O, m, l) of the groups are merged through LDS at the end.
 // S = 16384, 32 heads, causal, D = 256: 5281 us (833 TFLOP/s) on four wavefronts, 3920 us (1122) on eight, which is
 // where the clock the chip sustains under matrix load stops the D = 128 kernel too; D = 192, 4x64/8 heads,
 // S = 3835: 2250 -> 1463 us.  Outputs are bit-identical (same tiles, same order).
 
-template <int D, int DT_IN, int DT_OUT, bool CAUSAL, int NWV = NWAVES>
-__global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm128(const Params p)
+template <int D, int DT_IN, int DT_OUT, bool CAUSAL, int NWV = NWAVES, int NG = 1>
+__global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm128(const Params p)
 {
     using T = In<DT_IN>;
     constexpr int BM = NWV * 32;             // queries per work-group (hides the file-scope value)
@@ -178,12 +181,17 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     constexpr int NB2 = NAUT_K1_NBUF;              // buffers per operand (D <= 128)
     constexpr int LDW = TILEB / 1024 / NWV;        // direct loads (1 KB each) per wavefront per tile
     static_assert(LDW >= 1 && (NB2 - 1) * 2 * LDW < 64, "every wavefront loads; vmcnt field");
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[(WIDE ? 2 * NB : 2 * NB2) * TILEB];
-    __shared__ float dl_lds[NWV * 64];
+    static_assert(NG == 1 || !WIDE, "key groups: D <= 128");
+    constexpr int RINGB = (WIDE ? 2 * NB : 2 * NB2) * TILEB;  // bytes of a key group's tile buffers
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[NG * RINGB];
+    __shared__ float dl_lds[NG * NWV * 64];
+    __shared__ float ml_lds[NG > 1 ? (NG - 1) * NWV * 64 * 2 : 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: it feeds scalar operands of the tile loads
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: it feeds scalar operands of the tile loads
+    const int wave = NG == 1 ? wave_wg : wave_wg % NWV;           // inside its key group
+    const int grp = NG == 1 ? 0 : wave_wg / NWV;
     const int l32 = lane & 31;
     const int h = lane >> 5;
 
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     };
     // wide: (row, byte in the row) per load; D <= 128: the byte offset inside a whole tile
     int wk_row[LDW], wk_col[LDW], wv_row[LDW], wv_col[LDW];
-    const unsigned smem_base = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem;
+    const unsigned smem_base = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem + (unsigned)(grp * RINGB);
 #pragma unroll
     for (int n = 0; n < LDW; ++n) {
         source_of(n, wk_row[n], wk_col[n], wv_row[n], wv_col[n]);
@@ -287,6 +295,7 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         }
     }
     const int last_tile = (S + BN - 1) / BN - 1;  // of the sequence: the only one that can be ragged
+    const int my_tiles = (ntiles - grp + NG - 1) / NG;  // of this key group: grp, grp + NG, ...
     // The address of a load is the tile's base, a 64-bit wave-uniform pointer, plus a 32-bit lane offset inside
     // the tile (at most BN rows of the largest row stride the entry point admits); rows beyond the end of the
     // sequence re-read its last row.
@@ -366,7 +375,7 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
 #pragma unroll
         for (int r = 0; r < 16; ++r)
             oacc[db][r] = 0.f;
-    float m_run = -INFINITY;  // running max, in the exp2 domain (already times c)
+    float m_run = NG == 1 ? -INFINITY : M_INIT;  // running max, in the exp2 domain (already times c)
     float l_run = 0.f;        // this lane's share of the running sum (its 16 of every 32 keys)
     // What the sum of P as rounded for the second product, the divisor of O, has over l (this lane's share; see
     // "the two sums" in kernel 2).  It is touched only in rare blocks and in the epilogue, so it lives in a word
@@ -375,7 +384,7 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
     // (its index is re-derived from the hardware lane count where it is used: no register holds it either)
     auto dl_slot = [&]() -> float& {
         const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        return dl_lds[wave * 64 + ln];
+        return dl_lds[wave_wg * 64 + ln];
     };
     dl_slot() = 0.f;
     const float c = p.c;
@@ -392,8 +401,8 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         tile_barrier();
     } else {
         static_for<0, NB2 - 1>([&](auto TC) {
-            if (decltype(TC)::value < ntiles)
-                issue_tile(decltype(TC)::value, decltype(TC)::value);
+            if (decltype(TC)::value < my_tiles)
+                issue_tile(decltype(TC)::value * NG + grp, decltype(TC)::value);
         });
         int cpr_late = cpr;
         asm volatile("" : "+s"(cpr_late));  // ordered after the asm of the tile loads: so is everything that uses it
@@ -408,7 +417,7 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         constexpr int U = decltype(UC)::value;
         const int KT = ACC ? (j % NB) * TILEB : PAIR ? U * TILEB : U * 2 * TILEB;   // byte offset of this step's K tile
         const int VT = ACC ? KT + NB * TILEB : PAIR ? KT : KT + TILEB;
-        const int kv0 = j * BN;
+        const int kv0 = (j * NG + grp) * BN;
         if constexpr (WIDE) {
             // buffer (j + NB - 1) % NB was last read in step j - 1, which every wavefront has left
             if (j + NB - 1 < ntiles)
@@ -418,13 +427,13 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
         } else {
             // Tile j must have landed.  Loads complete in order, so with the tiles j+1 .. j+NB2-2 requested after
             // it this wavefront may leave theirs in flight; near the end fewer were requested and it waits for all.
-            if (j + NB2 - 2 < ntiles)
+            if (j + NB2 - 2 < my_tiles)
                 wait_loads<(NB2 - 2) * 2 * LDW>();
             else
                 wait_loads<0>();
             tile_barrier();  // publishes tile j; every wavefront has left step j-1, whose buffer is refilled next
-            if (j + NB2 - 1 < ntiles)
-                issue_tile(j + NB2 - 1, (U + NB2 - 1) % NB2);
+            if (j + NB2 - 1 < my_tiles)
+                issue_tile((j + NB2 - 1) * NG + grp, (U + NB2 - 1) % NB2);
             if constexpr (SAFE_SYNC) {  // checking build: nothing in flight while the step computes
                 wait_loads<0>();
                 tile_barrier();
@@ -433,7 +442,7 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
 
         // Causal block skipping per wavefront: nothing to do if every key of the tile lies
         // beyond this wavefront's last query.
-        const bool active = !CAUSAL || kv0 <= q_wave0 + 31;
+        const bool active = (!CAUSAL || kv0 <= q_wave0 + 31) && (NG == 1 || j < my_tiles);
         if (active) {
             f32x16_t sacc[KB];
 #pragma unroll
@@ -566,16 +575,61 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
             tile_barrier();
         }
     };
-    for (int j0 = 0; j0 < ntiles; j0 += NU) {
+    const int nsteps = (ntiles + NG - 1) / NG;  // of the first group, which has the most: all meet the same barriers
+    for (int j0 = 0; j0 < nsteps; j0 += NU) {
         static_for<0, NU>([&](auto UC) {
             const int j = j0 + decltype(UC)::value;
-            if (j < ntiles)  // uniform over the work-group
+            if (j < nsteps)  // uniform over the work-group
                 step(UC, j);
         });
     }
 
     if constexpr (!WIDE)
         __syncthreads();  // every wavefront has left the last step: the tiles are dead, the epilogue stages O in them
+    if constexpr (NG > 1) {
+        // Split-merge of the key groups: the others leave O, m and l (dl is in LDS already) in the layout they hold
+        // them in, lane by lane, each in its own dead tiles; the first group's wavefronts add them up and store.
+        static_assert(NWV * DB * 16 * 64 * 4 <= RINGB, "a group's O fits its tile buffers");
+        constexpr int OW = DB * 16 * 64;  // floats per wavefront
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // as in the epilogue: no address of the merge is held across the key loop
+        if (grp > 0) {
+            float* const mo = (float*)(smem + grp * RINGB) + wave * OW;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *(f32x4_t*)(mo + ((db * 4 + g) * 64 + ln) * 4) =
+                        f32x4_t{oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]};
+            float* const ml = ml_lds + ((grp - 1) * NWV + wave) * 128 + ln;
+            ml[0] = m_run;
+            ml[64] = l_run;
+        }
+        __syncthreads();
+        if (grp > 0)
+            return;
+#pragma unroll 1  // one group's partials in registers at a time
+        for (int o = 1; o < NG; ++o) {
+            const float* const ml = ml_lds + ((o - 1) * NWV + wave) * 128 + ln;
+            const float* const mo = (const float*)(smem + o * RINGB) + wave * OW;
+            // The halves of a row hold the same maximum, and key 0, which every row sees, is the first group's.
+            const float m_new = fmaxf(m_run, ml[0]);
+            const float f0 = __builtin_amdgcn_exp2f(m_run - m_new), f1 = __builtin_amdgcn_exp2f(ml[0] - m_new);
+            m_run = m_new;
+            l_run = l_run * f0 + ml[64] * f1;
+            float& dl = dl_slot();
+            dl = dl * f0 + dl_lds[(o * NWV + wave) * 64 + ln] * f1;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const f32x4_t x = *(const f32x4_t*)(mo + ((db * 4 + g) * 64 + ln) * 4);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        oacc[db][4 * g + i] = oacc[db][4 * g + i] * f0 + x[i] * f1;
+                }
+        }
+    }
     // Epilogue: one division by l (the per-step divide/multiply pairs telescope away), lse, store.
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     const float dl_run = dl_slot();
@@ -670,7 +724,6 @@ __global__ __launch_bounds__(NWV * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm1
 #endif
 constexpr int LA = 3;           // tile loads are issued this many iterations ahead of their use
 constexpr int NBUF = LA + 1;    // LDS buffers per operand
-constexpr float M_INIT = -1.0e30f;  // finite stand-in for "no maximum yet": keeps -inf - (-inf) out
 
 // sum over the two 32-lane halves (same exchange as half_max)
 __device__ __forceinline__ float half_sum(float x)
@@ -1432,6 +1485,19 @@ inline int pick_variant(int S, long long nbh, int D, int causal)
     return (avg_keys >= 8192 && wg256 < 1024) ? V_W8Q32 : V_BM128;
 }
 
+// D <= 128, 128-query work-groups: key groups per work-group.  A grid that leaves each CU at most one work-group (with
+// the mask: two, whose second round is short) leaves half of its wavefront slots idle, and the time is that of the longest
+// key loop; two groups of four wavefronts halve that loop.  Below nine tiles the merge costs what the shorter loop
+// saves (kernel time at eight tiles, 32 heads, causal, D = 128: 14.9 us with one group, 14.4 with two; at two tiles
+// 8.3 / 9.2).  Measured with one / two groups: 32 heads, S = 1003, causal, D = 128 23.4 / 20.9 us; 8 heads, S = 2048 39.9 /
+// 33.3 (D = 64: 27.4 / 23.1); 32 heads, S = 2048 (512 work-groups), causal 47.4 / 45.8, D = 64 30.5 / 28.9; without the
+// mask 256 work-groups 23.1 / 23.3 (D = 64: 15.7 / 14.8), 512 127.8 / 135.0.  Four groups (D = 64) gain 1 us more on the
+// smallest grids only.
+inline int key_groups(int S, long long nbh, int causal)
+{
+    return S > 8 * BN && nbh * ((S + BM - 1) / BM) <= (causal ? 512 : 256) ? 2 : 1;
+}
+
 template <int D, int DT_IN, int DT_OUT>
 int launch(const Params& p, int causal, hipStream_t stream)
 {
@@ -1460,6 +1526,11 @@ int launch(const Params& p, int causal, hipStream_t stream)
         } else if (variant == V_W4Q64) {
 #define NAUT_TAIL , 2, 4
             NAUT_LAUNCH(naut_fwd_kernel_v2, layout_width(D), 256);
+#undef NAUT_TAIL
+            launched = true;
+        } else if (key_groups(p.S, nbh, causal) == 2) {
+#define NAUT_TAIL , 4, 2
+            NAUT_LAUNCH(naut_fwd_kernel_bm128, D, 512);
 #undef NAUT_TAIL
             launched = true;
         }

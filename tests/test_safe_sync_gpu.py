@@ -137,6 +137,31 @@ def test_wide_head_eight_wavefronts(D, idt, odt, causal, monkeypatch):
         gu.check(outs[0][0], outs[0][1], o_ref, lse_ref, "D=%d S=%d" % (D, S))
 
 
+@pytest.mark.parametrize("D,idt,odt", [(64, synth.BF16, synth.F32), (80, synth.F16, synth.F16), (128, synth.BF16, synth.BF16)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_key_groups(D, idt, odt, causal, monkeypatch):
+    """Small grids with more than eight key tiles run on two key groups: odd and even tile counts, ragged tails, a last
+    step that only the first group has, rows that see keys of the first group alone; both builds and the oracle."""
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "bm128")
+    for S in (512, 513, 575, 576, 577, 640, 641, 703, 1024, 1025):
+        q, k, v = make(1, 2, 1, S, D, idt, 30000 + S)
+        qd, kd, vd = (gu.to_device(a, idt) for a in (q, k, v))
+        st = [t.stride(a) for t in (qd, kd, vd, qd) for a in (0, 1, 2)]
+        outs = []
+        print("key groups", D, causal, S, flush=True)
+        for L in libs():
+            o = torch.full((1, 2, S, D), float("nan"), dtype=gu.TORCH_DT[odt], device="cuda")
+            lse = torch.full((1, 2, S), float("nan"), dtype=torch.float32, device="cuda")
+            rc = L.naut_attn_fwd_strided(qd.data_ptr(), kd.data_ptr(), vd.data_ptr(), o.data_ptr(), lse.data_ptr(), 1, 2, 1, S, D,
+                                         int(causal), 1.0 / math.sqrt(D), None, idt, odt, nb.NautStrides(*st))
+            assert rc == 0, L.naut_last_error_string()
+            torch.cuda.synchronize()
+            outs.append((o.double().cpu().numpy(), lse.double().cpu().numpy()))
+        assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1]), "D=%d S=%d" % (D, S)
+        o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, 1.0 / math.sqrt(D))
+        gu.check(outs[0][0], outs[0][1], o_ref, lse_ref, "D=%d S=%d" % (D, S))
+
+
 def test_long_sequence_bit_identical():
     """One long causal head group on the pipelined kernel: hundreds of iterations per work-group."""
     q, k, v = make(1, 8, 8, 8192, 128, synth.BF16, 24000)
