@@ -21,7 +21,7 @@
 //     the factor cancels in O / l.  The conversion does not saturate (it makes NaN), hence the bound.
 //
 // Work decomposition as the 128-query kernel of naut_attn_kernels.h: 4 wavefronts x 32 queries per
-// work-group, 64-key tiles.  K and V tiles go straight from global memory to LDS (global_load_lds_dwordx4,
+// work-group (two such groups on small grids), 64-key tiles.  K and V tiles go straight from global memory to LDS (global_load_lds_dwordx4,
 // the swizzle of the LDS layouts applied to the source address), F8_NBUF - 1 tiles ahead over a ring of
 // F8_NBUF buffers per operand: every wavefront waits for its own loads of the tile about to be used (vmcnt),
 // one barrier publishes them, and the buffer read in the previous step is refilled right after it.
@@ -74,9 +74,12 @@ struct Fp8Params {
 
 // STRIDED = false: contiguous [B][H][S][D] tensors, every stride a compile-time constant (the launch
 // parameters' strides are not read); true: strides from the launch parameters.
-template <int D, bool CAUSAL, bool STRIDED>
-__global__ __launch_bounds__(F8_THREADS, 2) void naut_fwd_kernel_fp8(const Fp8Params p)
+// NG key groups of four wavefronts (see key_groups): group g takes key tiles g, g + NG, ... through tile buffers of its
+// own, and the partial (O, m, l) of the groups are merged through LDS at the end.
+template <int D, bool CAUSAL, bool STRIDED, int NG>
+__global__ __launch_bounds__(NG * F8_THREADS, NG == 1 ? 2 : 1) void naut_fwd_kernel_fp8(const Fp8Params p)
 {
+    static_assert(NG == 1 || NG == 2, "the merge stages one group's O");
     constexpr int TILEB = F8_BN * D;            // bytes per K or V tile
     constexpr int CPR16 = D / 16;               // 16-byte chunks per row
     constexpr int NLDW = TILEB / 1024 / F8_WAVES;  // 1 KB direct loads per wavefront, tile and operand
@@ -86,11 +89,15 @@ __global__ __launch_bounds__(F8_THREADS, 2) void naut_fwd_kernel_fp8(const Fp8Pa
     static_assert(NLDW >= 1, "every wavefront takes part in the tile loads");
     static_assert(LA >= 1 && LA * 2 * NLDW < 64, "vmcnt field");
 
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[F8_NBUF * 2 * TILEB];  // K0 V0 K1 V1 ...
+    constexpr int RINGB = F8_NBUF * 2 * TILEB;    // bytes of a key group's tile buffers
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[NG * RINGB];  // per group: K0 V0 K1 V1 ...
+    __shared__ float ml_lds[NG > 1 ? F8_WAVES * 64 * 2 : 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = NG == 1 ? wave_wg : wave_wg % F8_WAVES;  // inside its key group
+    const int grp = NG == 1 ? 0 : wave_wg / F8_WAVES;
     const int l32 = lane & 31;
     const int h = lane >> 5;
 
@@ -136,6 +143,7 @@ __global__ __launch_bounds__(F8_THREADS, 2) void naut_fwd_kernel_fp8(const Fp8Pa
 
     const int kv_end = CAUSAL ? (S < (qt + 1) * F8_BM ? S : (qt + 1) * F8_BM) : S;
     const int ntiles = (kv_end + F8_BN - 1) / F8_BN;
+    const int my_tiles = (ntiles - grp + NG - 1) / NG;  // of this key group: grp, grp + NG, ...
 
     // Direct global->LDS tile loads.  Load n of a tile fills its physical 16-byte chunks 64n .. 64n+63, lane i
     // the chunk 64n+i, so the lane fetches the logical chunk that k8_off / v8_off place there; wavefront w
@@ -154,7 +162,7 @@ __global__ __launch_bounds__(F8_THREADS, 2) void naut_fwd_kernel_fp8(const Fp8Pa
         k_col[i] = (kc < cpr16 ? kc : cpr16 - 1) * 16;
         v_col[i] = (vc < cpr16 ? vc : cpr16 - 1) * 16;
     }
-    const unsigned smem_base = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem;
+    const unsigned smem_base = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem + (unsigned)(grp * RINGB);
     const unsigned ld_dst = smem_base + (unsigned)(wave * NLDW * 1024);
     const int last_tile = (S + F8_BN - 1) / F8_BN - 1;
     const int rows_last = S - last_tile * F8_BN;  // rows of the sequence's last tile, >= 1
@@ -212,30 +220,30 @@ __global__ __launch_bounds__(F8_THREADS, 2) void naut_fwd_kernel_fp8(const Fp8Pa
 
     // prologue: the first LA tiles
     static_for<0, LA>([&](auto T) {
-        if (decltype(T)::value < ntiles)
-            issue_tile(decltype(T)::value, T);
+        if (decltype(T)::value < my_tiles)
+            issue_tile(decltype(T)::value * NG + grp, T);
     });
 
     // one key tile; BUFC = j % F8_NBUF as a constant (the driver loop below is unrolled over the buffers)
     auto step = [&](auto BUFC, int j) {
         constexpr int BUF = decltype(BUFC)::value;
         constexpr int KT = BUF * 2 * TILEB, VT = KT + TILEB;  // byte offsets of this step's K and V tiles
-        const int kv0 = j * F8_BN;
+        const int kv0 = (j * NG + grp) * F8_BN;
         // Tile j must have landed.  Loads complete in order, so with the tiles j+1 .. j+LA-1 requested after it
         // this wavefront may leave their loads in flight; near the end fewer were requested and it waits for all.
-        if (j + LA - 1 < ntiles)
+        if (j + LA - 1 < my_tiles)
             wait_loads<(LA - 1) * 2 * NLDW>();
         else
             wait_loads<0>();
         tile_barrier();  // publishes tile j; every wavefront is done with the buffer of tile j-1, refilled next
-        if (j + LA < ntiles)
-            issue_tile(j + LA, std::integral_constant<int, (BUF + LA) % F8_NBUF>{});
+        if (j + LA < my_tiles)
+            issue_tile((j + LA) * NG + grp, std::integral_constant<int, (BUF + LA) % F8_NBUF>{});
         if constexpr (SAFE_SYNC) {  // checking build: nothing in flight while a step computes
             wait_loads<0>();
             tile_barrier();
         }
 
-        const bool active = !CAUSAL || kv0 <= q_wave0 + 31;
+        const bool active = (!CAUSAL || kv0 <= q_wave0 + 31) && (NG == 1 || j < my_tiles);
         if (active) {
             f32x16_t sacc[2];
 #pragma unroll
@@ -313,12 +321,51 @@ __global__ __launch_bounds__(F8_THREADS, 2) void naut_fwd_kernel_fp8(const Fp8Pa
             }
         }
     };
-    for (int j = 0; j < ntiles; j += F8_NBUF)
+    const int nsteps = (ntiles + NG - 1) / NG;  // of the first group, which has the most: all meet the same barriers
+    for (int j = 0; j < nsteps; j += F8_NBUF)
         static_for<0, F8_NBUF>([&](auto B_) {
-            if (j + decltype(B_)::value < ntiles)
+            if (j + decltype(B_)::value < nsteps)
                 step(B_, j + decltype(B_)::value);
         });
     __syncthreads();  // the tiles are dead from here on: the epilogue stages O in them
+    if constexpr (NG == 2) {
+        // Split-merge of the key groups: the second leaves O, m and l in the layout it holds them in, lane by lane; the
+        // first adds them up and stores.  The O lies behind the part of the tiles that the epilogue stages rows in, which
+        // a wavefront may reach while another still merges.
+        constexpr int OB = F8_WAVES * DB * 16 * 64 * 4;
+        static_assert(OB + F8_WAVES * 32 * D * 2 <= NG * RINGB, "a group's O and the staged rows fit the tile buffers");
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // no address of the merge is held across the key loop
+        float* const mo = (float*)(smem + NG * RINGB - OB) + wave * DB * 16 * 64 + ln * 4;
+        float* const ml = ml_lds + wave * 128 + ln;
+        if (grp > 0) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *(f32x4_t*)(mo + (db * 4 + g) * 256) =
+                        f32x4_t{oacc[db][4 * g], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]};
+            ml[0] = m_run;
+            ml[64] = l_run;
+        }
+        __syncthreads();
+        if (grp > 0)
+            return;
+        // The halves of a row hold the same maximum, and key 0, which every row sees, is the first group's.
+        const float m_new = fmaxf(m_run, ml[0]);
+        const float f0 = __builtin_amdgcn_exp2f(m_run - m_new), f1 = __builtin_amdgcn_exp2f(ml[0] - m_new);
+        m_run = m_new;
+        l_run = l_run * f0 + ml[64] * f1;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4_t x = *(const f32x4_t*)(mo + (db * 4 + g) * 256);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    oacc[db][4 * g + i] = oacc[db][4 * g + i] * f0 + x[i] * f1;
+            }
+    }
 
     // Epilogue: one division by l (the 2^7 of P cancels), times descale_v; lse undoes the shift.
     const float l_tot = l_run + __shfl_xor(l_run, 32);
@@ -367,6 +414,18 @@ __global__ __launch_bounds__(F8_THREADS, 2) void naut_fwd_kernel_fp8(const Fp8Pa
                 *(i32x4_a8*)(o_bh + (size_t)q * o_rs + (ln % CPRO) * 16) = rows[i];
         }
     }
+}
+
+// Key groups per work-group.  A grid of at most one work-group per CU (with the causal mask: two, whose second round is
+// short) runs one wavefront per SIMD, which waits for its own LDS reads, softmax and MFMAs, and takes as long as its
+// longest key loop; two groups of four wavefronts halve that loop.  Measured (us a call, one / two groups, D = 128): 32
+// heads, S = 1003, causal 17.0 / 15.2; 8 heads, S = 2048 27.5 / 22.8; 8 heads, S = 8192 (512 work-groups) 102.5 / 85.0;
+// 32 heads, S = 2048 (512) 30.6 / 29.8; no mask, 8 heads, S = 4096 (256) 50.1 / 41.4.  Beyond the line the chip holds
+// three one-group work-groups per CU: 40 heads, S = 1024, no mask (320) 21.5 / 26.6; 32 heads, S = 3000, causal (768)
+// 49.4 / 58.7.  At eight tiles the two are equal (10.8 / 10.7 at S = 576), so shorter loops keep one group.
+inline int key_groups(int S, long long nblocks, int causal)
+{
+    return S > 8 * F8_BN && nblocks <= (causal ? 512 : 256) ? 2 : 1;
 }
 
 }  // namespace
@@ -450,9 +509,14 @@ int naut_attn_fwd_fp8_strided(const void* q, const void* k, const void* v, void*
     const bool strided = D != DK || st->q_b != cs.q_b || st->q_h != cs.q_h || st->q_s != cs.q_s || st->k_b != cs.k_b ||
                          st->k_h != cs.k_h || st->k_s != cs.k_s || st->v_b != cs.v_b || st->v_h != cs.v_h ||
                          st->v_s != cs.v_s || st->o_b != cs.o_b || st->o_h != cs.o_h || st->o_s != cs.o_s;
+    const int ng = key_groups(S, nblocks, causal);
 #define NAUT_F8_LAUNCH(DD, CC, SS)                                                          \
-    if (DK == DD && (causal != 0) == CC && strided == SS)                                   \
-        hipLaunchKernelGGL((naut_fwd_kernel_fp8<DD, CC, SS>), grid, dim3(F8_THREADS), 0, hs, p);
+    if (DK == DD && (causal != 0) == CC && strided == SS) {                                 \
+        if (ng == 2)                                                                        \
+            hipLaunchKernelGGL((naut_fwd_kernel_fp8<DD, CC, SS, 2>), grid, dim3(2 * F8_THREADS), 0, hs, p); \
+        else                                                                                \
+            hipLaunchKernelGGL((naut_fwd_kernel_fp8<DD, CC, SS, 1>), grid, dim3(F8_THREADS), 0, hs, p); \
+    }
     NAUT_F8_LAUNCH(128, true, false)
     NAUT_F8_LAUNCH(128, false, false)
     NAUT_F8_LAUNCH(64, true, false)

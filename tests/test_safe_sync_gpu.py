@@ -239,6 +239,42 @@ def test_fp8_every_tile_count_bit_identical():
             assert np.array_equal(outs[0], outs[1]), "fp8 prefill differs at S = %d" % S
 
 
+@pytest.mark.parametrize("D,pad", [(64, 0), (80, 32), (128, 0), (128, 16)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_fp8_key_groups(D, pad, causal):
+    """Small FP8 grids with more than eight key tiles run on two key groups: odd and even tile counts, ragged tails, a
+    last step that only the first group has, wavefronts that see keys of the first group alone, dense and padded rows;
+    both builds and the oracle (bounds of the FP8 tests: 0.07 max|V| for P rounded to E4M3, rms(V)/100 on average)."""
+    dq, dk, dv = F8_SCALES
+    for S in (512, 513, 575, 576, 577, 640, 641, 703, 705, 1024, 1025):
+        q = synth.fill_e4m3(1, 2, S, D, 31000 + S, synth.TAG_Q, dq)
+        k = synth.fill_e4m3(1, 1, S, D, 31000 + S, synth.TAG_K, dk, S // 50, 8.0)
+        v = synth.fill_e4m3(1, 1, S, D, 31000 + S, synth.TAG_V, dv)
+
+        def padded(a):
+            buf = np.full(a.shape[:3] + (D + pad,), 0x7F, dtype=np.uint8)
+            buf[..., :D] = a
+            return torch.from_numpy(buf).cuda()[..., :D]
+        qd, kd, vd = padded(q), padded(k), padded(v)
+        outs = []
+        print("fp8 key groups", D, pad, causal, S, flush=True)
+        for L in libs():
+            o = torch.full((1, 2, S, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+            lse = torch.full((1, 2, S), float("nan"), dtype=torch.float32, device="cuda")
+            st = [t.stride(a) for t in (qd, kd, vd, o) for a in (0, 1, 2)]
+            rc = L.naut_attn_fwd_fp8_strided(qd.data_ptr(), kd.data_ptr(), vd.data_ptr(), o.data_ptr(), lse.data_ptr(), 1, 2, 1,
+                                             S, D, int(causal), 1.0 / math.sqrt(D), dq, dk, dv, None, nb.NautStrides(*st))
+            assert rc == 0, L.naut_last_error_string()
+            torch.cuda.synchronize()
+            outs.append((o.double().cpu().numpy(), lse.double().cpu().numpy()))
+        assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1]), "D=%d S=%d" % (D, S)
+        o_ref, lse_ref = oracle.attn_rows_e4m3(q, k, v, dq, dk, dv, causal, 1.0 / math.sqrt(D))
+        vf = dv * oracle.decode_e4m3(v)
+        d = np.abs(outs[0][0] - o_ref)
+        assert d.max() <= 0.07 * np.abs(vf).max() and d.mean() <= 1e-2 * math.sqrt((vf ** 2).mean()), "D=%d S=%d" % (D, S)
+        assert (np.abs(outs[0][1] - lse_ref) / np.maximum(1.0, np.abs(lse_ref))).max() <= 1e-3, "D=%d S=%d lse" % (D, S)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D", [(1, 4, 4, 1, 100, 128), (2, 8, 2, 1, 777, 128), (1, 8, 1, 3, 500, 64),
                                             (2, 32, 8, 1, 16384, 128)])
 def test_fp8_decode_bit_identical(B, Hq, Hkv, Sq, Sk, D):
