@@ -160,7 +160,7 @@ const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int 
  * split-merge identity of softmax (the rolling update of Section 4.2/4.3 applied across splits
  * instead of across steps); the partials live in `workspace`, DEVICE memory owned by the caller, 16-byte
  * aligned, of at least naut_attn_decode_workspace_bytes(...) bytes, which the call overwrites and
- * which must not be shared by calls that may overlap.  Two kernels are enqueued on `stream`; nothing
+ * which must not be shared by calls that may overlap.  One or two kernels are enqueued on `stream`; nothing
  * is allocated, nothing is synchronised.  Errors as above (a NULL workspace is NAUT_ERR_NULL, a short one
  * NAUT_ERR_SHAPE).
  */

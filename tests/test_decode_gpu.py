@@ -245,3 +245,41 @@ def test_decode_very_long_cache(Sk, Sq):
     o, lse = gu.run_hip_decode(q, k, v, idt, idt, True, scale)
     o_ref, lse_ref = oracle.attn_cross16(q, k, v, idt, True, scale)
     gu.check(o, lse, o_ref, lse_ref, "decode Sk=%d" % Sk)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D,odt", [
+    (9, 16, 8, 1, 1500, 64, synth.BF16),      # 72 caches: three splits fill a round of 256 work-groups, four start another
+    (33, 8, 8, 1, 2100, 64, synth.F32),       # 264: two or more rounds instead of one and a bit
+    (20, 16, 8, 1, 700, 128, synth.BF16),     # 160: one split, stored without a merge
+    (20, 8, 8, 2, 261, 72, synth.F32),        # the same, a narrow head, fp32 output, two positions
+    (2, 40, 2, 2, 257, 80, synth.BF16),       # forty rows per cache: two chunks, the second partly padding
+    (1, 8, 1, 1, 20000, 128, synth.BF16),     # 79 splits: several batches of the merge
+    (1, 4, 4, 1, 2081, 256, synth.BF16),
+])
+def test_decode_split_counts(B, Hq, Hkv, Sq, Sk, D, odt):
+    """Every kind of split plan against the oracle, and with the least workspace that is taken: what is refused there
+    is an error, what is accepted is right."""
+    scale = 1.0 / math.sqrt(D)
+    q, k, v = make(B, Hq, Hkv, Sq, Sk, D, synth.BF16, 32000 + Sk)
+    qd, kd, vd = (gu.to_device(a, synth.BF16) for a in (q, k, v))
+    o_ref, lse_ref = oracle.attn_cross16(q, k, v, synth.BF16, True, scale)
+    need = nb.decode_workspace_bytes(B, Hq, Hkv, Sq, Sk, D)
+    DK = 64 if D <= 64 else 128 if D <= 128 else 256
+    part = B * Hkv * -(-(Hq // Hkv * Sq) // 32) * 32 * (DK + 2) * 4   # of one split of every cache
+    assert need % part == 0
+    taken = 0
+    for n in range(need // part, 0, -1):
+        o = torch.full((B, Hq, Sq, D + 8), 7.0, dtype=gu.TORCH_DT[odt], device="cuda")
+        lse = torch.full((B, Hq, Sq), float("nan"), dtype=torch.float32, device="cuda")
+        ws = torch.full((n * part,), 0xFF, dtype=torch.uint8, device="cuda")
+        print("decode splits", B, Hq, Hkv, Sq, Sk, D, n, flush=True)
+        try:
+            nb.naut_attn_decode_strided(qd, kd, vd, o[..., :D], lse, True, scale, ws)
+        except nb.NautError as e:
+            assert e.code == nb.NAUT_ERR_SHAPE and n < need // part
+            break
+        torch.cuda.synchronize()
+        taken += 1
+        gu.check(o[..., :D].double().cpu().numpy(), lse.double().cpu().numpy(), o_ref, lse_ref, "splits %d" % n)
+        assert torch.all(o[..., D:] == 7.0).item(), "the gaps between O rows were written"
+    assert taken >= 1
