@@ -161,7 +161,8 @@ const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int 
  * instead of across steps); the partials live in `workspace`, DEVICE memory owned by the caller, 16-byte
  * aligned, of at least naut_attn_decode_workspace_bytes(...) bytes, which the call overwrites and
  * which must not be shared by calls that may overlap.  One or two kernels are enqueued on `stream`; nothing
- * is allocated, nothing is synchronised.  Errors as above (a NULL workspace is NAUT_ERR_NULL, a short one
+ * is allocated, nothing is synchronised.  With less than that many bytes a call splits the keys less finely (the
+ * rounding of the result depends on the split), down to a least size below which it is refused.  Errors as above (a NULL workspace is NAUT_ERR_NULL, a short one
  * NAUT_ERR_SHAPE).
  */
 int naut_attn_decode(const void* q, const void* k, const void* v, void* o, float* lse,

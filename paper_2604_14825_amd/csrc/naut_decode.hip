@@ -46,7 +46,7 @@ constexpr float DEC_M_INIT = -1.0e30f;     // finite stand-in for "no maximum ye
 #ifndef NAUT_DEC_TARGET
 #define NAUT_DEC_TARGET 256
 #endif
-constexpr int DEC_TARGET_WGS = NAUT_DEC_TARGET;  // one work-group per CU: only one is resident at a time (LDS), and a single round measured fastest (256..1024 tried)
+constexpr int DEC_TARGET_WGS = NAUT_DEC_TARGET;  // work-groups that run at a time: one per CU (LDS)
 
 struct DecodeParams {
     const void* q;
@@ -84,7 +84,7 @@ __device__ __forceinline__ float half_sum_f(float x)
 // reuses its own, now idle, region of REGION bytes) and the work-group's partial goes to the workspace.
 // m is the reference maximum the wavefront's l and O are relative to (log2 units).
 // With a single split that partial is the result: it is divided by l and stored as O right here, and there is no merge
-// kernel (32/8 heads, D = 128, 512 keys, B = 40: 27.9 -> 24.5 us).
+// kernel (32/8 heads, D = 128, 512 keys, B = 40: 27.9 -> 24.5 us; B = 12, split in three before: 14.6 -> 12.2).
 template <int D, int REGION, int NW, int DT_IN>
 __device__ __forceinline__ void merge_wavefronts(unsigned char* smem, const f32x16_t (&oacc)[D / 32], float m_run,
                                                  float l_run, const DecodeParams& p, int bhk, int chunk, int split)
@@ -674,7 +674,8 @@ __global__ __launch_bounds__(MRG_THREADS) void naut_decode_merge_kernel(const De
 
 struct Plan {
     int nchunks, nsplit, bps;
-    size_t ws_bytes;
+    size_t ws_bytes;    // workspace asked for
+    size_t ws_least;    // the least that is taken (see make_plan)
 };
 
 // Scratch of naut_attn_decode_static: the split partials live in this file-scope device array instead of a
@@ -712,29 +713,80 @@ void* static_scratch(int* err)
     return ptr;
 }
 
-// D: the width the kernels are compiled for (64, 128 or 256)
-bool make_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, Plan* pl)
+// D: the width the kernels are compiled for (64, 128 or 256); Sk counts keys in units that make a block DEC_BLK of them.
+//
+// How many splits: a work-group occupies a CU (LDS), so the work-groups run in rounds of 256, and a last round of n of
+// them lasts longer than its n/256 of a full round's bytes: one CU streams at most about 2.2 times its even share of the
+// memory's rate.  The candidates are the counts that fill one, two, three or four rounds without starting another; the
+// time of each is priced from three measurements: a full chip takes 2.9 us for 64 KB per CU, a further round about 2 us
+// of fill and drain, the merge kernel with its launch about 7 us (a single split needs none).  Measured with the first
+// count that reaches 256 work-groups, as it was / the one picked here (us a call, 32/8 heads, one position, D = 128):
+// 4096 keys, B = 9 42.7 / 33.6, B = 12 52.0 / 43.2, B = 20 77.0 / 63.8, B = 33 133 / 113, B = 40 139 / 124;
+// 512 keys, B = 12 14.6 / 12.2.  Where base divides 256 the two are the same.
+//
+// The workspace must hold the least count's partials (the first count that reaches 256 work-groups); with less room than
+// the picked count needs, the best candidate that fits is taken.  No count takes more than DEC_MAX_PARTS partials unless
+// the least does, so the 16 MiB static scratch holds the picked count wherever it holds the least (D <= 128).
+constexpr unsigned DEC_MAX_PARTS = 960;
+
+bool make_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int block_bytes, size_t room, Plan* pl)
 {
-    const int W = dec_waves(D);
+    const unsigned W = dec_waves(D);  // 2 or 4
     const long long R = (long long)(Hq / Hkv) * Sq;
     const long long nchunks = (R + DEC_ROWS - 1) / DEC_ROWS;
-    const long long nblk = ((long long)Sk + DEC_BLK - 1) / DEC_BLK;
-    const long long base = (long long)B * Hkv * nchunks;
-    long long nsplit = (DEC_TARGET_WGS + base - 1) / base;
-    const long long max_split = (nblk + 2 * W - 1) / (2 * W);  // at least two blocks per wavefront
-    nsplit = nsplit > max_split ? max_split : nsplit;
-    nsplit = nsplit < 1 ? 1 : nsplit;
-    long long bps = (nblk + nsplit - 1) / nsplit;
-    bps = (bps + W - 1) / W * W;
-    nsplit = (nblk + bps - 1) / bps;
-    if (nchunks > 65535 || (long long)B * Hkv > 65535 || nsplit > 0x7fffffffLL || R > 0x7fffffffLL)
+    if (nchunks > 65535 || (long long)B * Hkv > 65535 || R > 0x7fffffffLL)
         return false;
+    const unsigned nblk = ((unsigned)Sk + DEC_BLK - 1) / DEC_BLK;
+    const unsigned base = (unsigned)B * Hkv * (unsigned)nchunks;
+    const unsigned max_split = (nblk + 2 * W - 1) / (2 * W);  // at least two blocks per wavefront
+    const unsigned part_bytes = DEC_ROWS * (D + 2) * sizeof(float);
+    // a count without empty splits, and its blocks per split
+    auto settle = [&](unsigned n, unsigned* bps) {
+        n = n > max_split ? max_split : n < 1 ? 1 : n;
+        if (n == 1) {
+            *bps = (nblk + W - 1) / W * W;
+            return 1u;
+        }
+        *bps = ((nblk + n - 1) / n + W - 1) / W * W;
+        return (nblk + *bps - 1) / *bps;
+    };
+    unsigned bps;
+    const unsigned first = DEC_TARGET_WGS / base, at_least = first * base == DEC_TARGET_WGS ? first : first + 1;
+    const unsigned least = settle(at_least, &bps);
+    const unsigned parts = base * least;
     pl->nchunks = (int)nchunks;
-    pl->nsplit = (int)nsplit;
+    pl->nsplit = (int)least;
     pl->bps = (int)bps;
-    pl->ws_bytes = (size_t)(base * nsplit) * DEC_ROWS * (D + 2) * sizeof(float);
+    pl->ws_least = pl->ws_bytes = (size_t)parts * part_bytes;
+    // No other candidate: a fuller split would leave a wavefront less than two blocks, or the least fills whole rounds.
+    if (first >= max_split || first * base == DEC_TARGET_WGS || room < pl->ws_least)
+        return true;
+    const unsigned most = parts > DEC_MAX_PARTS ? parts : DEC_MAX_PARTS;
+    const double block_us = block_bytes * (2.9 / 65536.0);  // a block per CU while the whole chip streams
+    double best = 0.0;
+    for (unsigned rounds = 1; rounds <= 4; ++rounds) {
+        unsigned b;
+        const unsigned n = settle(rounds * DEC_TARGET_WGS / base, &b);
+        const unsigned wgs = base * n, full = wgs / DEC_TARGET_WGS, rest = wgs % DEC_TARGET_WGS;
+        if (n > 1 && (wgs > most || (size_t)wgs * part_bytes > room))
+            break;  // so is every later one
+        const double turn = b * block_us, share = rest * (1.0 / DEC_TARGET_WGS);
+        const double us = full * (turn + 2.0) + (rest ? turn * (share > 0.45 ? share : 0.45) + 2.0 : 0.0) + (n > 1 ? 7.0 : 0.0);
+        if (rounds == 1 || us < best) {
+            pl->nsplit = (int)n;
+            pl->bps = (int)b;
+            best = us;
+        }
+        if (n >= max_split)
+            break;
+    }
+    if ((unsigned)pl->nsplit > least)
+        pl->ws_bytes = (size_t)base * pl->nsplit * part_bytes;
     return true;
 }
+
+constexpr int dec_width(int D) { return D <= 64 ? 64 : D <= 128 ? 128 : 256; }
+constexpr int block_bytes16(int D) { return 2 * DEC_BLK * D * 2; }  // K and V of one block
 
 template <int D, int DT_IN, int DT_OUT>
 int launch_decode(const DecodeParams& p, hipStream_t stream)
@@ -762,7 +814,7 @@ size_t naut_attn_decode_workspace_bytes(int B, int Hq, int Hkv, int Sq, int Sk, 
 {
     Plan pl;
     if (B <= 0 || Hq <= 0 || Hkv <= 0 || Sq <= 0 || Sk <= 0 || Hq % Hkv != 0 || D <= 0 || D % 8 != 0 || D > 256 ||
-        !make_plan(B, Hq, Hkv, Sq, Sk, D <= 64 ? 64 : D <= 128 ? 128 : 256, &pl))
+        !make_plan(B, Hq, Hkv, Sq, Sk, dec_width(D), block_bytes16(dec_width(D)), SIZE_MAX, &pl))
         return 0;
     return pl.ws_bytes;
 }
@@ -792,11 +844,11 @@ int decode_16bit(const void* q, const void* k, const void* v, void* o, float* ls
         return fail(NAUT_ERR_UNSUPPORTED, "negative scale is not supported");
     if (D % 8 != 0 || D > 256)
         return fail(NAUT_ERR_UNSUPPORTED, "D must be a multiple of 8, at most 256");
-    const int DK = D <= 64 ? 64 : D <= 128 ? 128 : 256;  // width the kernels are compiled for
+    const int DK = dec_width(D);  // width the kernels are compiled for
     if ((in_dtype != NAUT_BF16 && in_dtype != NAUT_F16) || (out_dtype != in_dtype && out_dtype != NAUT_F32))
         return fail(NAUT_ERR_UNSUPPORTED, "supported dtypes: q/k/v bf16 or f16; o of the same type or f32");
     Plan pl;
-    if (!make_plan(B, Hq, Hkv, Sq, Sk, DK, &pl))
+    if (!make_plan(B, Hq, Hkv, Sq, Sk, DK, block_bytes16(DK), use_static ? DEC_STATIC_BYTES : workspace_bytes, &pl))
         return fail(NAUT_ERR_UNSUPPORTED, "shape exceeds the grid limits");
     if (use_static)
         workspace = nullptr;
@@ -805,17 +857,17 @@ int decode_16bit(const void* q, const void* k, const void* v, void* o, float* ls
     if ((uintptr_t)lse & 3)
         return fail(NAUT_ERR_ALIGN, "lse must be 4-byte aligned");
     if (use_static) {
-        if (pl.ws_bytes > DEC_STATIC_BYTES) {
+        if (pl.ws_least > DEC_STATIC_BYTES) {
             snprintf(g_err, sizeof g_err,
                      "these sizes need %zu bytes of split partials, more than the %zu-byte static scratch of "
                      "naut_attn_decode_static: use naut_attn_decode with a workspace",
-                     pl.ws_bytes, DEC_STATIC_BYTES);
+                     pl.ws_least, DEC_STATIC_BYTES);
             return NAUT_ERR_UNSUPPORTED;
         }
     } else {
         if (!workspace)
             return fail(NAUT_ERR_NULL, "workspace must be a non-NULL device pointer");
-        if (workspace_bytes < pl.ws_bytes)
+        if (workspace_bytes < pl.ws_least)
             return fail(NAUT_ERR_SHAPE, "workspace is smaller than naut_attn_decode_workspace_bytes()");
     }
 
@@ -933,7 +985,7 @@ int naut_attn_decode_fp8_strided(const void* q, const void* k, const void* v, vo
         return fail(NAUT_ERR_UNSUPPORTED, "D must be a multiple of 16, at most 128");
     const int DK = D <= 64 ? 64 : 128;  // width the kernels are compiled for
     Plan pl;  // over 64-key blocks: the plan of a cache half as long in 32-key blocks
-    if (!make_plan(B, Hq, Hkv, Sq, (Sk + 1) / 2, DK, &pl))
+    if (!make_plan(B, Hq, Hkv, Sq, (Sk + 1) / 2, DK, 2 * DEC8_BLK * DK, workspace_bytes, &pl))
         return fail(NAUT_ERR_UNSUPPORTED, "shape exceeds the grid limits");
     if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o | (uintptr_t)workspace) & 15)
         return fail(NAUT_ERR_ALIGN, "q, k, v, o and workspace must be 16-byte aligned");
@@ -941,7 +993,7 @@ int naut_attn_decode_fp8_strided(const void* q, const void* k, const void* v, vo
         return fail(NAUT_ERR_ALIGN, "lse must be 4-byte aligned");
     if (!workspace)
         return fail(NAUT_ERR_NULL, "workspace must be a non-NULL device pointer");
-    if (workspace_bytes < pl.ws_bytes)
+    if (workspace_bytes < pl.ws_least)
         return fail(NAUT_ERR_SHAPE, "workspace is smaller than naut_attn_decode_workspace_bytes()");
 
     naut_strides cs;  // contiguous q, o [B][Hq][Sq][D] and k, v [B][Hkv][Sk][D]
