@@ -149,7 +149,7 @@ struct XMfma<NAUT_F16> {
 //       MFMAs in asm.  It is bound by the dependences of its one instruction stream (46 % of the wavefront time is
 //       waiting), but one work-group of it takes 0.8 times as long as one of the other, so it stays for grids that do
 //       not fill the chip (see wide_variant).
-// NG key groups of NWV wavefronts (D <= 128; see key_groups): group g takes key tiles g, g + NG, ... through tile
+// NG key groups of NWV wavefronts (D <= 128: 2 x 4 or 4 x 2; see key_groups): group g takes key tiles g, g + NG, ... through tile
 // buffers of its own, and the partial (O, m, l) of the groups are merged through LDS at the end.
 // S = 16384, 32 heads, causal, D = 256: 5281 us (833 TFLOP/s) on four wavefronts, 3920 us (1122) on eight, which is
 // where the clock the chip sustains under matrix load stops the D = 128 kernel too; D = 192, 4x64/8 heads,
@@ -160,8 +160,9 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
 {
     using T = In<DT_IN>;
     constexpr int BM = NWV * 32;             // queries per work-group (hides the file-scope value)
-    constexpr int BN = D > 128 ? 32 : 64;    // keys per step (hides the file-scope value used by kernel 2)
     constexpr int W = layout_width(D);       // row width of the LDS layouts
+    // keys per step of a group (hides the file-scope value used by kernel 2); four groups: what their rings leave room for
+    constexpr int BN = D > 128 || (NG == 4 && W == 128) ? 32 : 64;
     constexpr int ROWB = W * 2;              // bytes per K/V row in LDS
     constexpr int TILEB = BN * ROWB;         // bytes per K or V tile
     constexpr int CPR = W / 8;               // 16-byte chunks per row
@@ -176,12 +177,11 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
     constexpr bool WIDE = D > 128;
     constexpr bool ACC = WIDE && NWV == 4;         // O and Q live in the accumulation registers
     constexpr bool PAIR = WIDE && NWV == 8;        // two wavefronts per SIMD on 256 ordinary registers each
-    static_assert(NWV == 4 || WIDE, "eight wavefronts: wide heads only");
+    static_assert(WIDE ? NG == 1 && NWV >= 4 : NWV == 4 || (NWV == 2 && NG == 4), "the shapes that are launched");
     constexpr int NB = 4;                          // buffers per operand (wide)
     constexpr int NB2 = NAUT_K1_NBUF;              // buffers per operand (D <= 128)
     constexpr int LDW = TILEB / 1024 / NWV;        // direct loads (1 KB each) per wavefront per tile
     static_assert(LDW >= 1 && (NB2 - 1) * 2 * LDW < 64, "every wavefront loads; vmcnt field");
-    static_assert(NG == 1 || !WIDE, "key groups: D <= 128");
     constexpr int RINGB = (WIDE ? 2 * NB : 2 * NB2) * TILEB;  // bytes of a key group's tile buffers
     __shared__ __attribute__((aligned(1024))) unsigned char smem[NG * RINGB];
     __shared__ float dl_lds[NG * NWV * 64];
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
     // Tile scheduler: heaviest (last) query tiles first; consecutive block ids walk the
     // (batch, head) axis so that each XCD (block id mod 8) keeps to a fixed subset of heads.
     const int nbh = p.B * p.Hq;
-    const int nqt = NWV == 4 ? p.nqt : p.nqt2;
+    const int nqt = NWV == 4 ? p.nqt : NWV == 8 ? p.nqt2 : (p.S + BM - 1) / BM;
     const int bid = blockIdx.x;
     int qt, bh;
     if (NWV == 8 && (nbh & 7) == 0) {  // as in kernel 2: an XCD's run of heads, a few at a time
@@ -1485,16 +1485,25 @@ inline int pick_variant(int S, long long nbh, int D, int causal)
     return (avg_keys >= 8192 && wg256 < 1024) ? V_W8Q32 : V_BM128;
 }
 
-// D <= 128, 128-query work-groups: key groups per work-group.  A grid that leaves each CU at most one work-group (with
-// the mask: two, whose second round is short) leaves half of its wavefront slots idle, and the time is that of the longest
-// key loop; two groups of four wavefronts halve that loop.  Below nine tiles the merge costs what the shorter loop
-// saves (kernel time at eight tiles, 32 heads, causal, D = 128: 14.9 us with one group, 14.4 with two; at two tiles
-// 8.3 / 9.2).  Measured with one / two groups: 32 heads, S = 1003, causal, D = 128 23.4 / 20.9 us; 8 heads, S = 2048 39.9 /
-// 33.3 (D = 64: 27.4 / 23.1); 32 heads, S = 2048 (512 work-groups), causal 47.4 / 45.8, D = 64 30.5 / 28.9; without the
-// mask 256 work-groups 23.1 / 23.3 (D = 64: 15.7 / 14.8), 512 127.8 / 135.0.  Four groups (D = 64) gain 1 us more on the
-// smallest grids only.
+// D <= 128, the kernel of 32 queries per wavefront: key groups per work-group.  A grid that leaves each CU at most one
+// work-group (with the mask: two, whose second round is short) leaves half of its wavefront slots idle, and the time is
+// that of the longest key loop; two groups of four wavefronts halve that loop, four groups of two quarter it and spread
+// the queries over twice the CUs.
+//   Four groups: 64-query work-groups, one per CU (LDS), all in one round; with the mask also two rounds if the loops are
+//   long enough to even out (the light query tiles go to the CUs that are done first).  Kernel time with one / two / four
+//   groups, D = 128, causal: 8 heads, S = 512 14.2 / 13.5 / 12.0 us, S = 1024 22.5 / 19.8 / 16.2, S = 2048 39.6 / 33.1 /
+//   25.6; 8 heads, S = 4096 (512 work-groups) 74.1 / 60.9 / 52.2 (D = 64: 50.5 / 41.1 / 33.0); 16 heads, S = 2048 (512)
+//   40.6 / 34.4 / 33.5; 32 heads, S = 1003 (512) 24.0 / 21.5 / 24.9.  No mask: 8 heads, S = 2048 38.5 / 33.1 / 27.0, S =
+//   4096 (512) 78.3 / 71.9 / 88.6.  Up to 256 keys one group is as good (32 heads, S = 256 10.1 / 10.5 / 10.1).
+//   Two groups: below nine tiles the merge costs what the shorter loop saves (eight tiles, 32 heads, causal, D = 128: 14.9
+//   us with one group, 14.4 with two; at two tiles 8.3 / 9.2).  One / two groups: 32 heads, S = 1003, causal, D = 128 24.0
+//   / 21.5 us; 32 heads, S = 2048 (512 work-groups) 49.6 / 45.6, D = 64 31.7 / 29.8; without the mask 256 work-groups 24.7
+//   / 23.7 (D = 64: 16.7 / 15.4), 512 71.6 / 76.5.
 inline int key_groups(int S, long long nbh, int causal)
 {
+    const long long wgs64 = nbh * ((S + 63) / 64);
+    if (S > 256 && (wgs64 <= 256 || (causal && wgs64 <= 512 && S >= 2048)))
+        return 4;
     return S > 8 * BN && nbh * ((S + BM - 1) / BM) <= (causal ? 512 : 256) ? 2 : 1;
 }
 
@@ -1505,7 +1514,8 @@ int launch(const Params& p, int causal, hipStream_t stream)
     const int variant = D > 128 ? wide_variant(p.S, nbh, causal) : pick_variant(p.S, nbh, D, causal);
     if (variant < 0)
         return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64 or bm128)");
-    const long long nblocks = nbh * (variant == V_BM128 ? p.nqt : p.nqt2);
+    const int groups = D <= 128 && variant == V_BM128 ? key_groups(p.S, nbh, causal) : 1;
+    const long long nblocks = nbh * (groups == 4 ? (p.S + 63) / 64 : variant == V_BM128 ? p.nqt : p.nqt2);
     if (nblocks > 0x7fffffffLL)
         return fail(NAUT_ERR_UNSUPPORTED, "B*Hq*ceil(S/128) exceeds the 1-D grid limit");
     const dim3 grid((unsigned)nblocks);
@@ -1528,7 +1538,12 @@ int launch(const Params& p, int causal, hipStream_t stream)
             NAUT_LAUNCH(naut_fwd_kernel_v2, layout_width(D), 256);
 #undef NAUT_TAIL
             launched = true;
-        } else if (key_groups(p.S, nbh, causal) == 2) {
+        } else if (groups == 4) {
+#define NAUT_TAIL , 2, 4
+            NAUT_LAUNCH(naut_fwd_kernel_bm128, D, 512);
+#undef NAUT_TAIL
+            launched = true;
+        } else if (groups == 2) {
 #define NAUT_TAIL , 4, 2
             NAUT_LAUNCH(naut_fwd_kernel_bm128, D, 512);
 #undef NAUT_TAIL

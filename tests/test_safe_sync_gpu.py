@@ -162,6 +162,35 @@ def test_key_groups(D, idt, odt, causal, monkeypatch):
         gu.check(outs[0][0], outs[0][1], o_ref, lse_ref, "D=%d S=%d" % (D, S))
 
 
+@pytest.mark.parametrize("D,idt,odt", [(64, synth.BF16, synth.BF16), (80, synth.F16, synth.F32), (96, synth.BF16, synth.F32),
+                                       (128, synth.F16, synth.F16)])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("Hq,lengths", [(2, (256, 257, 288, 289, 319, 321, 383, 385, 511)), (32, (513, 576, 577, 703)), (4, (2048,))])
+def test_four_and_two_key_groups(D, idt, odt, causal, Hq, lengths, monkeypatch):
+    """The lines between one, two and four key groups: two heads run on four groups from 257 keys on (query tiles that end
+    before the later groups' first tile, groups with one tile fewer than the first, ragged tails), 32 heads on two, four
+    heads of 2048 on four; both builds and the oracle."""
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "bm128")
+    Hkv = max(1, Hq // 8)
+    for S in lengths:
+        q, k, v = make(1, Hq, Hkv, S, D, idt, 33000 + S)
+        qd, kd, vd = (gu.to_device(a, idt) for a in (q, k, v))
+        st = [t.stride(a) for t in (qd, kd, vd, qd) for a in (0, 1, 2)]
+        outs = []
+        print("key groups", D, causal, Hq, S, flush=True)
+        for L in libs():
+            o = torch.full((1, Hq, S, D), float("nan"), dtype=gu.TORCH_DT[odt], device="cuda")
+            lse = torch.full((1, Hq, S), float("nan"), dtype=torch.float32, device="cuda")
+            rc = L.naut_attn_fwd_strided(qd.data_ptr(), kd.data_ptr(), vd.data_ptr(), o.data_ptr(), lse.data_ptr(), 1, Hq, Hkv, S,
+                                         D, int(causal), 1.0 / math.sqrt(D), None, idt, odt, nb.NautStrides(*st))
+            assert rc == 0, L.naut_last_error_string()
+            torch.cuda.synchronize()
+            outs.append((o.double().cpu().numpy(), lse.double().cpu().numpy()))
+        assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1]), "D=%d S=%d" % (D, S)
+        o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, 1.0 / math.sqrt(D))
+        gu.check(outs[0][0], outs[0][1], o_ref, lse_ref, "D=%d S=%d" % (D, S))
+
+
 def test_long_sequence_bit_identical():
     """One long causal head group on the pipelined kernel: hundreds of iterations per work-group."""
     q, k, v = make(1, 8, 8, 8192, 128, synth.BF16, 24000)
