@@ -35,6 +35,7 @@
 // buffers in kernel 2 and for heads wider than 128.
 #ifndef NAUT_ATTN_KERNELS_H
 #define NAUT_ATTN_KERNELS_H
+#include <cfloat>
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -375,7 +376,9 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
 #pragma unroll
         for (int r = 0; r < 16; ++r)
             oacc[db][r] = 0.f;
-    float m_run = NG == 1 ? -INFINITY : M_INIT;  // running max, in the exp2 domain (already times c)
+    // running max, in the exp2 domain (already times c).  A key group may see nothing but masked keys of a row, so
+    // with several the start is finite: the lowest value there is, below any score that is itself finite.
+    float m_run = NG == 1 ? -INFINITY : -FLT_MAX;
     float l_run = 0.f;        // this lane's share of the running sum (its 16 of every 32 keys)
     // What the sum of P as rounded for the second product, the divisor of O, has over l (this lane's share; see
     // "the two sums" in kernel 2).  It is touched only in rare blocks and in the epilogue, so it lives in a word

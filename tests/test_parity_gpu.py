@@ -168,6 +168,33 @@ def test_every_tile_count(variant, causal, monkeypatch):
             gu.check(o, lse, o_ref, lse_ref, "S=%d %s causal=%d" % (S, variant, causal))
 
 
+@pytest.mark.parametrize("Hq,S", [(1, 600), (32, 600), (160, 600)])   # grids of four, two and one key groups
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("causal", [True, False])
+def test_rows_of_very_low_scores(Hq, S, D, causal, monkeypatch):
+    """Rows whose scores are finite and all below -1e30: no start value of the running maximum may be
+    above them.  Scores and scale are powers of two, so the scores reach the exponential without rounding; a row is
+    then the plain mean of V over its highest keys, exact up to the one rounding of a sum of at most S values of 0..15."""
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "bm128")
+    high = 2.0 ** (55 if D == 64 else 54)        # scaled scores: -2^113, -2^114 (D = 128: -2^112, -2^113)
+    q = torch.full((1, Hq, S, D), high, dtype=torch.bfloat16, device="cuda")
+    k = torch.full((1, 1, S, D), -2.0 * high, dtype=torch.bfloat16, device="cuda")
+    k[:, :, ::5] = -high                         # every fifth key, key 0 among them, scores half as low as the rest
+    v = (torch.arange(S * D, device="cuda") * 7 % 16).to(torch.bfloat16).view(1, 1, S, D)
+    o = torch.full((1, Hq, S, D), float("nan"), device="cuda")
+    lse = torch.full((1, Hq, S), float("nan"), device="cuda")
+    print("very low scores", Hq, S, D, causal, flush=True)
+    nb.naut_attn_fwd(q, k, v, o, lse, causal, 0.125)
+    torch.cuda.synchronize()
+    vd = v[0, 0].double()[::5]
+    if causal:
+        ref = (vd.cumsum(0) / torch.arange(1, vd.shape[0] + 1, device="cuda")[:, None])[torch.arange(S, device="cuda") // 5]
+    else:
+        ref = vd.mean(0, keepdim=True).expand(S, D)
+    assert torch.allclose(o[0].double(), ref.expand(Hq, S, D), rtol=0, atol=16 * 2.0 ** -22), (o[0].double() - ref).abs().max()
+    assert torch.allclose(lse.double(), torch.full_like(lse, -D * high * high * 0.125).double(), rtol=2e-7), lse
+
+
 VARIANT_SHAPES = [
     (1, 2, 1, 1, 64, True, synth.BF16, synth.BF16),
     (2, 4, 2, 129, 128, True, synth.BF16, synth.BF16),
