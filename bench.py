@@ -452,6 +452,7 @@ def main() -> int:
         "dtype": "bf16" if w.in_dtype == synth.BF16 else "f16", "data": "synthetic",
         "config": {"workload": w.name, "B": w.B, "Hq": w.Hq, "Hkv": w.Hkv, "S": w.S, "D": w.D,
                    "causal": w.causal, "outlier_k_rows": w.n_outlier, "kernel": variant,
+                   "key_groups": nb.key_groups(w.B, w.Hq, w.S, w.D, w.causal),
                    "flop_convention": "4*B*Hq*S^2*D, halved for causal",
                    "pct_of_bf16_mfma_peak": 100.0 * tflops / PEAK_BF16_TFLOPS},
         "roofline": roof, "context": PAPER_CONTEXT,

@@ -144,10 +144,21 @@ int naut_version(void);
  * warps on short sequences against 128x128 with 8); here it is a fixed rule on the number of
  * work-groups and the length of the key loop, fitted to timings of every variant over a grid of
  * shapes (python -m paper_2604_14825_amd.tune prints that table and flags where the rule loses), and
- * overridable with the environment variable NAUT_ATTN_VARIANT=w8q32|w4q64|bm128.
+ * overridable with the environment variable NAUT_ATTN_VARIANT=w8q32|w4q64|bm128|bm128g1|bm128g2|bm128g4
+ * (the last three also fix the key groups, see below).
  * Host only; used by the benchmark to match profiler rows to launches.
  */
 const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int in_dtype, int out_dtype);
+
+/*
+ * Key groups per work-group that naut_attn_fwd_strided (and naut_attn_fwd_fp8_strided) would launch for these
+ * sizes, 0 if they are unsupported.  "fwd_bm128_w4q32_bn64" has three forms: one group is the tile of the name;
+ * two are two groups of four wavefronts that take the key tiles of one 128-query tile in turn; four are four
+ * groups of two wavefronts on a 64-query tile (D > 64: 32-key steps).  The groups' partial results are merged
+ * inside the work-group.  Every other variant has one group.
+ */
+int naut_attn_key_groups(int B, int Hq, int S, int D, int causal);
+int naut_attn_fwd_fp8_key_groups(int B, int Hq, int S, int D, int causal);
 
 /*
  * Decode-time attention (the paper's second workload, "DC", Section 6: decoding with a key/value

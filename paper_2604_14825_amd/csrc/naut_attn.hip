@@ -175,8 +175,19 @@ const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int 
         return nullptr;
     if (D == 256)
         return wide_variant(S, (long long)B * Hq, causal) == V_W8Q32 ? "fwd_bm256_w8q32_bn32" : "fwd_bm128_w4q32_bn32";
-    const int variant = pick_variant(S, (long long)B * Hq, D, causal);
+    int groups;
+    const int variant = pick_variant(S, (long long)B * Hq, D, causal, &groups);
     return variant < 0 ? nullptr : kVariantName[variant];
+}
+
+int naut_attn_key_groups(int B, int Hq, int S, int D, int causal)
+{
+    if (B <= 0 || Hq <= 0 || S <= 0 || D <= 0 || D % 8 != 0 || D > 256)
+        return 0;
+    int groups = 1;
+    if (D > 128)
+        return wide_variant(S, (long long)B * Hq, causal) < 0 ? 0 : 1;
+    return pick_variant(S, (long long)B * Hq, compiled_width(D), causal, &groups) < 0 ? 0 : groups;
 }
 
 }  // extern "C"

@@ -1435,10 +1435,28 @@ __global__ __launch_bounds__(NWV * 64, 1) void naut_fwd_kernel_v2(const Params p
 
 // Kernel variants (the tile shape / wavefront count / buffering choice the paper leaves to its
 // auto-tuner, Section 4.4 and Section 7.2).  NAUT_ATTN_VARIANT=w8q32|w4q64|bm128 overrides the
-// shape-based choice for A/B runs (read at every call, so that one process can time all of them; any other
-// non-empty value makes the call fail).
-enum Variant { V_W8Q32 = 0, V_W4Q64 = 1, V_BM128 = 2 };
+// shape-based choice for A/B runs, bm128g1|bm128g2|bm128g4 that of the key groups too (read at every call, so that
+// one process can time all of them; any other non-empty value makes the call fail).
+enum Variant { V_W8Q32 = 0, V_W4Q64 = 1, V_BM128 = 2, V_UNKNOWN = -1, V_BY_SHAPE = -2 };
 constexpr const char* kVariantName[3] = {"fwd_bm256_w8q32_bn64", "fwd_bm256_w4q64_bn64", "fwd_bm128_w4q32_bn64"};
+
+// The variant that NAUT_ATTN_VARIANT names, and its key groups (0: by shape).
+inline int named_variant(int* groups)
+{
+    static const struct { const char* name; int variant, groups; } names[] = {
+        {"w8q32", V_W8Q32, 0}, {"w4q64", V_W4Q64, 0}, {"bm128", V_BM128, 0},
+        {"bm128g1", V_BM128, 1}, {"bm128g2", V_BM128, 2}, {"bm128g4", V_BM128, 4}};
+    *groups = 0;
+    const char* e = getenv("NAUT_ATTN_VARIANT");
+    if (!e || !e[0])
+        return V_BY_SHAPE;
+    for (const auto& n : names)
+        if (!strcmp(e, n.name)) {
+            *groups = n.groups;
+            return n.variant;
+        }
+    return V_UNKNOWN;  // a name that selects nothing is an error, not a silent fall-back to the rule
+}
 
 // D > 128: eight wavefronts per work-group, or four (V_BM128) where all 128-query work-groups run at once, one per CU.
 // With the causal mask the second round's work-groups are short and start as the first ones end: two rounds still
@@ -1447,26 +1465,25 @@ constexpr const char* kVariantName[3] = {"fwd_bm256_w8q32_bn64", "fwd_bm256_w4q6
 // 58.4 / 56.7, S = 1500 (768) 115.8 / 85.8; D = 192 draws the line in the same place.
 inline int wide_variant(int S, long long nbh, int causal)
 {
-    if (const char* e = getenv("NAUT_ATTN_VARIANT")) {  // the names that have no wide form choose nothing here
-        if (!strcmp(e, "w8q32"))
-            return V_W8Q32;
-        if (!strcmp(e, "bm128"))
-            return V_BM128;
-    }
+    int groups;
+    const int named = named_variant(&groups);
+    if (named == V_W8Q32 || (named == V_BM128 && groups <= 1))  // the names that have no wide form choose nothing here
+        return named;
     return nbh * ((S + BM - 1) / BM) <= (causal ? 512 : 256) ? V_BM128 : V_W8Q32;
 }
 
-inline int pick_variant(int S, long long nbh, int D, int causal)
+inline int key_groups(int S, long long nbh, int causal);
+
+// D <= 128; also the key groups of the choice (1 where it is not kernel 1)
+inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
 {
-    if (const char* e = getenv("NAUT_ATTN_VARIANT")) {
-        if (!strcmp(e, "w8q32"))
-            return V_W8Q32;
-        if (!strcmp(e, "w4q64"))
-            return V_W4Q64;
-        if (!strcmp(e, "bm128"))
-            return V_BM128;
-        if (e[0] != 0)
-            return -1;  // a name that selects nothing is an error, not a silent fall-back to the rule
+    int named_groups;
+    const int named = named_variant(&named_groups);
+    *groups = named_groups ? named_groups : key_groups(S, nbh, causal);
+    if (named != V_BY_SHAPE) {
+        if (named != V_BM128)
+            *groups = 1;
+        return named;
     }
     // Rule fitted to the timings of `python -m paper_2604_14825_amd.tune` over sequence lengths
     // 256..16384, 2..512 heads, both head dimensions, with and without the causal mask.  The
@@ -1481,11 +1498,10 @@ inline int pick_variant(int S, long long nbh, int D, int causal)
     // selectable by name only.
     const long long wg256 = nbh * ((S + BM2 - 1) / BM2);
     const int avg_keys = causal ? (S + 1) / 2 : S;
-    if (wg256 < 256)
-        return V_BM128;
-    if (D > 64)
-        return avg_keys >= (causal ? 2048 : 1024) ? V_W8Q32 : V_BM128;
-    return (avg_keys >= 8192 && wg256 < 1024) ? V_W8Q32 : V_BM128;
+    const bool pipelined = wg256 >= 256 && (D > 64 ? avg_keys >= (causal ? 2048 : 1024) : avg_keys >= 8192 && wg256 < 1024);
+    if (pipelined)
+        *groups = 1;
+    return pipelined ? V_W8Q32 : V_BM128;
 }
 
 // D <= 128, the kernel of 32 queries per wavefront: key groups per work-group.  A grid that leaves each CU at most one
@@ -1514,10 +1530,10 @@ template <int D, int DT_IN, int DT_OUT>
 int launch(const Params& p, int causal, hipStream_t stream)
 {
     const long long nbh = (long long)p.B * p.Hq;
-    const int variant = D > 128 ? wide_variant(p.S, nbh, causal) : pick_variant(p.S, nbh, D, causal);
+    int groups = 1;
+    const int variant = D > 128 ? wide_variant(p.S, nbh, causal) : pick_variant(p.S, nbh, D, causal, &groups);
     if (variant < 0)
-        return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64 or bm128)");
-    const int groups = D <= 128 && variant == V_BM128 ? key_groups(p.S, nbh, causal) : 1;
+        return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64, bm128, bm128g1, bm128g2 or bm128g4)");
     const long long nblocks = nbh * (groups == 4 ? (p.S + 63) / 64 : variant == V_BM128 ? p.nqt : p.nqt2);
     if (nblocks > 0x7fffffffLL)
         return fail(NAUT_ERR_UNSUPPORTED, "B*Hq*ceil(S/128) exceeds the 1-D grid limit");

@@ -539,4 +539,11 @@ int naut_attn_fwd_fp8(const void* q, const void* k, const void* v, void* o, floa
                                      stream, nullptr);
 }
 
+int naut_attn_fwd_fp8_key_groups(int B, int Hq, int S, int D, int causal)
+{
+    if (B <= 0 || Hq <= 0 || S <= 0 || D <= 0 || D % 16 != 0 || D > 128)
+        return 0;
+    return key_groups(S, (long long)B * Hq * ((S + F8_BM - 1) / F8_BM), causal);
+}
+
 }  // extern "C"

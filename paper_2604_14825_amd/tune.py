@@ -3,7 +3,8 @@
 
 The paper leaves tile shape, warp count and pipeline depth to an auto-tuner that picks per workload
 (Section 4.4; Section 7.2 names the shapes it chose for short and long sequences).  This library
-ships three compiled variants and a fixed rule that chooses among them from the shape; this script
+ships three compiled variants (the 128-query one with one, two or four key groups per work-group) and a fixed rule
+that chooses among them from the shape; this script
 is the measurement behind that rule: it runs each variant through the C ABI (selected with the
 NAUT_ATTN_VARIANT environment variable, which the library reads at every call), prints one line per
 shape with the time of each variant, the fastest one and the one the built-in rule picks, and
@@ -22,8 +23,8 @@ import json
 import os
 import sys
 
-VARIANTS = ("w8q32", "w4q64", "bm128")
-LONG_NAME = {"w8q32": "fwd_bm256_w8q32_bn64", "w4q64": "fwd_bm256_w4q64_bn64", "bm128": "fwd_bm128_w4q32_bn64"}
+VARIANTS = ("w8q32", "w4q64", "bm128g1", "bm128g2", "bm128g4")
+SHORT_NAME = {"fwd_bm256_w8q32_bn64": "w8q32", "fwd_bm256_w4q64_bn64": "w4q64", "fwd_bm128_w4q32_bn64": "bm128g%d"}
 
 
 def default_grid():
@@ -67,7 +68,9 @@ def main() -> int:
         lse = torch.empty((B, Hq, S), dtype=torch.float32, device="cuda")
         scale = D ** -0.5
         os.environ.pop("NAUT_ATTN_VARIANT", None)
-        rule = nb.variant_name(B, Hq, S, D, bool(causal), synth.BF16, synth.BF16)
+        rule_short = SHORT_NAME[nb.variant_name(B, Hq, S, D, bool(causal), synth.BF16, synth.BF16)]
+        if "%d" in rule_short:
+            rule_short %= nb.key_groups(B, Hq, S, D, bool(causal))
         def run(var):
             os.environ["NAUT_ATTN_VARIANT"] = var
             nb.naut_attn_fwd(q, k, v, o, lse, bool(causal), scale, stream=stream)
@@ -91,7 +94,6 @@ def main() -> int:
             times[var] = per[len(per) // 2] * 1e3  # microseconds, median
         os.environ.pop("NAUT_ATTN_VARIANT", None)
         best = min(times, key=times.get)
-        rule_short = [s for s, l in LONG_NAME.items() if l == rule][0]
         loss = times[rule_short] / times[best] - 1.0
         flops = 4.0 * B * Hq * S * S * D * (0.5 if causal else 1.0)
         print("%-34s %s   %-8s  %-8s %s  (%.0f TFLOP/s)" % (

@@ -59,6 +59,31 @@ def test_variant_rule_and_override(monkeypatch):
     assert "NAUT_ATTN_VARIANT" in nb.last_error_string()
 
 
+def test_key_groups_by_name_and_by_shape(monkeypatch):
+    """The key groups of a prefill launch can be seen and, for comparisons, named."""
+    monkeypatch.delenv("NAUT_ATTN_VARIANT", raising=False)
+    bf = nb.NAUT_BF16
+    assert nb.key_groups(1, 2, 256, 64, False) == 1                       # a short loop
+    assert [nb.key_groups(1, 8, 1024, D, True) for D in (64, 80, 96, 128)] == [4, 4, 4, 4]
+    assert nb.key_groups(1, 32, 1003, 128, True) == 2
+    assert nb.key_groups(4, 32, 4096, 128, True) == 1                     # another kernel
+    assert nb.key_groups(1, 8, 1024, 256, True) == 1
+    assert nb.key_groups(1, 8, 1024, 100, True) == 0 and nb.key_groups(1, 8, 1024, 264, True) == 0
+    assert nb.key_groups(1, 32, 1003, 128, True, fp8=True) == 2 and nb.key_groups(4, 32, 4096, 128, True, fp8=True) == 1
+    assert nb.key_groups(1, 8, 1024, 72, True, fp8=True) == 0
+    for g in (1, 2, 4):
+        monkeypatch.setenv("NAUT_ATTN_VARIANT", "bm128g%d" % g)
+        assert nb.variant_name(1, 32, 16384, 128, True, bf, bf) == "fwd_bm128_w4q32_bn64"
+        assert nb.key_groups(1, 32, 16384, 128, True) == g and nb.key_groups(1, 2, 256, 64, False) == g
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "bm128")                      # the kernel; its groups by shape
+    assert nb.key_groups(1, 8, 1024, 128, True) == 4 and nb.key_groups(4, 32, 4096, 128, True) == 1
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "w8q32")
+    assert nb.key_groups(1, 8, 1024, 128, True) == 1
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "bm128g3")
+    assert nb.key_groups(1, 8, 1024, 128, True) == 0
+    assert nb.naut_attn_fwd_raw(A, A, A, A, A, 1, 8, 8, 1024, 128, 1, 0.1, None) == nb.NAUT_ERR_UNSUPPORTED
+
+
 A = 0x10000  # a fake, 16-byte aligned, never dereferenced device address
 
 
