@@ -66,7 +66,7 @@ def _key_profile(kind, S):
     raise ValueError(kind)
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])   # bm128: four key groups here
 @pytest.mark.parametrize("kind", ["ascending", "descending", "late_spike"])
 def test_moving_reference_maximum(kind, variant, monkeypatch):
     """Score profiles that exercise the repair path of the online softmax: a maximum that keeps growing,
@@ -90,15 +90,15 @@ def test_moving_reference_maximum(kind, variant, monkeypatch):
         gu.check(o, lse, o_ref, lse_ref, kind + "/" + variant + "/hot")
 
 
-@pytest.mark.parametrize("variant,D", [("w8q32", 128), ("w4q64", 128), ("bm128", 128), ("bm128", 64), ("bm128", 256)])
+@pytest.mark.parametrize("variant,D", [("w8q32", 128), ("w4q64", 128), ("bm128", 128), ("bm128", 64), ("bm128", 256),
+                                       ("bm128g1", 128), ("bm128g2", 128), ("bm128g1", 64), ("bm128g2", 64), ("w8q32", 256)])
 def test_dominant_key_behind_a_lagging_reference(variant, D, monkeypatch):
     """The last key of every fourth row (its diagonal, under the causal mask) dominates the row by a few binades --
     too few to make a kernel move its reference maximum -- and carries values of magnitude 4 to 5.5, where one
     bf16 step of O is 3e-2.  The largest P of such a row is an arbitrary number, not 1; unless O is divided by the sum of the
     P that went into it, the rounding of that P (up to 2^-8) is an error of 2^-8 |v| on top of the rounding of O, and
     the 2e-2 bar is missed."""
-    if D <= 128:
-        monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)   # bm128, D <= 128: four key groups at this size
     B, H, S, idt, odt = 1, 4, 1500, synth.BF16, synth.BF16
     seed = 4545 + D
     q = synth.fill(B, H, S, D, seed, synth.TAG_Q, idt)
@@ -132,9 +132,12 @@ def test_dominant_key_behind_a_lagging_reference(variant, D, monkeypatch):
     assert np.isfinite(o).all() and d.max() <= gu.TOL_MAX, "dominant key/%s/D%d: max|dO| = %.3e" % (variant, D, d.max())
 
 
+@pytest.mark.parametrize("variant", ["w8q32", "bm128"])
 @pytest.mark.parametrize("kind", ["ascending", "descending", "late_spike"])
-def test_moving_reference_maximum_wide(kind):
-    """The same score profiles on the D = 256 kernel, whose rescale block moves O between register files."""
+def test_moving_reference_maximum_wide(kind, variant, monkeypatch):
+    """The same score profiles on both D = 256 shapes; the rescale block of the four-wavefront one moves O between
+    register files."""
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     B, Hq, Hkv, S, D, idt, odt = 1, 4, 2, 500, 256, synth.BF16, synth.F32
     seed = 4343
     q = synth.fill(B, Hq, S, D, seed, synth.TAG_Q, idt)
@@ -142,7 +145,7 @@ def test_moving_reference_maximum_wide(kind):
     v = synth.fill(B, Hkv, S, D, seed, synth.TAG_V, idt)
     k = synth.round16(_bits_to_f32(k, idt) * _key_profile(kind, S)[None, None, :, None], idt)
     scale = 1.0 / math.sqrt(D)
-    print("case wide", kind, flush=True)
+    print("case wide", kind, variant, flush=True)
     for causal, sc in ((True, scale), (False, 4.0 * scale)):
         o, lse = gu.run_hip(q, k, v, idt, odt, causal, sc)
         o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, sc)
@@ -150,11 +153,12 @@ def test_moving_reference_maximum_wide(kind):
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("variant", ["w8q32", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "bm128", "bm128g1", "bm128g2", "bm128g4"])
 def test_every_tile_count(variant, causal, monkeypatch):
     """Sequence lengths just below, at and just above every multiple of 64 up to 704: every residue of the key-tile
-    count modulo the unrolled loops' period (4 LDS buffers in the 256-query kernel, 2 in the 128-query one), with
-    and without a ragged last tile, and every position of the causal diagonal inside a 256-query work-group."""
+    count modulo the unrolled loops' period (4 LDS buffers in the 256-query kernel; in the 128-query one 2 times its key
+    groups, whose tiles are 32 keys where there are four), with and without a ragged last tile, and every position of
+    the causal diagonal inside a 256-query work-group."""
     monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     B, Hq, Hkv, D, idt, odt = 1, 2, 1, 128, synth.BF16, synth.F32
     scale = 1.0 / math.sqrt(D)
@@ -205,7 +209,7 @@ VARIANT_SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2", "bm128g4"])
 def test_every_kernel_variant(variant, monkeypatch):
     """Each tile shape / wavefront layout the library can choose gives the same attention."""
     monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)

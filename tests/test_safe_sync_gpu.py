@@ -61,7 +61,7 @@ SMALL = [
 ]
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2", "bm128g4"])
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,causal,idt,odt", SMALL)
 def test_small_shapes_bit_identical(B, Hq, Hkv, S, D, causal, idt, odt, variant, monkeypatch):
     monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
@@ -70,7 +70,7 @@ def test_small_shapes_bit_identical(B, Hq, Hkv, S, D, causal, idt, odt, variant,
     both_prefill(q, k, v, idt, odt, causal, 1.0 / math.sqrt(D), "small/%s" % variant)
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "bm128", "bm128g1", "bm128g2", "bm128g4"])
 @pytest.mark.parametrize("causal", [True, False])
 def test_every_tile_count_bit_identical(variant, causal, monkeypatch):
     """S = 64 t - 1, 64 t and 64 t + 1 for t = 1 .. 9: every phase of the four-buffer rotation, with and without a ragged tail."""
@@ -82,7 +82,7 @@ def test_every_tile_count_bit_identical(variant, causal, monkeypatch):
             both_prefill(q, k, v, synth.BF16, synth.BF16, causal, 1.0 / math.sqrt(128), "tiles S=%d/%s" % (S, variant))
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
 @pytest.mark.parametrize("kind", ["ascending", "descending", "late_spike"])
 def test_moving_reference_bit_identical(kind, variant, monkeypatch):
     """The score profiles that drive the rare blocks (reference moves, heavy blocks) of the online softmax."""
@@ -142,7 +142,7 @@ def test_wide_head_eight_wavefronts(D, idt, odt, causal, monkeypatch):
 def test_key_groups(D, idt, odt, causal, monkeypatch):
     """Small grids with more than eight key tiles run on two key groups: odd and even tile counts, ragged tails, a last
     step that only the first group has, rows that see keys of the first group alone; both builds and the oracle."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", "bm128")
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "bm128g2")
     for S in (512, 513, 575, 576, 577, 640, 641, 703, 1024, 1025):
         q, k, v = make(1, 2, 1, S, D, idt, 30000 + S)
         qd, kd, vd = (gu.to_device(a, idt) for a in (q, k, v))

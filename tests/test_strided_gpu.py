@@ -29,7 +29,7 @@ def run_strided(qd, kd, vd, od, causal, scale, want_lse=True):
     return od.double().cpu().numpy(), (lse.double().cpu().numpy() if want_lse else None)
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
 @pytest.mark.parametrize("D", [8, 32, 40, 64, 80, 96, 112, 128])
 def test_head_dimensions(D, variant, monkeypatch):
     """Every multiple of 8 runs on the 64- or 128-wide kernels; contiguous layout."""
@@ -45,7 +45,7 @@ def test_head_dimensions(D, variant, monkeypatch):
     gu.check(o, lse, o_ref, lse_ref, "D=%d %s" % (D, variant))
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
 @pytest.mark.parametrize("D,causal,idt,odt", [(128, True, synth.BF16, synth.BF16), (64, False, synth.F16, synth.F16),
                                              (96, True, synth.BF16, synth.BF16)])
 def test_bshd_layout(D, causal, idt, odt, variant, monkeypatch):
@@ -85,7 +85,7 @@ def test_padded_rows_and_untouched_gaps():
     assert torch.all(o_buf[..., D:] == 7.0).item(), "the gaps between O rows were written"
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
 @pytest.mark.parametrize("D,odt", [(128, synth.BF16), (64, synth.F16), (80, synth.BF16)])
 def test_o_rows_aligned_to_8_bytes_only(D, odt, variant, monkeypatch):
     """16-bit O with a row pitch of D + 4 elements: rows start on 8-byte, not 16-byte, boundaries (the least the
@@ -207,11 +207,13 @@ def test_wide_head_24_heads_groups_of_two():
     gu.check(o.reshape(-1, D)[rows], lse.reshape(-1)[rows], o_ref, lse_ref, "D=256, 24 heads")
 
 
-@pytest.mark.parametrize("D,variant", [(256, None), (128, "bm128"), (128, "w8q32"), (128, "w4q64"), (64, "bm128")])
+@pytest.mark.parametrize("D,variant", [(256, None), (128, "bm128"), (128, "w8q32"), (128, "w4q64"), (64, "bm128"),
+                                       (256, "w8q32"), (128, "bm128g1"), (64, "bm128g1"), (128, "bm128g2")])
 def test_wide_head_row_stride_beyond_32_bits(D, variant, monkeypatch):
     """K and V rows 16 MiB apart (the largest row stride the entry point admits), on every kernel: S times the
-    stride passes 2^32 bytes, so the tile addresses must be formed in 64 bits, and 63 rows of it must fit the
-    32-bit offsets inside a tile."""
+    stride passes 2^32 bytes, so the tile addresses must be formed in 64 bits, and the last row of a tile (the 64th; the
+    32nd at D = 256 and with the four key groups that bm128 runs at D = 128 here) must fit the 32-bit offsets inside
+    a tile."""
     if variant is not None:
         monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     B, H, S, idt = 1, 1, 300, synth.BF16
@@ -236,6 +238,7 @@ def test_wide_head_row_stride_beyond_32_bits(D, variant, monkeypatch):
 
 @pytest.mark.parametrize("D,variant", [(72, "w8q32"), (80, "w8q32"), (88, "w8q32"), (96, "w8q32"), (104, "w8q32"),
                                        (72, "bm128"), (88, "bm128"), (96, "bm128"), (104, "bm128"),
+                                       (72, "bm128g1"), (88, "bm128g1"), (96, "bm128g2"), (104, "bm128g1"),
                                        (136, ""), (184, ""), (192, ""), (200, "")])
 @pytest.mark.parametrize("causal,idt,odt,S", [(True, synth.BF16, synth.BF16, 197), (False, synth.F16, synth.F32, 322)])
 def test_compiled_widths(D, variant, causal, idt, odt, S, monkeypatch):
