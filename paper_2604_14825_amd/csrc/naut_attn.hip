@@ -173,8 +173,10 @@ const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int 
 {
     if (B <= 0 || Hq <= 0 || S <= 0 || (D != 64 && D != 128 && D != 256) || !dtype_pair_ok(in_dtype, out_dtype))
         return nullptr;
-    if (D == 256)
-        return wide_variant(S, (long long)B * Hq, causal) == V_W8Q32 ? "fwd_bm256_w8q32_bn32" : "fwd_bm128_w4q32_bn32";
+    if (D == 256) {
+        const int wide = wide_variant(S, (long long)B * Hq, causal);
+        return wide < 0 ? nullptr : wide == V_W8Q32 ? "fwd_bm256_w8q32_bn32" : "fwd_bm128_w4q32_bn32";
+    }
     int groups;
     const int variant = pick_variant(S, (long long)B * Hq, D, causal, &groups);
     return variant < 0 ? nullptr : kVariantName[variant];

@@ -1467,8 +1467,8 @@ inline int wide_variant(int S, long long nbh, int causal)
 {
     int groups;
     const int named = named_variant(&groups);
-    if (named == V_W8Q32 || (named == V_BM128 && groups <= 1))  // the names that have no wide form choose nothing here
-        return named;
+    if (named == V_W8Q32 || (named == V_BM128 && groups <= 1) || named == V_UNKNOWN)
+        return named;  // w4q64 and several key groups have no wide form: they choose nothing here
     return nbh * ((S + BM - 1) / BM) <= (causal ? 512 : 256) ? V_BM128 : V_W8Q32;
 }
 

@@ -59,6 +59,20 @@ def test_variant_rule_and_override(monkeypatch):
     assert "NAUT_ATTN_VARIANT" in nb.last_error_string()
 
 
+def test_unknown_variant_names_fail_at_every_head_dimension(monkeypatch):
+    bf = nb.NAUT_BF16
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "w8q23")
+    for D in (64, 128, 256):
+        assert nb.variant_name(1, 32, 1024, D, True, bf, bf) is None
+        assert nb.key_groups(1, 32, 1024, D, True) == 0
+        assert nb.naut_attn_fwd_raw(A, A, A, A, A, 1, 32, 32, 1024, D, 1, 0.1, None) == nb.NAUT_ERR_UNSUPPORTED
+        assert "NAUT_ATTN_VARIANT" in nb.last_error_string()
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "w8q32")
+    assert nb.variant_name(1, 32, 1024, 256, True, bf, bf) == "fwd_bm256_w8q32_bn32"
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", "w4q64")      # a name without a wide form: by shape there, as without it
+    assert nb.variant_name(1, 32, 1024, 256, True, bf, bf) == "fwd_bm128_w4q32_bn32"
+
+
 def test_key_groups_by_name_and_by_shape(monkeypatch):
     """The key groups of a prefill launch can be seen and, for comparisons, named."""
     monkeypatch.delenv("NAUT_ATTN_VARIANT", raising=False)
