@@ -1472,14 +1472,14 @@ inline int wide_variant(int S, long long nbh, int causal)
     return nbh * ((S + BM - 1) / BM) <= (causal ? 512 : 256) ? V_BM128 : V_W8Q32;
 }
 
-inline int key_groups(int S, long long nbh, int causal);
+inline int key_groups(int S, long long nbh, int D, int causal);
 
 // D <= 128; also the key groups of the choice (1 where it is not kernel 1)
 inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
 {
     int named_groups;
     const int named = named_variant(&named_groups);
-    *groups = named_groups ? named_groups : key_groups(S, nbh, causal);
+    *groups = named_groups ? named_groups : key_groups(S, nbh, D, causal);
     if (named != V_BY_SHAPE) {
         if (named != V_BM128)
             *groups = 1;
@@ -1504,10 +1504,9 @@ inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
     return pipelined ? V_W8Q32 : V_BM128;
 }
 
-// D <= 128, the kernel of 32 queries per wavefront: key groups per work-group.  A grid that leaves each CU at most one
-// work-group (with the mask: two, whose second round is short) leaves half of its wavefront slots idle, and the time is
-// that of the longest key loop; two groups of four wavefronts halve that loop, four groups of two quarter it and spread
-// the queries over twice the CUs.
+// D <= 128, the kernel of 32 queries per wavefront: key groups per work-group (D: the compiled width).  A grid that leaves
+// each CU at most one work-group leaves half of its wavefront slots idle, and the time is that of the longest key loop;
+// two groups of four wavefronts halve that loop, four groups of two quarter it and spread the queries over twice the CUs.
 //   Four groups: 64-query work-groups, one per CU (LDS), all in one round; with the mask also two rounds if the loops are
 //   long enough to even out (the light query tiles go to the CUs that are done first).  Kernel time with one / two / four
 //   groups, D = 128, causal: 8 heads, S = 512 14.2 / 13.5 / 12.0 us, S = 1024 22.5 / 19.8 / 16.2, S = 2048 39.6 / 33.1 /
@@ -1516,14 +1515,31 @@ inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
 //   4096 (512) 78.3 / 71.9 / 88.6.  Up to 256 keys one group is as good (32 heads, S = 256 10.1 / 10.5 / 10.1).
 //   Two groups: below nine tiles the merge costs what the shorter loop saves (eight tiles, 32 heads, causal, D = 128: 14.9
 //   us with one group, 14.4 with two; at two tiles 8.3 / 9.2).  One / two groups: 32 heads, S = 1003, causal, D = 128 24.0
-//   / 21.5 us; 32 heads, S = 2048 (512 work-groups) 49.6 / 45.6, D = 64 31.7 / 29.8; without the mask 256 work-groups 24.7
-//   / 23.7 (D = 64: 16.7 / 15.4), 512 71.6 / 76.5.
-inline int key_groups(int S, long long nbh, int causal)
+//   / 21.5 us; without the mask 256 work-groups 24.7 / 23.7 (D = 64: 16.7 / 15.4), 512 71.6 / 76.5.
+//   Causal grids beyond 256 work-groups run two groups in two rounds (D = 64: two share a CU, with half the time each has
+//   alone), where one group has all of up to 512 (D = 64: 1024) on the chip at once.  The second round is short only if
+//   few of its work-groups are heavy, which takes many query tiles: the longest grid that gains grows with S, about as
+//   fitted here to 549 shapes each of D = 64, 80, 96, 112 and 128, S = 520..2176 and 258..512 work-groups (mean over them
+//   against one group: 0.945, 0.816, 0.845, 0.947, 0.954, none but five of D = 64 more than 2 % slower; two groups up to 512
+//   everywhere: 0.953, 0.816, 0.850, 0.967, 0.995, 78, 16, 38, 170 and 225 slower, by up to 32 %).  One / two groups, D =
+//   128: 96 heads, S = 640 (480 work-groups) 22.3 / 26.1, 64 heads, S = 1024 (512) 29.7 / 32.0, 40 heads, S = 1280 (400)
+//   31.8 / 30.8, 32 heads, S = 2048 (512) 51.3 / 47.6; D = 64: 15.2 / 16.6, 19.2 / 19.6, 21.7 / 20.2, 32.1 / 30.3.
+//   At D = 128 one group per CU also has to cover the latency of its tiles alone, which costs most where every XCD's L2 sees
+//   every head (B * Hq odd; 33 heads, S = 1604 40.7 / 47.0, 32 heads 38.9 / 34.4) and least where each keeps to an eighth.
+inline int key_groups(int S, long long nbh, int D, int causal)
 {
-    const long long wgs64 = nbh * ((S + 63) / 64);
+    const long long wgs64 = nbh * ((S + 63) / 64), wgs = nbh * ((S + BM - 1) / BM);
     if (S > 256 && (wgs64 <= 256 || (causal && wgs64 <= 512 && S >= 2048)))
         return 4;
-    return S > 8 * BN && nbh * ((S + BM - 1) / BM) <= (causal ? 512 : 256) ? 2 : 1;
+    if (S <= 8 * BN || wgs > (causal ? 512 : 256))
+        return 1;
+    if (wgs <= 256)
+        return 2;
+    const int beyond = D <= 64   ? (S - 192) * 7 / 32  // work-groups beyond the first 256
+                       : D <= 96 ? (S - 384) * 14 / 32
+                       : nbh & 1 ? (S - 700) * 5 / 64
+                                 : (S - 448) * (nbh & 7 ? 5 : 6) / 32;
+    return wgs - 256 <= beyond ? 2 : 1;
 }
 
 template <int D, int DT_IN, int DT_OUT>

@@ -59,6 +59,22 @@ def test_variant_rule_and_override(monkeypatch):
     assert "NAUT_ATTN_VARIANT" in nb.last_error_string()
 
 
+def test_key_groups_of_two_rounds(monkeypatch):
+    """Causal grids of 257 to 512 work-groups of 128 queries: two key groups run them in two rounds, which pays only where
+    few of the second round's tiles are heavy (measured both ways, see the rule)."""
+    monkeypatch.delenv("NAUT_ATTN_VARIANT", raising=False)
+    one = [(96, 640, 128), (96, 640, 96), (96, 640, 64), (96, 520, 80), (80, 520, 128), (80, 520, 64), (64, 520, 128),
+           (64, 700, 128), (64, 900, 128), (64, 1024, 128), (48, 900, 128), (48, 1280, 128), (64, 900, 64), (33, 1604, 128)]
+    two = [(24, 2048, 128), (32, 2048, 128), (32, 2048, 64), (32, 2048, 80), (32, 1536, 128), (40, 1280, 64), (64, 1024, 96),
+           (8, 8192, 64), (32, 1003, 128)]
+    for H, S, D in one + two:
+        assert 128 < H * -(-S // 128) <= 512
+        assert nb.key_groups(1, H, S, D, True) == (1 if (H, S, D) in one else 2), (H, S, D)
+    assert nb.key_groups(3, 32, 640, 128, True) == 1
+    for H, S, D in two:                                                   # without the mask one round is the limit
+        assert nb.key_groups(1, H, S, D, False) == (2 if H * -(-S // 128) <= 256 else 1), (H, S, D)
+
+
 def test_unknown_variant_names_fail_at_every_head_dimension(monkeypatch):
     bf = nb.NAUT_BF16
     monkeypatch.setenv("NAUT_ATTN_VARIANT", "w8q23")
