@@ -416,16 +416,25 @@ __global__ __launch_bounds__(NG * F8_THREADS, NG == 1 ? 2 : 1) void naut_fwd_ker
     }
 }
 
-// Key groups per work-group.  A grid of at most one work-group per CU (with the causal mask: two, whose second round is
-// short) runs one wavefront per SIMD, which waits for its own LDS reads, softmax and MFMAs, and takes as long as its
-// longest key loop; two groups of four wavefronts halve that loop.  Measured (us a call, one / two groups, D = 128): 32
-// heads, S = 1003, causal 17.0 / 15.2; 8 heads, S = 2048 27.5 / 22.8; 8 heads, S = 8192 (512 work-groups) 102.5 / 85.0;
-// 32 heads, S = 2048 (512) 30.6 / 29.8; no mask, 8 heads, S = 4096 (256) 50.1 / 41.4.  Beyond the line the chip holds
-// three one-group work-groups per CU: 40 heads, S = 1024, no mask (320) 21.5 / 26.6; 32 heads, S = 3000, causal (768)
-// 49.4 / 58.7.  At eight tiles the two are equal (10.8 / 10.7 at S = 576), so shorter loops keep one group.
-inline int key_groups(int S, long long nblocks, int causal)
+// Key groups per work-group (D: the compiled width).  A grid of at most one work-group per CU runs one wavefront per SIMD,
+// which waits for its own LDS reads, softmax and MFMAs, and takes as long as its longest key loop; two groups of four
+// wavefronts halve that loop.  Measured (us a call, one / two groups, D = 128): 32 heads, S = 1003, causal 17.0 / 15.2; 8
+// heads, S = 2048 27.5 / 22.8; no mask, 8 heads, S = 4096 (256 work-groups) 50.1 / 41.4, beyond that line 40 heads, S = 1024
+// (320) 21.5 / 26.6.  At nine tiles the two are close (32 heads, S = 520, causal 11.3 / 10.9, S = 576 10.8 / 10.7), at four
+// one is faster (2 heads, S = 256 9.3 / 9.5): up to eight tiles stay on one group.
+//   Causal grids beyond 256 work-groups run two groups one work-group to a CU (D = 64: two) in two rounds, one group three
+// to a CU all at once.  The second round is short only if few of its work-groups are heavy, which takes many query tiles:
+// the longest grid that gains grows with S, about as fitted here to 549 shapes each of D = 64 and 128, S = 520..2176 and
+// 258..512 work-groups (mean over them against one group 0.921 and 0.947, nine and five of them 2 to 5.5 % slower; two
+// groups up to 512 everywhere: 0.924 and 0.997, 53 and 226 slower, by up to 38 %).  One / two groups, D = 128: 80 heads, S =
+// 520 (400 work-groups) 12.9 / 17.0, 64 heads, S = 1024 (512) 20.1 / 22.4, 40 heads, S = 1280 (400) 22.0 / 21.6, 32 heads, S
+// = 2048 (512) 33.8 / 32.9, 8 heads, S = 8192 (512) 102.5 / 85.0; D = 64: 10.0 / 10.7, 15.6 / 15.5, 17.8 / 16.3, 25.5 / 23.9.
+// Beyond 512: 32 heads, S = 3000 (768) 49.4 / 58.7.
+inline int key_groups(int S, long long nblocks, int D, int causal)
 {
-    return S > 8 * F8_BN && nblocks <= (causal ? 512 : 256) ? 2 : 1;
+    if (S <= 8 * F8_BN || nblocks > (causal ? 512 : 256))
+        return 1;
+    return nblocks - 256 <= (D <= 64 ? (S - 320) * 10 / 32 : (S - 576) * 6 / 32) || nblocks <= 256 ? 2 : 1;
 }
 
 }  // namespace
@@ -509,7 +518,7 @@ int naut_attn_fwd_fp8_strided(const void* q, const void* k, const void* v, void*
     const bool strided = D != DK || st->q_b != cs.q_b || st->q_h != cs.q_h || st->q_s != cs.q_s || st->k_b != cs.k_b ||
                          st->k_h != cs.k_h || st->k_s != cs.k_s || st->v_b != cs.v_b || st->v_h != cs.v_h ||
                          st->v_s != cs.v_s || st->o_b != cs.o_b || st->o_h != cs.o_h || st->o_s != cs.o_s;
-    const int ng = key_groups(S, nblocks, causal);
+    const int ng = key_groups(S, nblocks, DK, causal);
 #define NAUT_F8_LAUNCH(DD, CC, SS)                                                          \
     if (DK == DD && (causal != 0) == CC && strided == SS) {                                 \
         if (ng == 2)                                                                        \
@@ -543,7 +552,7 @@ int naut_attn_fwd_fp8_key_groups(int B, int Hq, int S, int D, int causal)
 {
     if (B <= 0 || Hq <= 0 || S <= 0 || D <= 0 || D % 16 != 0 || D > 128)
         return 0;
-    return key_groups(S, (long long)B * Hq * ((S + F8_BM - 1) / F8_BM), causal);
+    return key_groups(S, (long long)B * Hq * ((S + F8_BM - 1) / F8_BM), D <= 64 ? 64 : 128, causal);
 }
 
 }  // extern "C"

@@ -75,6 +75,18 @@ def test_key_groups_of_two_rounds(monkeypatch):
         assert nb.key_groups(1, H, S, D, False) == (2 if H * -(-S // 128) <= 256 else 1), (H, S, D)
 
 
+def test_fp8_key_groups_of_two_rounds():
+    """The same for FP8, where three one-group work-groups fit a CU."""
+    one = [(96, 640, 128), (80, 520, 128), (80, 520, 80), (80, 520, 64), (96, 640, 64), (64, 900, 128), (64, 900, 64),
+           (64, 1024, 128), (48, 900, 96), (48, 1280, 128)]
+    two = [(32, 1003, 128), (32, 520, 128), (8, 8192, 128), (32, 2048, 128), (32, 2048, 64), (40, 1280, 64), (32, 1280, 128)]
+    for H, S, D in one + two:
+        assert 128 < H * -(-S // 128) <= 512
+        assert nb.key_groups(1, H, S, D, True, fp8=True) == (1 if (H, S, D) in one else 2), (H, S, D)
+    assert nb.key_groups(1, 8, 4096, 128, False, fp8=True) == 2 and nb.key_groups(1, 40, 1024, 128, False, fp8=True) == 1
+    assert nb.key_groups(1, 32, 512, 128, True, fp8=True) == 1            # eight tiles
+
+
 def test_unknown_variant_names_fail_at_every_head_dimension(monkeypatch):
     bf = nb.NAUT_BF16
     monkeypatch.setenv("NAUT_ATTN_VARIANT", "w8q23")
