@@ -202,10 +202,15 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
     const int nqt = NWV == 4 ? p.nqt : NWV == 8 ? p.nqt2 : (p.S + BM - 1) / BM;
     const int bid = blockIdx.x;
     int qt, bh;
-    if (NWV == 8 && (nbh & 7) == 0) {  // as in kernel 2: an XCD's run of heads, a few at a time
+    if (NWV == 8 && (nbh & 7) == 0) {
+        // As in kernel 2 an XCD takes a run of heads, about HEADS_AT_ONCE at a time, but in groups of nearly one size:
+        // every group starts with its heaviest tiles, and a last group of one or two heads would run them when
+        // everything else is done (D = 256, causal, S = 1536, 72 heads, nine to an XCD: eight and one 153 us, nine 113;
+        // S = 2048, 136 heads: eight, eight and one 392, nine and eight 327; all at once costs 2 to 4 % of larger grids).
         const int xcd = bid & 7, s = bid >> 3;
         const int hpx = nbh >> 3;
-        const int G = hpx < HEADS_AT_ONCE ? hpx : HEADS_AT_ONCE;
+        const int groups = hpx < HEADS_AT_ONCE ? 1 : (hpx + HEADS_AT_ONCE / 2) / HEADS_AT_ONCE;
+        const int G = (hpx + groups - 1) / groups;
         const int per_group = nqt * G;
         const int g = s / per_group, sg = s % per_group;
         const int ng = hpx - g * G < G ? hpx - g * G : G;

@@ -189,22 +189,30 @@ def test_wide_head_bshd_long_sampled_rows():
     gu.check(o.reshape(-1, D)[rows], lse.reshape(-1)[rows], o_ref, lse_ref, "bshd D=256")
 
 
-def test_wide_head_24_heads_groups_of_two():
-    """D = 256 with B*Hq = 24: every XCD gets three heads and works on two at a time, so its last group is
-    smaller than the others (the multi-group branch of the 128-query kernel's tile scheduler)."""
-    B, Hq, Hkv, S, D, idt = 3, 8, 4, 1024, 256, synth.BF16
+@pytest.mark.parametrize("B,Hq,Hkv,S", [(3, 8, 4, 1024), (9, 8, 2, 300), (1, 80, 8, 513), (13, 8, 1, 300), (1, 136, 8, 257)])
+def test_wide_head_groups_of_heads(B, Hq, Hkv, S, monkeypatch):
+    """The tile scheduler of the eight-wavefront D = 256 shape with B*Hq a multiple of eight: 24, 72, 80, 104 and 136
+    heads are 3, 9, 10, 13 and 17 to an XCD, taken in groups of 3, 9, 10, 7 + 6 and 9 + 8.  Every element of O against
+    the four-wavefront shape (the same tiles in the same order: bit-identical), sampled rows against the oracle."""
+    D, idt = 256, synth.BF16
     q, k, v = make(B, Hq, Hkv, S, D, idt, 9600)
     scale = 1.0 / math.sqrt(D)
     qd, kd, vd = (gu.to_device(a, idt) for a in (q, k, v))
-    od = torch.full((B, Hq, S, D), float("nan"), dtype=torch.bfloat16, device="cuda")
-    print("wide head, 24 heads", flush=True)
-    o, lse = run_strided(qd, kd, vd, od, True, scale)
-    assert np.isfinite(o).all(), "an output tile was never written"
-    rng = np.random.default_rng(6)
-    rows = np.unique(np.concatenate([rng.integers(0, B * Hq * S, 3000),
-                                     [bh * S + i for bh in range(B * Hq) for i in (0, 127, 128, S - 1)]]))
-    o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, True, scale, rows=rows)
-    gu.check(o.reshape(-1, D)[rows], lse.reshape(-1)[rows], o_ref, lse_ref, "D=256, 24 heads")
+    for causal in (True, False):
+        outs = []
+        for variant in ("w8q32", "bm128"):
+            monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
+            od = torch.full((B, Hq, S, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+            print("wide head groups", B, Hq, S, causal, variant, flush=True)
+            outs.append(run_strided(qd, kd, vd, od, causal, scale))
+        o, lse = outs[0]
+        assert np.isfinite(o).all(), "an output tile was never written"
+        assert np.array_equal(o, outs[1][0]) and np.array_equal(lse, outs[1][1])
+        rng = np.random.default_rng(6)
+        rows = np.unique(np.concatenate([rng.integers(0, B * Hq * S, 2000),
+                                         [bh * S + i for bh in range(B * Hq) for i in (0, 255, 256, S - 1)]]))
+        o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, scale, rows=rows)
+        gu.check(o.reshape(-1, D)[rows], lse.reshape(-1)[rows], o_ref, lse_ref, "D=256, %d heads" % (B * Hq))
 
 
 @pytest.mark.parametrize("D,variant", [(256, None), (128, "bm128"), (128, "w8q32"), (128, "w4q64"), (64, "bm128"),
