@@ -174,7 +174,7 @@ const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int 
     if (B <= 0 || Hq <= 0 || S <= 0 || (D != 64 && D != 128 && D != 256) || !dtype_pair_ok(in_dtype, out_dtype))
         return nullptr;
     if (D == 256) {
-        const int wide = wide_variant(S, (long long)B * Hq, causal);
+        const int wide = wide_variant(S, (long long)B * Hq, D, causal);
         return wide < 0 ? nullptr : wide == V_W8Q32 ? "fwd_bm256_w8q32_bn32" : "fwd_bm128_w4q32_bn32";
     }
     int groups;
@@ -188,7 +188,7 @@ int naut_attn_key_groups(int B, int Hq, int S, int D, int causal)
         return 0;
     int groups = 1;
     if (D > 128)
-        return wide_variant(S, (long long)B * Hq, causal) < 0 ? 0 : 1;
+        return wide_variant(S, (long long)B * Hq, compiled_width(D), causal) < 0 ? 0 : 1;
     return pick_variant(S, (long long)B * Hq, compiled_width(D), causal, &groups) < 0 ? 0 : groups;
 }
 

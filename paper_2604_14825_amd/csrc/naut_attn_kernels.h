@@ -1463,18 +1463,26 @@ inline int named_variant(int* groups)
     return V_UNKNOWN;  // a name that selects nothing is an error, not a silent fall-back to the rule
 }
 
-// D > 128: eight wavefronts per work-group, or four (V_BM128) where all 128-query work-groups run at once, one per CU.
-// With the causal mask the second round's work-groups are short and start as the first ones end: two rounds still
-// count as one.  Measured at D = 256 (us, four / eight wavefronts): one head set of 32, S = 1024, no mask (256 of 128
-// queries) 47.5 / 55.6, S = 1500 (384) 115.8 / 81.0; causal, S = 2048 (512) 92.5 / 100.0, 64 heads, S = 1024 (512)
-// 58.4 / 56.7, S = 1500 (768) 115.8 / 85.8; D = 192 draws the line in the same place.
-inline int wide_variant(int S, long long nbh, int causal)
+// D > 128: eight wavefronts per work-group, or four (V_BM128).  Either runs one work-group per CU; one of four wavefronts
+// covers 128 queries in 0.8 of the time that one of eight takes for 256.
+//   No mask: whole rounds of 256 work-groups are what counts.  Four / eight wavefronts, D = 256 (us): 32 heads, S = 1024 (one
+//   round of either) 47.5 / 55.6; S = 1500 (two / one) 115.8 / 81.0; 96 heads, S = 577 (two / two) 60.8 / 76.6; 64 heads, S =
+//   1152 (three / two) 142.1 / 131.6.  Over 781 shapes of D = 192 and 256 the rule loses 1.1 % at most against the better of
+//   the two (one round of four or none, as it was: up to 30 %).  At four rounds against three the two are level, and the
+//   longer loops of D = 256 are faster on four wavefronts (104 heads, S = 1152 191 / 203, 320 heads, S = 300 82 / 76).
+//   With the mask the second round's work-groups are short and start as the first ones end: two rounds still count as one.
+//   S = 2048 (512 of four wavefronts) 92.5 / 100.0, 64 heads, S = 1024 (512) 58.4 / 56.7, S = 1500 (768) 115.8 / 85.8.
+inline int wide_variant(int S, long long nbh, int D, int causal)
 {
     int groups;
     const int named = named_variant(&groups);
     if (named == V_W8Q32 || (named == V_BM128 && groups <= 1) || named == V_UNKNOWN)
         return named;  // w4q64 and several key groups have no wide form: they choose nothing here
-    return nbh * ((S + BM - 1) / BM) <= (causal ? 512 : 256) ? V_BM128 : V_W8Q32;
+    const long long wgs = nbh * ((S + BM - 1) / BM), wgs2 = nbh * ((S + BM2 - 1) / BM2);
+    if (causal)
+        return wgs <= 512 ? V_BM128 : V_W8Q32;
+    const long long r4 = (wgs + 255) / 256, r8 = (wgs2 + 255) / 256;
+    return 4 * r4 <= 5 * r8 || (r4 == 4 && r8 == 3 && D == 256 && S >= 1024) ? V_BM128 : V_W8Q32;
 }
 
 inline int key_groups(int S, long long nbh, int D, int causal);
@@ -1552,7 +1560,7 @@ int launch(const Params& p, int causal, hipStream_t stream)
 {
     const long long nbh = (long long)p.B * p.Hq;
     int groups = 1;
-    const int variant = D > 128 ? wide_variant(p.S, nbh, causal) : pick_variant(p.S, nbh, D, causal, &groups);
+    const int variant = D > 128 ? wide_variant(p.S, nbh, D, causal) : pick_variant(p.S, nbh, D, causal, &groups);
     if (variant < 0)
         return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64, bm128, bm128g1, bm128g2 or bm128g4)");
     const long long nblocks = nbh * (groups == 4 ? (p.S + 63) / 64 : variant == V_BM128 ? p.nqt : p.nqt2);

@@ -87,6 +87,18 @@ def test_fp8_key_groups_of_two_rounds():
     assert nb.key_groups(1, 32, 512, 128, True, fp8=True) == 1            # eight tiles
 
 
+def test_wide_variant_counts_whole_rounds(monkeypatch):
+    """D = 256 without the mask: the shape whose rounds of 256 work-groups are the shorter in sum, a round of four
+    wavefronts counting 0.8 of one of eight."""
+    monkeypatch.delenv("NAUT_ATTN_VARIANT", raising=False)
+    name = {4: "fwd_bm128_w4q32_bn32", 8: "fwd_bm256_w8q32_bn32"}
+    for H, S, waves in ((32, 1024, 4), (32, 1500, 8), (96, 520, 4), (96, 640, 4), (160, 300, 4), (56, 1152, 4), (64, 1152, 8),
+                        (104, 1152, 4), (320, 300, 8), (32, 16384, 8), (64, 4096, 8)):
+        assert nb.variant_name(1, H, S, 256, False, nb.NAUT_BF16, nb.NAUT_BF16) == name[waves], (H, S)
+    for H, S, waves in ((32, 2048, 4), (64, 1024, 4), (64, 1500, 8), (32, 16384, 8)):   # causal: 512 work-groups of four
+        assert nb.variant_name(1, H, S, 256, True, nb.NAUT_BF16, nb.NAUT_BF16) == name[waves], (H, S)
+
+
 def test_unknown_variant_names_fail_at_every_head_dimension(monkeypatch):
     bf = nb.NAUT_BF16
     monkeypatch.setenv("NAUT_ATTN_VARIANT", "w8q23")
