@@ -34,7 +34,6 @@ constexpr int DEC_WAVES = NAUT_DEC_WAVES;  // wavefronts of the split kernel, ea
 constexpr int DEC_THREADS = DEC_WAVES * 64;
 constexpr int MRG_WAVES = 4;               // wavefronts of the merge kernel
 constexpr int MRG_THREADS = MRG_WAVES * 64;
-constexpr int MRG_BATCH = 8;               // splits a wavefront of the merge kernel loads at a time
 constexpr int DEC_ROWS = 32;               // query rows per work-group (one MFMA tile)
 constexpr int DEC_BLK = 32;                // keys per block
 // The reference maximum of the 16-bit kernel moves whenever a row's maximum grows: the largest P of a row is
@@ -578,7 +577,8 @@ __global__ __launch_bounds__(DEC_THREADS, 1) void naut_decode_split_fp8_kernel(c
 // once, stores O and lse.  Wavefront w takes splits w, w+4, ...; lanes run over D.  Bound by the latency of its
 // loads: with the maximum over all splits found in a pass of its own, as it was, 3.7 us for 17 splits of 32 rows and 6.4
 // for 128 of 8 (D = 128), now 3.0 and 4.7.
-template <int D, int DT_OUT>
+// BATCH: the most splits that a wavefront loads at a time (see launch_merge).
+template <int D, int DT_OUT, int BATCH>
 __global__ __launch_bounds__(MRG_THREADS) void naut_decode_merge_kernel(const DecodeParams p)
 {
     __shared__ float red_m[MRG_WAVES];
@@ -594,17 +594,17 @@ __global__ __launch_bounds__(MRG_THREADS) void naut_decode_merge_kernel(const De
     const float* ws_l = ws_m + nparts * DEC_ROWS;
     const float* ws_o = p.ws + (part0 * DEC_ROWS + rr) * D;                      // stride DEC_ROWS*D per split
 
-    // Every wavefront adds up its splits, MRG_BATCH at a time, relative to the largest m it has met; nothing of a batch
-    // depends on another load, so up to MRG_WAVES * MRG_BATCH splits cost one round trip to memory.
+    // Every wavefront adds up its splits, BATCH at a time, relative to the largest m it has met; nothing of a batch
+    // depends on another load, so up to MRG_WAVES * BATCH splits cost one round trip to memory.
     constexpr int EPT = D / 64;  // elements per lane
     typedef float fe_t __attribute__((ext_vector_type(EPT)));
     fe_t acc = (fe_t)(0.f);
     float M = DEC_M_INIT, L = 0.f;
-    for (int s0 = wave; s0 < p.nsplit; s0 += MRG_WAVES * MRG_BATCH) {
-        float m[MRG_BATCH], l[MRG_BATCH];
-        fe_t x[MRG_BATCH];
+    for (int s0 = wave; s0 < p.nsplit; s0 += MRG_WAVES * BATCH) {
+        float m[BATCH], l[BATCH];
+        fe_t x[BATCH];
 #pragma unroll
-        for (int u = 0; u < MRG_BATCH; ++u) {
+        for (int u = 0; u < BATCH; ++u) {
             const int s = s0 + u * MRG_WAVES;
             const size_t sc = s < p.nsplit ? s : s0;  // past the end: repeats a split, not added
             m[u] = ws_m[sc * DEC_ROWS];
@@ -613,14 +613,14 @@ __global__ __launch_bounds__(MRG_THREADS) void naut_decode_merge_kernel(const De
         }
         float m_new = M;
 #pragma unroll
-        for (int u = 0; u < MRG_BATCH; ++u)
+        for (int u = 0; u < BATCH; ++u)
             m_new = fmaxf(m_new, m[u]);
         const float alpha = __builtin_amdgcn_exp2f(M - m_new);
         M = m_new;
         L *= alpha;
         acc *= alpha;
 #pragma unroll
-        for (int u = 0; u < MRG_BATCH; ++u) {
+        for (int u = 0; u < BATCH; ++u) {
             const bool real = s0 + u * MRG_WAVES < p.nsplit;
             const float f = __builtin_amdgcn_exp2f(m[u] - M);
             L += real ? f * l[u] : 0.f;
@@ -670,6 +670,23 @@ __global__ __launch_bounds__(MRG_THREADS) void naut_decode_merge_kernel(const De
         unsigned short* og = (unsigned short*)orow + lane;
         *og = (unsigned short)(In<DT_OUT>::pack2(acc[0] * inv_l, 0.f) & 0xffff);
     }
+}
+
+// A batch reads a split again for each it has too many, so few splits take a small one.  Two or four splits, in a batch of
+// eight / of one (us a call, D = 128): 5 caches of 8 heads, 1024 keys 11.8 / 11.2, 15 caches, 512 keys, 8 query heads to a
+// K/V head 13.9 / 13.0 (13.5 before there were batches).  At 16 splits four are no better than eight.  A kernel of its own
+// for each: one that picks the batch as it runs is 6 to 12 % of the call slower on many splits (one cache of one head,
+// 131072 keys 24.5 / 27.3).
+template <int D, int DT_OUT>
+void launch_merge(const DecodeParams& p, hipStream_t stream)
+{
+    const dim3 grid((unsigned)p.R, (unsigned)(p.B * p.Hkv));
+    if (p.nsplit <= MRG_WAVES)
+        hipLaunchKernelGGL((naut_decode_merge_kernel<D, DT_OUT, 1>), grid, dim3(MRG_THREADS), 0, stream, p);
+    else if (p.nsplit <= 2 * MRG_WAVES)
+        hipLaunchKernelGGL((naut_decode_merge_kernel<D, DT_OUT, 2>), grid, dim3(MRG_THREADS), 0, stream, p);
+    else
+        hipLaunchKernelGGL((naut_decode_merge_kernel<D, DT_OUT, 8>), grid, dim3(MRG_THREADS), 0, stream, p);
 }
 
 struct Plan {
@@ -798,8 +815,7 @@ int launch_decode(const DecodeParams& p, hipStream_t stream)
         return fail_launch(e);
     if (p.nsplit == 1)
         return NAUT_OK;
-    const dim3 g2((unsigned)p.R, (unsigned)(p.B * p.Hkv));
-    hipLaunchKernelGGL((naut_decode_merge_kernel<D, DT_OUT>), g2, dim3(MRG_THREADS), 0, stream, p);
+    launch_merge<D, DT_OUT>(p, stream);
     e = hipGetLastError();
     if (e != hipSuccess)
         return fail_launch(e);
@@ -1053,7 +1069,6 @@ int naut_attn_decode_fp8_strided(const void* q, const void* k, const void* v, vo
     p.cpr = D / 8;
     hipStream_t hs = (hipStream_t)stream;
     const dim3 g1((unsigned)p.nsplit, (unsigned)p.nchunks, (unsigned)(p.B * p.Hkv));
-    const dim3 g2((unsigned)p.R, (unsigned)(p.B * p.Hkv));
     if (DK == 128)
         hipLaunchKernelGGL((naut_decode_split_fp8_kernel<128>), g1, dim3(DEC_THREADS), 0, hs, p);
     else
@@ -1064,9 +1079,9 @@ int naut_attn_decode_fp8_strided(const void* q, const void* k, const void* v, vo
     if (p.nsplit == 1)
         return NAUT_OK;
     if (DK == 128)
-        hipLaunchKernelGGL((naut_decode_merge_kernel<128, NAUT_BF16>), g2, dim3(MRG_THREADS), 0, hs, p);
+        launch_merge<128, NAUT_BF16>(p, hs);
     else
-        hipLaunchKernelGGL((naut_decode_merge_kernel<64, NAUT_BF16>), g2, dim3(MRG_THREADS), 0, hs, p);
+        launch_merge<64, NAUT_BF16>(p, hs);
     e = hipGetLastError();
     if (e != hipSuccess)
         return fail_launch(e);

@@ -255,6 +255,10 @@ def test_decode_very_long_cache(Sk, Sq):
     (2, 40, 2, 2, 257, 80, synth.BF16),       # forty rows per cache: two chunks, the second partly padding
     (1, 8, 1, 1, 20000, 128, synth.BF16),     # 79 splits: several batches of the merge
     (1, 4, 4, 1, 2081, 256, synth.BF16),
+    (1, 16, 8, 1, 1000, 128, synth.BF16),     # four splits: the merge takes one a wavefront
+    (1, 16, 8, 2, 1300, 64, synth.F32),       # six: two
+    (1, 16, 8, 1, 2048, 128, synth.F32),      # eight: two
+    (1, 16, 8, 1, 2300, 128, synth.BF16),     # nine: eight at a time
 ])
 def test_decode_split_counts(B, Hq, Hkv, Sq, Sk, D, odt):
     """Every kind of split plan against the oracle, and with the least workspace that is taken: what is refused there
