@@ -1567,33 +1567,37 @@ int launch(const Params& p, int causal, hipStream_t stream)
     if (nblocks > 0x7fffffffLL)
         return fail(NAUT_ERR_UNSUPPORTED, "B*Hq*ceil(S/128) exceeds the 1-D grid limit");
     const dim3 grid((unsigned)nblocks);
-#define NAUT_LAUNCH(KERNEL, DD, THREADS)                                          \
+#define NAUT_LAUNCH(KERNEL, THREADS)                                              \
     do {                                                                          \
         if (causal)                                                               \
-            hipLaunchKernelGGL((KERNEL<DD, DT_IN, DT_OUT, true NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p);  \
+            hipLaunchKernelGGL((KERNEL<D, DT_IN, DT_OUT, true NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p);  \
         else                                                                      \
-            hipLaunchKernelGGL((KERNEL<DD, DT_IN, DT_OUT, false NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p); \
+            hipLaunchKernelGGL((KERNEL<D, DT_IN, DT_OUT, false NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p); \
     } while (0)
     bool launched = false;
     if constexpr (D <= 128) {
         if (variant == V_W8Q32) {
 #define NAUT_TAIL , 1, 8
-            NAUT_LAUNCH(naut_fwd_kernel_v2, D, 512);
+            NAUT_LAUNCH(naut_fwd_kernel_v2, 512);
 #undef NAUT_TAIL
             launched = true;
         } else if (variant == V_W4Q64) {
+            if constexpr (D != layout_width(D)) {  // by name only: not compiled for the widths in between
+                return launch<layout_width(D), DT_IN, DT_OUT>(p, causal, stream);
+            } else {
 #define NAUT_TAIL , 2, 4
-            NAUT_LAUNCH(naut_fwd_kernel_v2, layout_width(D), 256);
+                NAUT_LAUNCH(naut_fwd_kernel_v2, 256);
 #undef NAUT_TAIL
+            }
             launched = true;
         } else if (groups == 4) {
 #define NAUT_TAIL , 2, 4
-            NAUT_LAUNCH(naut_fwd_kernel_bm128, D, 512);
+            NAUT_LAUNCH(naut_fwd_kernel_bm128, 512);
 #undef NAUT_TAIL
             launched = true;
         } else if (groups == 2) {
 #define NAUT_TAIL , 4, 2
-            NAUT_LAUNCH(naut_fwd_kernel_bm128, D, 512);
+            NAUT_LAUNCH(naut_fwd_kernel_bm128, 512);
 #undef NAUT_TAIL
             launched = true;
         }
@@ -1601,14 +1605,14 @@ int launch(const Params& p, int causal, hipStream_t stream)
     if constexpr (D > 128) {
         if (variant == V_W8Q32) {
 #define NAUT_TAIL , 8
-            NAUT_LAUNCH(naut_fwd_kernel_bm128, D, 512);
+            NAUT_LAUNCH(naut_fwd_kernel_bm128, 512);
 #undef NAUT_TAIL
             launched = true;
         }
     }
     if (!launched) {
 #define NAUT_TAIL
-        NAUT_LAUNCH(naut_fwd_kernel_bm128, D, NTHREADS);
+        NAUT_LAUNCH(naut_fwd_kernel_bm128, NTHREADS);
 #undef NAUT_TAIL
     }
 #undef NAUT_LAUNCH
