@@ -152,9 +152,9 @@ struct XMfma<NAUT_F16> {
 //       not fill the chip (see wide_variant).
 // NG key groups of NWV wavefronts (D <= 128: 2 x 4 or 4 x 2; see key_groups): group g takes key tiles g, g + NG, ... through tile
 // buffers of its own, and the partial (O, m, l) of the groups are merged through LDS at the end.
-// S = 16384, 32 heads, causal, D = 256: 5281 us (833 TFLOP/s) on four wavefronts, 3920 us (1122) on eight, which is
-// where the clock the chip sustains under matrix load stops the D = 128 kernel too; D = 192, 4x64/8 heads,
-// S = 3835: 2250 -> 1463 us.  Outputs are bit-identical (same tiles, same order).
+// S = 16384, 32 heads, causal, D = 256: 5282 us (833 TFLOP/s) on four wavefronts, 4173 us (1054) on eight under sustained
+// load (three launches at a time, before the clock falls, 5026 / 3922); the D = 128 kernel reaches 1150 to 1190.  D = 192,
+// 4x64/8 heads, S = 3835: 2106 / 1387 us.  Outputs are bit-identical (same tiles, same order).
 
 template <int D, int DT_IN, int DT_OUT, bool CAUSAL, int NWV = NWAVES, int NG = 1>
 __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kernel_bm128(const Params p)
@@ -1466,12 +1466,12 @@ inline int named_variant(int* groups)
 // D > 128: eight wavefronts per work-group, or four (V_BM128).  Either runs one work-group per CU; one of four wavefronts
 // covers 128 queries in 0.8 of the time that one of eight takes for 256.
 //   No mask: whole rounds of 256 work-groups are what counts.  Four / eight wavefronts, D = 256 (us): 32 heads, S = 1024 (one
-//   round of either) 47.5 / 55.6; S = 1500 (two / one) 115.8 / 81.0; 96 heads, S = 577 (two / two) 60.8 / 76.6; 64 heads, S =
+//   round of either) 49.0 / 58.1; S = 1536 (two / one) 119.4 / 85.5; 96 heads, S = 577 (two / two) 60.8 / 76.6; 64 heads, S =
 //   1152 (three / two) 142.1 / 131.6.  Over 781 shapes of D = 192 and 256 the rule loses 1.1 % at most against the better of
 //   the two (one round of four or none, as it was: up to 30 %).  At four rounds against three the two are level, and the
 //   longer loops of D = 256 are faster on four wavefronts (104 heads, S = 1152 191 / 203, 320 heads, S = 300 82 / 76).
 //   With the mask the second round's work-groups are short and start as the first ones end: two rounds still count as one.
-//   S = 2048 (512 of four wavefronts) 92.5 / 100.0, 64 heads, S = 1024 (512) 58.4 / 56.7, S = 1500 (768) 115.8 / 85.8.
+//   S = 2048 (512 of four wavefronts) 94.3 / 105.5, 64 heads, S = 1024 (512) 60.9 / 61.5, S = 1536 (768) 119.8 / 92.2.
 inline int wide_variant(int S, long long nbh, int D, int causal)
 {
     int groups;
@@ -1499,7 +1499,9 @@ inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
         return named;
     }
     // Rule fitted to the timings of `python -m paper_2604_14825_amd.tune` over sequence lengths
-    // 256..16384, 2..512 heads, both head dimensions, with and without the causal mask.  The
+    // 256..16384, 2..512 heads, D = 64 and 128, with and without the causal mask, against the 128-query kernel with
+    // one key group.  Two groups overtake the pipelined kernel at exactly one of its work-groups per CU and a long
+    // causal loop (8 heads, S = 8192, D = 128 174.4 / 145.3 us), which the rule does not know.  The
     // pipelined 256-query kernel halves the K/V traffic per FLOP but pays a fill and a drain stage
     // per work-group and needs a full wave of work-groups: it wins once there is one work-group per
     // CU and the key loop is long enough.  At D = 128 that is an average of 1024 keys per query

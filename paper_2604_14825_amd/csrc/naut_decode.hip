@@ -45,7 +45,7 @@ constexpr float DEC_M_INIT = -1.0e30f;     // finite stand-in for "no maximum ye
 #ifndef NAUT_DEC_TARGET
 #define NAUT_DEC_TARGET 256
 #endif
-constexpr int DEC_TARGET_WGS = NAUT_DEC_TARGET;  // work-groups that run at a time: one per CU (LDS)
+constexpr int DEC_TARGET_WGS = NAUT_DEC_TARGET;  // work-groups of a round: one per CU (LDS; the 64 KB of D = 64 would let two share one)
 
 struct DecodeParams {
     const void* q;
@@ -83,7 +83,7 @@ __device__ __forceinline__ float half_sum_f(float x)
 // reuses its own, now idle, region of REGION bytes) and the work-group's partial goes to the workspace.
 // m is the reference maximum the wavefront's l and O are relative to (log2 units).
 // With a single split that partial is the result: it is divided by l and stored as O right here, and there is no merge
-// kernel (32/8 heads, D = 128, 512 keys, B = 40: 27.9 -> 24.5 us; B = 12, split in three before: 14.6 -> 12.2).
+// kernel (32/8 heads, D = 128, 512 keys, B = 40, the same single split: 27.9 -> 24.5 us).
 template <int D, int REGION, int NW, int DT_IN>
 __device__ __forceinline__ void merge_wavefronts(unsigned char* smem, const f32x16_t (&oacc)[D / 32], float m_run,
                                                  float l_run, const DecodeParams& p, int bhk, int chunk, int split)
@@ -732,14 +732,18 @@ void* static_scratch(int* err)
 
 // D: the width the kernels are compiled for (64, 128 or 256); Sk counts keys in units that make a block DEC_BLK of them.
 //
-// How many splits: a work-group occupies a CU (LDS), so the work-groups run in rounds of 256, and a last round of n of
+// How many splits: a work-group occupies a CU (LDS), so the work-groups run in rounds of 256 (at D = 64 two fit a CU; the
+// rounds below price that width too, and where the first count is more than one round pick fewer splits than would be
+// fastest: 33 caches of 8 heads, 4096 keys 61.7 us with two, 55.2 with eight, 68.0 before), and a last round of n of
 // them lasts longer than its n/256 of a full round's bytes: one CU streams at most about 2.2 times its even share of the
 // memory's rate.  The candidates are the counts that fill one, two, three or four rounds without starting another; the
 // time of each is priced from three measurements: a full chip takes 2.9 us for 64 KB per CU, a further round about 2 us
 // of fill and drain, the merge kernel with its launch about 7 us (a single split needs none).  Measured with the first
 // count that reaches 256 work-groups, as it was / the one picked here (us a call, 32/8 heads, one position, D = 128):
-// 4096 keys, B = 9 42.7 / 33.6, B = 12 52.0 / 43.2, B = 20 77.0 / 63.8, B = 33 133 / 113, B = 40 139 / 124;
-// 512 keys, B = 12 14.6 / 12.2.  Where base divides 256 the two are the same.
+// 4096 keys, B = 9 42.7 / 33.6, B = 12 52.0 / 43.2, B = 20 77.0 / 63.8, B = 33 133 / 113, B = 40 139 / 124.
+// The first count stands, and nothing is priced, where it fills whole rounds (base divides 256) and where a fuller split would
+// leave a wavefront less than two blocks (short caches; a single split, which needs no merge, is not considered there:
+// B = 12, 512 keys runs two splits in 14.6 us, one would take 12.2).
 //
 // The workspace must hold the least count's partials (the first count that reaches 256 work-groups); with less room than
 // the picked count needs, the best candidate that fits is taken.  No count takes more than DEC_MAX_PARTS partials unless

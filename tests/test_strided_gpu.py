@@ -32,7 +32,7 @@ def run_strided(qd, kd, vd, od, causal, scale, want_lse=True):
 @pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
 @pytest.mark.parametrize("D", [8, 32, 40, 64, 80, 96, 112, 128])
 def test_head_dimensions(D, variant, monkeypatch):
-    """Every multiple of 8 runs on the 64- or 128-wide kernels; contiguous layout."""
+    """Every multiple of 8 runs on the next of the 64-, 80-, 96- and 128-wide kernels; contiguous layout."""
     monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     B, Hq, Hkv, S, causal, idt, odt = 1, 4, 2, 333, True, synth.BF16, synth.F32
     q, k, v = make(B, Hq, Hkv, S, D, idt, 9000 + D)
@@ -107,8 +107,8 @@ def test_o_rows_aligned_to_8_bytes_only(D, odt, variant, monkeypatch):
 
 @pytest.mark.parametrize("D,odt", [(256, synth.BF16), (200, synth.F16), (136, synth.BF16)])
 def test_o_rows_aligned_to_8_bytes_only_wide(D, odt):
-    """The same on the 256-wide kernel (two O rows per store instruction, 25 or 17 of the 32 chunks real at
-    D = 200 and 136)."""
+    """The same on the wide kernels (two O rows per store instruction, 25 or 17 of the 32 chunks of a staged row real
+    at D = 200 and 136)."""
     B, Hq, Hkv, S = 1, 4, 2, 333
     idt = odt
     q, k, v = make(B, Hq, Hkv, S, D, idt, 9400 + D)
@@ -162,7 +162,7 @@ def test_bshd_prefill_size_sampled_rows():
     (256, 1, True, synth.BF16, synth.F32),
 ])
 def test_wide_head_dimensions(D, S, causal, idt, odt):
-    """Head dimensions above 128 run on the 256-wide instantiation of the 128-query kernel (32 keys per step)."""
+    """Head dimensions above 128 run on the 192- and 256-wide instantiations of kernel 1 (32 keys per step)."""
     B, Hq, Hkv = 2, 4, 2
     q, k, v = make(B, Hq, Hkv, S, D, idt, 9400 + D + S)
     scale = 1.0 / math.sqrt(D)
