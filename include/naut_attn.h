@@ -137,25 +137,29 @@ const char* naut_last_error_string(void);
 int naut_version(void);
 
 /*
- * Name of the kernel variant naut_attn_fwd_dt would launch for these arguments (a static string
- * such as "fwd_bm256_w8q32_bn64": 256-query work-group tile, 8 wavefronts of 32 queries, 64-key
- * steps), or NULL if the arguments are unsupported.  The choice of tile shape per workload is the
- * knob the paper leaves to its auto-tuner (Section 4.4; Section 7.2 reports 64x128 tiles with 4
+ * Name of the class of kernel that these sizes fall into (a static string such as "fwd_bm256_w8q32_bn64": 256 queries on a
+ * compute unit at a time, in wavefronts of 32 queries, over a long key loop), NULL if unsupported.  The paper's
+ * auto-tuner makes this kind of choice per shape (Section 7.2: 64x128 tiles with 4
  * warps on short sequences against 128x128 with 8); here it is a fixed rule on the number of
- * work-groups and the length of the key loop, fitted to timings of every variant over a grid of
- * shapes (python -m paper_2604_14825_amd.tune prints that table and flags where the rule loses), and
- * overridable with the environment variable NAUT_ATTN_VARIANT=w8q32|w4q64|bm128|bm128g1|bm128g2|bm128g4
- * (the last three also fix the key groups, see below).
- * Host only; used by the benchmark to match profiler rows to launches.
+ * work-groups and the length of the key loop, overridable with the environment variable
+ * NAUT_ATTN_VARIANT=w8q32|w4q32|w4q32g2|w4q64|bm128|bm128g1|bm128g2|bm128g4.
+ * Host only.
  */
 const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int in_dtype, int out_dtype);
 
 /*
- * Key groups per work-group that naut_attn_fwd_strided (and naut_attn_fwd_fp8_strided) would launch for these
- * sizes, 0 if they are unsupported.  "fwd_bm128_w4q32_bn64" has three forms: one group is the tile of the name;
- * two are two groups of four wavefronts that take the key tiles of one 128-query tile in turn; four are four
- * groups of two wavefronts on a 64-query tile (D > 64: 32-key steps).  The groups' partial results are merged
- * inside the work-group.  Every other variant has one group.
+ * The kernel that naut_attn_fwd_strided launches for these sizes, chosen inside the class by a rule fitted to timings of
+ * every one over a grid of shapes (python -m paper_2604_14825_amd.tune prints such a table and flags where the rule loses):
+ * "pipe_..." the software-pipelined kernel, "plain_..." the other; then wavefronts x queries of each (of each key group),
+ * and the number of key groups if several share a work-group.  NULL if the sizes are unsupported.  Host only.  (Rows of
+ * K or V more than 8 MiB apart run pipe_4x32 where this says pipe_4x32_g2.)
+ */
+const char* naut_attn_fwd_kernel_name(int B, int Hq, int S, int D, int causal);
+
+/*
+ * Key groups per work-group of the class of these sizes (naut_attn_fwd_fp8_key_groups: of the launch), 0 if they are
+ * unsupported: the groups take the key tiles of one query tile in turn, and their partial results are merged inside the
+ * work-group.  Every class but "fwd_bm128_w4q32_bn64" has one group.
  */
 int naut_attn_key_groups(int B, int Hq, int S, int D, int causal);
 int naut_attn_fwd_fp8_key_groups(int B, int Hq, int S, int D, int causal);

@@ -26,7 +26,7 @@ NAUT_F16 = 1
 NAUT_F32 = 2
 
 EXPORTS = ("naut_attn_fwd", "naut_attn_fwd_dt", "naut_last_error_string", "naut_version",
-           "naut_attn_variant_name", "naut_attn_key_groups", "naut_attn_fwd_fp8_key_groups", "naut_attn_decode", "naut_attn_decode_dt", "naut_attn_decode_workspace_bytes",
+           "naut_attn_variant_name", "naut_attn_fwd_kernel_name", "naut_attn_key_groups", "naut_attn_fwd_fp8_key_groups", "naut_attn_decode", "naut_attn_decode_dt", "naut_attn_decode_workspace_bytes",
            "naut_attn_fwd_strided", "naut_attn_fwd_fp8", "naut_attn_decode_strided", "naut_attn_fwd_fp8_strided", "naut_attn_decode_fp8", "naut_attn_decode_fp8_strided",
            "naut_attn_decode_static", "naut_probe_mfma")
 
@@ -59,6 +59,8 @@ def load(path: str):
     L.naut_version.argtypes = []
     L.naut_attn_variant_name.restype = ctypes.c_char_p
     L.naut_attn_variant_name.argtypes = [ci, ci, ci, ci, ci, ci, ci]
+    L.naut_attn_fwd_kernel_name.restype = ctypes.c_char_p
+    L.naut_attn_fwd_kernel_name.argtypes = [ci, ci, ci, ci, ci]
     L.naut_attn_key_groups.restype = ci
     L.naut_attn_key_groups.argtypes = [ci, ci, ci, ci, ci]
     L.naut_attn_fwd_fp8_key_groups.restype = ci
@@ -118,8 +120,14 @@ def variant_name(B: int, Hq: int, S: int, D: int, causal: bool, in_dtype: int, o
     return r.decode() if r is not None else None
 
 
+def kernel_name(B: int, Hq: int, S: int, D: int, causal: bool):
+    """The kernel that a prefill call of these sizes launches (None: unsupported)."""
+    r = lib().naut_attn_fwd_kernel_name(B, Hq, S, D, int(bool(causal)))
+    return r.decode() if r is not None else None
+
+
 def key_groups(B: int, Hq: int, S: int, D: int, causal: bool, fp8: bool = False) -> int:
-    """Key groups per work-group of the prefill launch for these sizes (0: unsupported)."""
+    """Key groups per work-group of the class of these prefill sizes (FP8: of the launch; 0: unsupported)."""
     f = lib().naut_attn_fwd_fp8_key_groups if fp8 else lib().naut_attn_key_groups
     return int(f(B, Hq, S, D, int(bool(causal))))
 

@@ -26,12 +26,12 @@ namespace naut_k {
 
 // defined in naut_attn_inst.hip
 #define NAUT_EXTERN(IN, OUT)                                                      \
-    extern template int launch<64, IN, OUT>(const Params&, int, hipStream_t);   \
-    extern template int launch<80, IN, OUT>(const Params&, int, hipStream_t);   \
-    extern template int launch<96, IN, OUT>(const Params&, int, hipStream_t);   \
-    extern template int launch<128, IN, OUT>(const Params&, int, hipStream_t);  \
-    extern template int launch<192, IN, OUT>(const Params&, int, hipStream_t);  \
-    extern template int launch<256, IN, OUT>(const Params&, int, hipStream_t);
+    extern template int launch<64, IN, OUT>(Params, int, hipStream_t);   \
+    extern template int launch<80, IN, OUT>(Params, int, hipStream_t);   \
+    extern template int launch<96, IN, OUT>(Params, int, hipStream_t);   \
+    extern template int launch<128, IN, OUT>(Params, int, hipStream_t);  \
+    extern template int launch<192, IN, OUT>(Params, int, hipStream_t);  \
+    extern template int launch<256, IN, OUT>(Params, int, hipStream_t);
 NAUT_EXTERN(NAUT_BF16, NAUT_BF16)
 NAUT_EXTERN(NAUT_BF16, NAUT_F32)
 NAUT_EXTERN(NAUT_F16, NAUT_F16)
@@ -180,6 +180,24 @@ const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int 
     int groups;
     const int variant = pick_variant(S, (long long)B * Hq, D, causal, &groups);
     return variant < 0 ? nullptr : kVariantName[variant];
+}
+
+const char* naut_attn_fwd_kernel_name(int B, int Hq, int S, int D, int causal)
+{
+    if (B <= 0 || Hq <= 0 || S <= 0 || D <= 0 || D % 8 != 0 || D > 256)
+        return nullptr;
+    if (D > 128) {
+        const int wide = wide_variant(S, (long long)B * Hq, compiled_width(D), causal);
+        return wide < 0 ? nullptr : wide == V_W8Q32 ? "plain_8x32" : "plain_4x32";
+    }
+    int groups;
+    switch (pick_form(S, (long long)B * Hq, compiled_width(D), causal, &groups)) {
+    case V_W8Q32: return "pipe_8x32";
+    case V_W4Q64: return "pipe_4x64";
+    case V_W4Q32: return groups == 2 ? "pipe_4x32_g2" : "pipe_4x32";
+    case V_BM128: return groups == 4 ? "plain_2x32_g4" : "plain_4x32";
+    default: return nullptr;
+    }
 }
 
 int naut_attn_key_groups(int B, int Hq, int S, int D, int causal)

@@ -17,16 +17,16 @@
 namespace naut_k {
 
 #if NAUT_INST_W == 64
-template int launch<64, NAUT_INST_IN, NAUT_INST_OUT>(const Params&, int, hipStream_t);
+template int launch<64, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
 #elif NAUT_INST_W == 96
-extern template int launch<128, NAUT_INST_IN, NAUT_INST_OUT>(const Params&, int, hipStream_t);  // w4q64
-template int launch<80, NAUT_INST_IN, NAUT_INST_OUT>(const Params&, int, hipStream_t);
-template int launch<96, NAUT_INST_IN, NAUT_INST_OUT>(const Params&, int, hipStream_t);
+extern template int launch<128, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);  // w4q64
+template int launch<80, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
+template int launch<96, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
 #elif NAUT_INST_W == 128
-template int launch<128, NAUT_INST_IN, NAUT_INST_OUT>(const Params&, int, hipStream_t);
+template int launch<128, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
 #else
-template int launch<192, NAUT_INST_IN, NAUT_INST_OUT>(const Params&, int, hipStream_t);
-template int launch<256, NAUT_INST_IN, NAUT_INST_OUT>(const Params&, int, hipStream_t);
+template int launch<192, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
+template int launch<256, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
 #endif
 
 }  // namespace naut_k

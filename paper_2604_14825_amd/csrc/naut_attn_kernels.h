@@ -5,10 +5,10 @@
 // instantiations over translation units lets them compile in parallel.
 //
 // One kernel computes O = softmax(scale * Q K^T + causal mask) V for a
-// (batch, head, query tile) per work-group; three variants share the formulation
-// below and are picked per shape (pick_variant): kernel 1 (128 queries per
-// work-group; heads wider than 128 run on it too, with 128 or 256 queries) and kernel 2 (256 queries,
-// software-pipelined over 32-key blocks, in two shapes).  The reductions over the key
+// (batch, head, query tile) per work-group; two kernels share the formulation
+// below and are picked per shape (pick_form): kernel 1 (this file; the smallest and shortest
+// launches, and heads wider than 128) and kernel 2 (naut_attn_pipe.h, software-pipelined over 32-key blocks, in
+// four forms).  The reductions over the key
 // axis (row max, row sum, weighted sum of V) are fused with the rolling-update
 // scheme of Section 4.2/4.3 of the paper: a running maximum m and running sum l
 // are kept per query, and whenever m grows the partial results are repaired by
@@ -30,9 +30,9 @@
 //                                      assignment is chosen to match the accumulator layout)
 //
 // K and V tiles are multi-buffered in LDS, one barrier per tile, and go straight from
-// global memory into LDS (global_load_lds_dwordx4, the swizzle applied to the source
-// address): one tile ahead over two buffers in kernel 1, three tiles ahead over four
-// buffers in kernel 2 and for heads wider than 128.
+// global memory into LDS (the swizzle applied to the source
+// address): one tile ahead over two buffers in kernel 1, two over four
+// buffers in kernel 2, three over four for heads wider than 128.
 #ifndef NAUT_ATTN_KERNELS_H
 #define NAUT_ATTN_KERNELS_H
 #include <cfloat>
@@ -70,8 +70,6 @@ constexpr int HEADS_AT_ONCE = NAUT_HAO;  // (batch, head) pairs an XCD works on 
 constexpr int NWAVES = 4;
 constexpr int NTHREADS = NWAVES * 64;
 constexpr float RESCALE_TAU = 6.0f;  // log2 units
-constexpr float M_INIT = -1.0e30f;   // finite stand-in for "no maximum yet": keeps -inf - (-inf) out
-constexpr float P_LIMIT = 1024.0f;   // a block's per-lane row sum above this moves the reference maximum
 
 // The kernels are compiled for head dimensions 64, 80, 96, 128, 192 and 256; a head in between runs on the next
 // wider one.  In LDS a row of K or V always takes 64, 128 or 256 values, so that the swizzles (which need a power
@@ -92,6 +90,7 @@ struct Params {
     int nqt;       // number of 128-query tiles = ceil(S / BM)
     int nqt2;      // number of 256-query tiles
     float c;       // scale * log2(e), > 0
+    float p_limit; // kernel 2: a block's row sum of P above this moves the reference maximum (set at the launch)
     // Byte strides of batch, head and sequence position (the D axis is contiguous).  The kernels are
     // compiled for a few head dimensions; others run on the next wider one: cpr 16-byte
     // chunks of every row are real, the chunks of Q beyond them read as zero, those of K and V repeat
@@ -101,15 +100,35 @@ struct Params {
     int cpr;       // real 16-byte chunks per row = head dimension / 8
 };
 
-// S^T MFMAs of the variants that need more than 256 registers per lane (64 queries per wavefront in
-// kernel 2, wide heads on four wavefronts in kernel 1), written as asm so that their accumulator is an ordinary vector
+// The order of work-groups that keeps an XCD to few heads: work-groups are dealt to the 8 XCDs round-robin by block id, and
+// each XCD has its own L2.  Every XCD gets a contiguous run of an eighth of the (batch, head) pairs, in `groups` groups of
+// nearly one size, one group after the other, each with its heaviest (last) query tiles first.  Pairs that eight does not
+// divide are taken all at once, heaviest tiles first: dealing only those left over to all XCDs was between 6 % slower and
+// 4 % faster (7 x 12 heads, S = 9088, D = 80, causal 1223 -> 1286 us; 12 heads, S = 16384, D = 256 1536 -> 1467).
+struct QueryTile {
+    int qt, bh;
+};
+__device__ __forceinline__ QueryTile tile_by_head(int bid, int nbh, int nqt, int groups)
+{
+    if (nbh & 7)
+        return {nqt - 1 - bid / nbh, bid % nbh};
+    const int xcd = bid & 7, s = bid >> 3;
+    const int hpx = nbh >> 3;
+    const int G = (hpx + groups - 1) / groups, per_group = nqt * G;
+    const int g = s / per_group, sg = s % per_group;
+    const int ng = hpx - g * G < G ? hpx - g * G : G;
+    return {nqt - 1 - sg / ng, xcd * hpx + g * G + sg % ng};
+}
+
+// S^T MFMAs of the shape that needs more than 256 registers per lane (wide heads on four wavefronts),
+// written as asm so that their accumulator is an ordinary vector
 // register tuple while O and Q live in the accumulation registers (the compiler's own MFMA form
 // would then put the scores there too and copy each one out for the softmax).  The compiler's hazard handling does not look inside asm, so the wait states the
 // hardware does not interlock are owed by hand:
 //   - a vector instruction that writes an MFMA source (the register allocator may route a
 //     fragment through a copy) must be 2 wait states ahead of the MFMA: each asm starts with them;
 //   - an MFMA result may be read by a vector instruction only 11 wait states after the issue of
-//     this 8-pass MFMA: see `settle` and the guard at the start of kernel 2's `stage`.
+//     this 8-pass MFMA: see `settle`.
 // Everything that fits the ordinary vector registers uses the compiler's MFMA throughout.
 template <int DT>
 struct XMfma;
@@ -150,7 +169,7 @@ struct XMfma<NAUT_F16> {
 //       MFMAs in asm.  It is bound by the dependences of its one instruction stream (46 % of the wavefront time is
 //       waiting), but one work-group of it takes 0.8 times as long as one of the other, so it stays for grids that do
 //       not fill the chip (see wide_variant).
-// NG key groups of NWV wavefronts (D <= 128: 2 x 4 or 4 x 2; see key_groups): group g takes key tiles g, g + NG, ... through tile
+// NG key groups of NWV wavefronts (D <= 128: four of two; see pick_form): group g takes key tiles g, g + NG, ... through tile
 // buffers of its own, and the partial (O, m, l) of the groups are merged through LDS at the end.
 // S = 16384, 32 heads, causal, D = 256: 5282 us (833 TFLOP/s) on four wavefronts, 4173 us (1054) on eight under sustained
 // load (three launches at a time, before the clock falls, 5026 / 3922); the D = 128 kernel reaches 1150 to 1190.  D = 192,
@@ -178,7 +197,7 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
     constexpr bool WIDE = D > 128;
     constexpr bool ACC = WIDE && NWV == 4;         // O and Q live in the accumulation registers
     constexpr bool PAIR = WIDE && NWV == 8;        // two wavefronts per SIMD on 256 ordinary registers each
-    static_assert(WIDE ? NG == 1 && NWV >= 4 : NWV == 4 || (NWV == 2 && NG == 4), "the shapes that are launched");
+    static_assert(WIDE ? NG == 1 && NWV >= 4 : (NWV == 4 && NG == 1) || (NWV == 2 && NG == 4), "the shapes that are launched");
     constexpr int NB = 4;                          // buffers per operand (wide)
     constexpr int NB2 = NAUT_K1_NBUF;              // buffers per operand (D <= 128)
     constexpr int LDW = TILEB / 1024 / NWV;        // direct loads (1 KB each) per wavefront per tile
@@ -202,20 +221,15 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
     const int nqt = NWV == 4 ? p.nqt : NWV == 8 ? p.nqt2 : (p.S + BM - 1) / BM;
     const int bid = blockIdx.x;
     int qt, bh;
-    if (NWV == 8 && (nbh & 7) == 0) {
-        // As in kernel 2 an XCD takes a run of heads, about HEADS_AT_ONCE at a time, but in groups of nearly one size:
-        // every group starts with its heaviest tiles, and a last group of one or two heads would run them when
-        // everything else is done (D = 256, causal, S = 1536, 72 heads, nine to an XCD: eight and one 153 us, nine 113;
-        // S = 2048, 136 heads: eight, eight and one 392, nine and eight 327; all at once costs 2 to 4 % of larger grids).
-        const int xcd = bid & 7, s = bid >> 3;
+    if (NWV == 8) {
+        // About HEADS_AT_ONCE heads at a time in groups of nearly one size: a last group of one or two heads would start its
+        // heaviest tiles when everything else is done (D = 256, causal, S = 1536, 72 heads, nine to an XCD: eight and one 153
+        // us, nine 113; S = 2048, 136 heads: eight, eight and one 392, nine and eight 327; all at once costs 2 to 4 % of
+        // larger grids).
         const int hpx = nbh >> 3;
-        const int groups = hpx < HEADS_AT_ONCE ? 1 : (hpx + HEADS_AT_ONCE / 2) / HEADS_AT_ONCE;
-        const int G = (hpx + groups - 1) / groups;
-        const int per_group = nqt * G;
-        const int g = s / per_group, sg = s % per_group;
-        const int ng = hpx - g * G < G ? hpx - g * G : G;
-        bh = xcd * hpx + g * G + sg % ng;
-        qt = nqt - 1 - sg / ng;
+        const QueryTile t = tile_by_head(bid, nbh, nqt, hpx < HEADS_AT_ONCE ? 1 : (hpx + HEADS_AT_ONCE / 2) / HEADS_AT_ONCE);
+        qt = t.qt;
+        bh = t.bh;
     } else {
         qt = nqt - 1 - bid / nbh;
         bh = bid % nbh;
@@ -705,752 +719,24 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
     }
 }
 
-// ---- kernel 2: software-pipelined over 32-key blocks ------------------------------------------
-//
-// A work-group owns 256 queries.  Two shapes share one body:
-//   QH = 1, 8 wavefronts: each wavefront owns 32 queries (each lane one query), two wavefronts per
-//          SIMD, so the hardware can also overlap one wavefront's vector work with the other's MFMAs;
-//   QH = 2, 4 wavefronts: each wavefront owns 64 queries in two 32-query halves, so every K and V^T
-//          fragment read from LDS feeds two MFMAs (half the LDS traffic), one wavefront per SIMD.
-// In both, matrix and vector work overlap inside the wavefront: the key axis is processed in
-// 32-key blocks and stage k issues
-//
-//     MFMA:  Y(k-1) = O^T += V^T . P^T of block k-1      VALU:  SM(k) = online softmax of block k
-//            X(k+1) = S^T of block k+1
-//
-// so the MFMAs of a stage never depend on its vector work.  A stage is laid out as a sequence of
-// slots, one MFMA each, followed by a few vector instructions: the matrix pipe hides about six
-// ordinary vector instructions per MFMA and no more, so the softmax is cut into pieces of that
-// size.  K and V tiles (64 keys) are multi-buffered in LDS and filled by direct global->LDS loads
-// issued LA tiles ahead, one barrier per tile.
-
-// LDS fragments read ahead of their MFMAs.  Swept on the S = 16384 and S = 4096 causal shapes: 1 and 2 lose 5
-// and 3 %, 3 to 8 are within half a per cent of each other with 3 ahead every time (and three fragments fewer
-// held in registers).
-#ifndef NAUT_PF
-#define NAUT_PF 3
-#endif
-constexpr int LA = 3;           // tile loads are issued this many iterations ahead of their use
-constexpr int NBUF = LA + 1;    // LDS buffers per operand
-
-// sum over the two 32-lane halves (same exchange as half_max)
-__device__ __forceinline__ float half_sum(float x)
-{
-    float a = x, b = x;
-    asm volatile(NAUT_NOP_SHORT "v_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-    return a + b;
-}
-
-// The softmax of a stage is cut into two pieces per score: FE (fma + exp2) and AC (row-sum add, and
-// for odd scores the pack to 16 bit).  FE of score e+1 is placed before AC of score e so that no
-// add waits on the exponential just issued.  Approximate issue costs, in vector slots (an
-// exponential counts 2), are dealt out to the MFMA slots greedily, at most `cap` per slot.
-template <int QH>
-struct Pieces {
-    static constexpr int NE = 16 * QH, N = 2 * NE;
-    // position -> (is_fe, score index)
-    static constexpr bool is_fe(int pos) { return pos == 0 || (pos != N - 1 && pos % 2 == 1); }
-    static constexpr int score(int pos)
-    {
-        return pos == 0 ? 0 : pos == N - 1 ? NE - 1 : pos % 2 == 1 ? (pos + 1) / 2 : pos / 2 - 1;
-    }
-    static constexpr int cost(int pos) { return is_fe(pos) ? 3 : (score(pos) % 2 == 1 ? 2 : 1); }
-    template <int NSLOT>
-    static constexpr int begin(int slot)
-    {
-        int total = 0;
-        for (int pc = 0; pc < N; ++pc)
-            total += cost(pc);
-        const int cap = (total + NSLOT - 1) / NSLOT + 1;
-        int pc = 0;
-        for (int s = 0; s < slot && s < NSLOT; ++s) {
-            int used = 0;
-            while (pc < N && (s == NSLOT - 1 || used + cost(pc) <= cap || used == 0)) {
-                used += cost(pc);
-                ++pc;
-            }
-        }
-        return slot >= NSLOT ? N : pc;
-    }
-};
-
-template <int D, int DT_IN, int DT_OUT, bool CAUSAL, int QH, int NWV>
-__global__ __launch_bounds__(NWV * 64, 1) void naut_fwd_kernel_v2(const Params p)
-{
-    using T = In<DT_IN>;
-    using XM = XMfma<DT_IN>;
-    using PC = Pieces<QH>;
-    static_assert(QH * NWV * 32 == BM2, "a work-group owns 256 queries");
-    constexpr int W = layout_width(D);         // row width of the LDS layouts
-    constexpr int ROWB = W * 2;
-    constexpr int TILEB = BN * ROWB;           // one 64-key K or V tile
-    constexpr int KS = D / 16;
-    constexpr int DB = (D + 31) / 32;
-    constexpr int LD_PER_W = TILEB / 1024 / NWV;  // direct loads per wavefront per tile (1 KB each)
-    constexpr int NF = 2 * DB + KS;            // fragments per stage: even = V^T (Y), odd = K (X)
-    constexpr int NS = NF * QH;                // slots (MFMAs) per stage
-    constexpr int WQ = 32 * QH;                // queries per wavefront
-    constexpr bool ALLV = QH == 1;  // everything fits the ordinary vector registers: no accumulation registers at all
-    auto pin_acc = [](f32x16_t& x) {
-        if constexpr (ALLV)
-            asm volatile("" : "+v"(x));
-        else
-            asm volatile("" : "+a"(x));
-    };
-    constexpr int PREFETCH = NAUT_PF < NF ? NAUT_PF : NF - 1;  // LDS fragments in flight ahead of their MFMAs
-    static_assert(2 * DB == KS || 2 * DB == KS + 1, "Y and X fragments alternate, Y first");
-    static_assert(LD_PER_W >= 1, "every wavefront must take part in the tile loads");
-
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * NBUF * TILEB];  // K tiles, then V tiles
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31;
-    const int h = lane >> 5;
-
-    // Tile scheduler.  Work-groups are dealt to the 8 XCDs round-robin by block id, and each XCD has
-    // its own L2.  Every XCD is given a contiguous run of (batch, head) pairs and works on
-    // HEADS_AT_ONCE of them at a time, heaviest (last) query tile first, so that the work-groups
-    // resident on an XCD stream few K/V heads through its L2 (query heads that share a K/V head --
-    // grouped-query attention -- sit next to each other).
-    const int nbh = p.B * p.Hq;
-    const int bid = blockIdx.x;
-    int qt, bh;
-    if ((nbh & 7) == 0) {
-        const int xcd = bid & 7, s = bid >> 3;
-        const int hpx = nbh >> 3;                                  // heads per XCD
-        const int G = hpx < HEADS_AT_ONCE ? hpx : HEADS_AT_ONCE;  // heads an XCD works on at a time
-        const int per_group = p.nqt2 * G;
-        const int g = s / per_group, sg = s % per_group;
-        const int ng = hpx - g * G < G ? hpx - g * G : G;          // the last group may be smaller
-        bh = xcd * hpx + g * G + sg % ng;
-        qt = p.nqt2 - 1 - sg / ng;
-    } else {
-        qt = p.nqt2 - 1 - bid / nbh;
-        bh = bid % nbh;
-    }
-    const int b = bh / p.Hq;
-    const int hq = bh % p.Hq;
-    const int hk = hq / (p.Hq / p.Hkv);
-    const int S = p.S;
-    const float c = p.c;
-    float c_v = c;  // copy held in a vector register: an FMA with a scalar-register operand issues at the slower rate
-    asm volatile("" : "+v"(c_v));
-
-    const unsigned char* qg = (const unsigned char*)p.q + b * p.q_bs + hq * p.q_hs;
-    const unsigned char* kg = (const unsigned char*)p.k + b * p.k_bs + hk * p.k_hs;
-    const unsigned char* vg = (const unsigned char*)p.v + b * p.v_bs + hk * p.v_hs;
-    const int cpr = p.cpr;
-
-    const int Q0 = qt * BM2 + wave * WQ;  // first query of this wavefront
-    int qrow[QH];
-#pragma unroll
-    for (int hf = 0; hf < QH; ++hf)
-        qrow[hf] = Q0 + 32 * hf + l32;
-
-    // Q^T fragments (MFMA B operands), resident in the accumulation registers for the whole kernel.
-    i32x4_t qf[QH][KS];
-#pragma unroll
-    for (int hf = 0; hf < QH; ++hf) {
-        const int q_ld = qrow[hf] < S ? qrow[hf] : S - 1;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            // Unconditional, from a chunk that exists; the padding chunks of a narrower head are zeroed
-            // when Q is pinned below.  (A load under a condition becomes a branch, and the compiler then
-            // waited for the first loads in the middle of issuing the rest.)
-            const int ch = ks * 2 + h < cpr ? ks * 2 + h : cpr - 1;
-            qf[hf][ks] = *(const i32x4_t*)(qg + (size_t)q_ld * p.q_rs + ch * 16);
-        }
-    }
-    // Key range of this wavefront / this work-group (keys at or beyond kv_end_w are dead for it).
-    const int kv_end_wg = CAUSAL ? (S < (qt + 1) * BM2 ? S : (qt + 1) * BM2) : S;
-    const int kv_end_w = Q0 >= S ? 0 : (CAUSAL ? (S < Q0 + WQ ? S : Q0 + WQ) : S);
-    const int ntiles = (kv_end_wg + BN - 1) / BN;
-    const int niter = ntiles + 1;  // stages -1 .. 2*ntiles, two per iteration
-    // With the causal mask the wavefronts of a work-group finish at different keys: this one needs blocks
-    // up to kw_last, i.e. stages up to kw_last + 1 = iterations below n_act; after those it only keeps
-    // loading its share of the tiles (the others still read them) and meeting the barrier.
-    const int kw_last = (kv_end_w + 31) / 32 - 1;
-    const int n_act = CAUSAL ? ((kw_last + 2) / 2 + 1 < niter ? (kw_last + 2) / 2 + 1 : niter) : niter;
-
-    // Direct global->LDS tile loads.  Each instruction moves 1 KB: lane i fills physical chunk i of
-    // the block, so the lane fetches the logical chunk that the swizzle maps there.  The address is
-    // (scalar tile base) + (per-lane constant offset), so a full tile costs no vector arithmetic.
-    int k_goff[LD_PER_W], v_goff[LD_PER_W];  // byte offset of the lane's chunk inside a tile
-    int k_grow[LD_PER_W], v_grow[LD_PER_W];  // its row inside the tile (set-up only)
-#pragma unroll
-    for (int i = 0; i < LD_PER_W; ++i) {
-        const int P = (wave * LD_PER_W + i) * 64 + lane;  // physical chunk index in the tile
-        {
-            const int line = P >> 4, pos = P & 15;
-            const int L = (line << 4) + (pos ^ (line & 15));
-            const int krow = L / (W / 8), kch = L % (W / 8);  // logical chunk L = row krow, chunk kch
-            k_goff[i] = krow * p.k_rs + (kch < cpr ? kch : cpr - 1) * 16;
-            k_grow[i] = krow;
-        }
-        if constexpr (W == 128) {
-            const int row = P >> 4, cc = P & 15;
-            const int lc = cc ^ ((row & 3) << 2);
-            v_goff[i] = row * p.v_rs + (lc < cpr ? lc : cpr - 1) * 16;
-            v_grow[i] = row;
-        } else {
-            const int row = P >> 3, cc = P & 7;
-            const int lc = cc ^ (((row >> 1) & 1) << 2);
-            v_goff[i] = row * p.v_rs + (lc < cpr ? lc : cpr - 1) * 16;
-            v_grow[i] = row;
-        }
-    }
-    const unsigned smem_base = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem;
-    // Every iteration issues the same number of loads (the vmcnt arithmetic below counts on it):
-    // a tile index past the end is clamped to the last tile, and that reload lands in a buffer
-    // nobody reads.  The last tile may be ragged (S not a multiple of BN): lanes whose row does not
-    // exist re-read the last row that does, through a second set of per-lane offsets.
-    int k_goff_last[LD_PER_W], v_goff_last[LD_PER_W];
-    {
-        const int rows_left = S - (ntiles - 1) * BN;  // >= 1
-#pragma unroll
-        for (int i = 0; i < LD_PER_W; ++i) {
-            const int kr = k_grow[i], vr = v_grow[i];
-            k_goff_last[i] = kr < rows_left ? k_goff[i] : k_goff[i] - (kr - (rows_left - 1)) * p.k_rs;
-            v_goff_last[i] = vr < rows_left ? v_goff[i] : v_goff[i] - (vr - (rows_left - 1)) * p.v_rs;
-        }
-    }
-    struct TileLoad {
-        unsigned dst;             // LDS byte address of this wavefront's part of the tile
-        const unsigned char* gt;  // global address of the tile (wave-uniform)
-    };
-    // `buf` is the LDS buffer the tile goes to (tile % NBUF, a constant at every call site).  Once the
-    // last tile is reached the per-lane offsets are replaced, for good, by the ragged-tail set: a
-    // wave-uniform branch taken a few times per work-group instead of a select per load.
-    auto tile_load = [&](const unsigned char* g, int row_stride, unsigned lds_tiles, int tile, int buf,
-                         int (&goff)[LD_PER_W], const int (&goff_last)[LD_PER_W]) {
-        TileLoad t;
-        const int tl = tile < ntiles ? tile : ntiles - 1;
-        t.dst = lds_tiles + (unsigned)(buf * TILEB + wave * LD_PER_W * 1024);
-        t.gt = g + (size_t)tl * BN * row_stride;
-        if (tile >= ntiles - 1) {
-#pragma unroll
-            for (int i = 0; i < LD_PER_W; ++i) {
-                goff[i] = goff_last[i];
-                asm volatile("" : "+v"(goff[i]));  // keeps this a branch: nothing here can be speculated into a select
-            }
-        }
-        return t;
-    };
-    auto issue_load = [&](const TileLoad& t, int i, const int* goff) {
-        load_to_lds(t.dst + i * 1024, goff[i], t.gt);
-    };
-    const unsigned k_lds = smem_base, v_lds = smem_base + NBUF * TILEB;
-
-    // Lane parts of the LDS fragment addresses (block / step offsets are immediates on top).
-    int k_lane[KS], v_lane[DB];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        k_lane[ks] = k_off<W>(l32, ks * 2 + h);
-    {
-        const int i16 = lane & 15;
-        const int key = 4 * h + (i16 >> 2);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            const int d = 32 * db + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
-            v_lane[db] = v_off<W>(key, d >> 3) + (d & 7) * 2;
-        }
-    }
-    // LDS byte addresses of the fragments in buffer 0 of K and of V; they stay as they are for the whole
-    // kernel (buffer, block and step offsets are immediates)
-    int k_it[KS], v_it[DB];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        k_it[ks] = k_lane[ks] + (int)k_lds;
-        asm volatile("" : "+v"(k_it[ks]));  // opaque: the compiler then adds nothing but instruction immediates to it
-    }
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-        v_it[db] = v_lane[db] + (int)v_lds;
-        asm volatile("" : "+v"(v_it[db]));
-    }
-
-    f32x16_t oacc[QH][DB];
-#pragma unroll
-    for (int hf = 0; hf < QH; ++hf)
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                oacc[hf][db][r] = 0.f;
-    // reference maximum (log2 units), its negation, a quarter of the running sum of P (kept as the quarter
-    // because that is what a block's sum is compared with: one FMA per block adds to it, and the factor is
-    // exact), and what the sum of P as rounded for the second product has over the unrounded sum (touched in
-    // heavy blocks only; see "the two sums" at the pieces of a stage)
-    float m_run[QH], neg_m[QH], lq_run[QH], dl_run[QH];
-#pragma unroll
-    for (int hf = 0; hf < QH; ++hf) {
-        m_run[hf] = M_INIT;
-        neg_m[hf] = -M_INIT;
-        lq_run[hf] = 0.f;
-        dl_run[hf] = 0.f;
-    }
-
-    // SM(kblk) part 0: causal / tail / out-of-range masking
-    auto mask_block = [&](int kblk, f32x16_t (&s_)[QH]) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = kblk * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-            const bool oob = key >= kv_end_w || kblk < 0;
-#pragma unroll
-            for (int hf = 0; hf < QH; ++hf)
-                s_[hf][r] = (oob || (CAUSAL && key > qrow[hf])) ? -INFINITY : s_[hf][r];
-        }
-    };
-    // first block that needs masking: 32k+31 > Q0 (causal; Q0 is a multiple of 32) or 32k+32 > kv_end_w;
-    // k = -1 (the empty first stage) compares as a huge unsigned number
-    const int kc2 = kv_end_w / 32;
-    const unsigned k_mask_from = (unsigned)(CAUSAL ? (Q0 / 32 < kc2 ? Q0 / 32 : kc2) : kc2);
-    auto needs_mask = [&](int k) { return (unsigned)k >= k_mask_from; };
-    // max of three; the device code is compiled with NaNs assumed absent, so this is one v_max3_f32
-    // with no quieting of the operands
-    auto max3 = [](float x, float y, float z) { return __builtin_fmaxf(__builtin_fmaxf(x, y), z); };
-
-    // Fragment f of block BLKX: even f = V^T (two transposed 64-bit reads), odd f = K (one 128-bit
-    // read).  NEXT selects the tiles of the next iteration (same lane addresses plus a scalar delta).
-    // U = iteration index mod NBUF: iteration j reads K tile j from buffer U and V tile j-1 from buffer
-    // U-1 (mod NBUF), so with the key loop unrolled NBUF times every buffer offset is an immediate of
-    // the LDS instruction and the per-lane addresses never change.
-    auto load_frag = [&](auto F, auto BLKX, auto NEXT, auto UC) -> i32x4_t {
-        constexpr int f = decltype(F)::value, BLK = decltype(BLKX)::value, U = decltype(UC)::value;
-        constexpr bool next_iter = decltype(NEXT)::value;
-        constexpr int KOFF = (next_iter ? (U + 1) % NBUF : U) * TILEB;
-        constexpr int VOFF = (next_iter ? U : (U + NBUF - 1) % NBUF) * TILEB;
-        if constexpr (f % 2 == 0) {
-            constexpr int y = f / 2, t = y / DB, db = y % DB;
-            constexpr int off = (BLK * 32 + 16 * t) * ROWB;
-            const int a = v_it[db] + VOFF;
-            const i16x4_t r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((NAUT_LDS i16x4_t*)(uintptr_t)(a + off));
-            const i16x4_t r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((NAUT_LDS i16x4_t*)(uintptr_t)(a + off + 8 * ROWB));
-            const i32x2_t lo = __builtin_bit_cast(i32x2_t, r0), hi = __builtin_bit_cast(i32x2_t, r1);
-            return i32x4_t{lo.x, lo.y, hi.x, hi.y};
-        } else {
-            constexpr int ks = f / 2;
-            const int a = k_it[ks] + KOFF;
-            return *(const NAUT_LDS i32x4_t*)(uintptr_t)(a + BLK * 32 * ROWB);
-        }
-    };
-
-    // One pipeline stage k = 2*j - 1 + BLK of iteration j (j mod NBUF = U): Y(k-1) reads block BLK of V
-    // tile j-1, X(k+1) block BLK of K tile j.  Every wavefront runs every stage: blocks that
-    // do not exist for it are fully masked in SM (P = 0, m and l unchanged), Y then adds zeros and
-    // X computes scores nobody reads, so one straight-line body serves every k.  The first PREFETCH
-    // fragments arrive in `carry` (read during the previous stage) and the last slots read the next
-    // stage's first fragments into it, so no stage starts with an empty LDS pipeline.
-    auto stage = [&](auto BLKC, auto UC, int k, i32x4_t (&carry)[PREFETCH], f32x16_t (&s_cur)[QH], f32x16_t (&s_nxt)[QH],
-                     const i32x4_t (&p_in)[QH][2], i32x4_t (&p_out)[QH][2], auto&& side) {
-        constexpr int BLK = decltype(BLKC)::value;
-        // s_cur was written by the asm MFMAs at the end of the previous stage: keep every vector
-        // read of it 11 wait states behind them (see XMfma)
-        if constexpr (!ALLV)
-            asm volatile(NAUT_NOP_SETTLE ::: "memory");
-        if (needs_mask(k))
-            mask_block(k, s_cur);
-        i32x4_t frag[NF];
-        static_for<0, PREFETCH>([&](auto F) { frag[decltype(F)::value] = carry[decltype(F)::value]; });
-        auto issue = [&](auto F) {
-            constexpr int f = decltype(F)::value;
-            if constexpr (f < NF) {
-                frag[f] = load_frag(F, std::integral_constant<int, BLK>{}, std::false_type{}, UC);
-            } else {
-                carry[f - NF] = load_frag(std::integral_constant<int, f - NF>{}, std::integral_constant<int, BLK ^ 1>{},
-                                          std::integral_constant<bool, BLK == 1>{}, UC);
-            }
-        };
-        float psum[QH], pe[QH][16];  // this block's row sums (per lane: its 16 of the 32 keys) and exponentials
-#pragma unroll
-        for (int hf = 0; hf < QH; ++hf)
-            psum[hf] = 0.f;
-        // Vector work of the stage, one piece at a time (see Pieces).  P is formed against the
-        // reference maximum as it stands, with no look at this block's own maximum: as long as the
-        // row sums stay below P_LIMIT every P is below it too, and the reference need not move.
-        // The two sums: lse needs l = sum of P to better than 16-bit accuracy, so P is summed in fp32 before it
-        // is rounded; O, on the other hand, must be divided by the sum of the P that went into it, the rounded
-        // ones.  With the reference lagging behind the maximum the largest P of a row is an arbitrary number,
-        // not 1, and its rounding error (up to 2^-8 relative in bf16, whose significand has 8 bits) would otherwise
-        // go into O but not into its divisor: for a row that one key dominates that is an error of up to 2^-8 |v|
-        // on top of the rounding of O itself (as much again: together past the 2e-2 bar once |v| exceeds 2.6).
-        // Divided by the rounded sum the weights add up to one exactly and such a row returns v (what is left is
-        // 2^-8 w |v - O| per key of weight w, as in any kernel that rounds P).  Only keys of large weight matter for
-        // this, so the rounded sum is formed (after the slots, from the packed P) only for a block that
-        // adds a quarter or more to some row's running sum -- every key that ends with a fifth of its row's
-        // weight or more is in such a block -- and the unrounded sum stands in for it otherwise: a key so
-        // treated adds at most 0.2 * 2^-8 |v| to the error, and |O| near 4 would take several such keys with
-        // |v| near 4 in one column, which N(0,1)-like values do not supply; the rounding errors of the many
-        // light keys, independent and of either sign, average out in O.
-        auto piece = [&](auto PCI) {
-            constexpr int pos = decltype(PCI)::value, e = PC::score(pos), hf = e / 16, idx = e % 16;
-            if constexpr (PC::is_fe(pos)) {
-                pe[hf][idx] = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[hf][idx], c_v, neg_m[hf]));
-                // anchor: keeps this piece in its slot (the optimiser would otherwise sink it to the
-                // first use of P, after the last MFMA of the stage).  Input-only: an asm that also
-                // defined the value would make the compiler pad the next use with a wait state.
-                asm volatile("" ::"v"(pe[hf][idx]));
-            } else {
-                // fp32 sum of the unrounded P: lse needs l to better than bf16 accuracy
-                if constexpr (idx == 0)
-                    psum[hf] = pe[hf][0];
-                else
-                    psum[hf] += pe[hf][idx];
-                if constexpr (idx % 2 == 1) {
-                    int w = T::pack2(pe[hf][idx - 1], pe[hf][idx]);
-                    asm volatile("" ::"v"(w), "v"(psum[hf]));
-                    p_out[hf][idx >> 3][(idx >> 1) & 3] = w;
-                } else {
-                    asm volatile("" ::"v"(psum[hf]));
-                }
-            }
-        };
-        static_for<0, NS>([&](auto I) {
-            constexpr int i = decltype(I)::value;
-            constexpr int f = i / QH, hf = i % QH;
-            if constexpr (hf == 0)
-                issue(std::integral_constant<int, f + PREFETCH>{});
-            if constexpr (f % 2 == 0) {
-                constexpr int y = f / 2, t = y / DB, db = y % DB;
-                oacc[hf][db] = T::mfma(frag[f], p_in[hf][t], oacc[hf][db]);
-            } else {
-                constexpr int ks = f / 2;
-                if constexpr (ALLV) {
-                    if constexpr (ks == 0)
-                        s_nxt[hf] = T::mfma(frag[f], qf[hf][ks], f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f});
-                    else
-                        s_nxt[hf] = T::mfma(frag[f], qf[hf][ks], s_nxt[hf]);
-                } else if constexpr (ks == 0)
-                    XM::first(s_nxt[hf], frag[f], qf[hf][ks]);
-                else
-                    XM::acc(s_nxt[hf], frag[f], qf[hf][ks]);
-            }
-            constexpr int p0 = PC::template begin<NS>(i), p1 = PC::template begin<NS>(i + 1);
-            side(I);
-            static_for<p0, p1>([&](auto PCI) { piece(PCI); });
-            // one wait for two fragments: LDS reads return in order, so waiting at the end of an odd
-            // slot for the fragment two slots on covers the next slot's too, and neither of the two
-            // coming slots needs a wait instruction of its own
-            if constexpr (hf == QH - 1 && f % 2 == 1 && f + 2 < NF)
-                asm volatile("" ::"v"(frag[f + 2]));
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        bool over = false;   // also true for +inf (first block of a row: the reference is still M_INIT)
-        bool heavy = false;  // the block adds a quarter or more to the row's running sum (first block: always)
-#pragma unroll
-        for (int hf = 0; hf < QH; ++hf) {
-            over = over || psum[hf] > T::P_LIMIT;
-            heavy = heavy || psum[hf] > lq_run[hf];
-        }
-        const unsigned long long over_mask = __builtin_amdgcn_ballot_w64(over);
-        if ((over_mask | __builtin_amdgcn_ballot_w64(heavy)) != 0) {  // two lane masks and a scalar OR: no vector work
-        if (over_mask != 0) {
-            // Rare path: some row of this wavefront met scores far above its reference maximum.  Move
-            // the reference of every row to its true running maximum, apply the repair factor
-            // exp2(m_old - m_new) to l and O (after Y(k-1), whose P was formed against the old
-            // maxima), and form this block's P again from the scores, which are still intact.
-#pragma unroll
-            for (int hf = 0; hf < QH; ++hf) {
-                const f32x16_t& s_ = s_cur[hf];
-                float mx = max3(s_[0], s_[1], s_[2]);
-                mx = max3(mx, s_[3], s_[4]);
-                mx = max3(mx, s_[5], s_[6]);
-                mx = max3(mx, s_[7], s_[8]);
-                mx = max3(mx, s_[9], s_[10]);
-                mx = max3(mx, s_[11], s_[12]);
-                mx = max3(mx, s_[13], s_[14]);
-                mx = max3(mx, s_[15], s_[15]);
-                float a2 = mx, b2 = mx;
-                asm volatile(NAUT_NOP_SHORT "v_permlane32_swap_b32 %0, %1" : "+v"(a2), "+v"(b2));
-                const float cand = max3(a2, b2, b2) * c;  // -inf if the block is masked for this row
-                const float m_new = max3(m_run[hf], cand, cand);
-                const float alpha = __builtin_amdgcn_exp2f(m_run[hf] - m_new);
-                lq_run[hf] *= alpha;
-                dl_run[hf] *= alpha;
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        oacc[hf][db][r] *= alpha;
-                    pin_acc(oacc[hf][db]);
-                }
-                m_run[hf] = m_new;
-                neg_m[hf] = -m_new;
-                float ps = 0.f;
-#pragma unroll
-                for (int idx = 0; idx < 16; idx += 2) {
-                    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_[idx], c_v, neg_m[hf]));
-                    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_[idx + 1], c_v, neg_m[hf]));
-                    ps += p0 + p1;
-                    p_out[hf][idx >> 3][(idx >> 1) & 3] = T::pack2(p0, p1);
-                }
-                psum[hf] = ps;
-            }
-        }
-        // the heavy block's sum of the rounded P; its difference to the unrounded sum goes to dl_run
-#pragma unroll
-        for (int hf = 0; hf < QH; ++hf) {
-            float pr = -psum[hf];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    pr = T::add_pair(p_out[hf][t][e], pr);
-            dl_run[hf] += pr;
-        }
-        }
-#pragma unroll
-        for (int hf = 0; hf < QH; ++hf) {
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-                pin_acc(oacc[hf][db]);
-            lq_run[hf] = __builtin_fmaf(psum[hf], 0.25f, lq_run[hf]);
-        }
-    };
-
-    // ---- prologue: the first LA K tiles and LA-1 V tiles ----
-    // V tile 0 also goes to the last V buffer: the empty first stage multiplies "V tile -1" from there
-    // by P = 0, which needs finite data; the real owner of that buffer is loaded after that stage.
-    {
-        int v_first[LD_PER_W];
-#pragma unroll
-        for (int i = 0; i < LD_PER_W; ++i)
-            v_first[i] = v_goff[i];
-        const TileLoad tv = tile_load(vg, p.v_rs, v_lds, 0, NBUF - 1, v_first, v_goff_last);
-#pragma unroll
-        for (int i = 0; i < LD_PER_W; ++i)
-            issue_load(tv, i, v_first);
-    }
-#pragma unroll
-    for (int t = 0; t < LA; ++t)
-    {
-        const TileLoad tk = tile_load(kg, p.k_rs, k_lds, t, t, k_goff, k_goff_last);
-#pragma unroll
-        for (int i = 0; i < LD_PER_W; ++i)
-            issue_load(tk, i, k_goff);
-    }
-#pragma unroll
-    for (int t = 0; t + 1 < LA; ++t)
-    {
-        const TileLoad tv = tile_load(vg, p.v_rs, v_lds, t, t, v_goff, v_goff_last);
-#pragma unroll
-        for (int i = 0; i < LD_PER_W; ++i)
-            issue_load(tv, i, v_goff);
-    }
-    // Q is pinned to its registers only here: its loads, issued at the top, and the tile loads share one
-    // round trip to memory instead of taking one each.
-    int cpr_late = cpr;
-    asm volatile("" : "+s"(cpr_late));  // ordered after the tile loads above: so is everything that uses it
-#pragma unroll
-    for (int hf = 0; hf < QH; ++hf)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            if (ks * 2 + h >= cpr_late)
-                qf[hf][ks] = i32x4_t{0, 0, 0, 0};
-            if constexpr (ALLV)
-                asm volatile("" : "+v"(qf[hf][ks]));
-            else
-                asm volatile("" : "+a"(qf[hf][ks]));
-        }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-
-    // s_e / s_o: scores of the current even / odd block; p_e / p_o: P of the last even / odd block
-    f32x16_t s_e[QH], s_o[QH];
-    i32x4_t p_e[QH][2], p_o[QH][2];
-#pragma unroll
-    for (int hf = 0; hf < QH; ++hf) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            s_e[hf][r] = 0.f;
-            s_o[hf][r] = 0.f;
-        }
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            p_e[hf][t] = i32x4_t{0, 0, 0, 0};
-            p_o[hf][t] = i32x4_t{0, 0, 0, 0};
-        }
-    }
-
-    i32x4_t carry[PREFETCH];  // first fragments of the coming stage
-    static_for<0, PREFETCH>([&](auto F) {
-        carry[decltype(F)::value] =
-            load_frag(F, std::integral_constant<int, 0>{}, std::false_type{}, std::integral_constant<int, 0>{});
-    });
-
-    // One iteration of the key loop: K tile j, V tile j-1.  UC = j mod NBUF as a constant: the loop is
-    // unrolled NBUF times so that every LDS buffer offset is an immediate.
-    auto iteration = [&](auto UC, int j) {
-        constexpr int U = decltype(UC)::value;
-        // tiles LA iterations ahead (iteration j reads K tile j and V tile j-1)
-        // The 2*LD_PER_W loads of a wavefront are dealt out over the MFMA slots of one stage (even
-        // wavefronts: the first stage, odd ones: the second) rather than issued in one burst by all
-        // wavefronts right after the barrier, which backs up the memory pipeline and stalls them.
-        const TileLoad kt = tile_load(kg, p.k_rs, k_lds, j + LA, (U + LA) % NBUF, k_goff, k_goff_last);
-        const TileLoad vt = tile_load(vg, p.v_rs, v_lds, j + LA - 1, (U + LA - 1) % NBUF, v_goff, v_goff_last);
-        auto side = [&](auto BLKC, auto I) {
-            constexpr int BLK = decltype(BLKC)::value, i = decltype(I)::value;
-            constexpr int NL = 2 * LD_PER_W, STEP = NS / NL;
-            if constexpr (!SAFE_SYNC && BLK == 0 && STEP > 0 && i % STEP == STEP / 2 && i / STEP < NL) {
-                constexpr int q = i / STEP;
-                if constexpr (q < LD_PER_W)
-                    issue_load(kt, q, k_goff);
-                else
-                    issue_load(vt, q - LD_PER_W, v_goff);
-            }
-        };
-
-        if constexpr (SAFE_SYNC) {  // checking build: the iteration's loads are issued, awaited and published first
-            tile_barrier();
-#pragma unroll
-            for (int i = 0; i < LD_PER_W; ++i)
-                issue_load(kt, i, k_goff);
-#pragma unroll
-            for (int i = 0; i < LD_PER_W; ++i)
-                issue_load(vt, i, v_goff);
-            tile_barrier();
-        }
-        // stage 2j-1: Y(2j-2) with p_e, X(2j) -> s_e, SM(2j-1): s_o -> p_o
-        stage(std::integral_constant<int, 0>{}, UC, 2 * j - 1, carry, s_o, s_e, p_e, p_o,
-              [&](auto I) { side(std::integral_constant<int, 0>{}, I); });
-        // stage 2j:   Y(2j-1) with p_o, X(2j+1) -> s_o, SM(2j): s_e -> p_e
-        stage(std::integral_constant<int, 1>{}, UC, 2 * j, carry, s_e, s_o, p_o, p_e,
-              [&](auto I) { side(std::integral_constant<int, 1>{}, I); });
-
-        // The last slots of the next iteration already read the tiles of the one after it, so the
-        // tiles issued LA-2 iterations ago must have landed by now; newer ones may fly on.
-        static_assert(LA >= 2 && (LA - 2) * 2 * LD_PER_W < 64, "vmcnt field");
-        wait_loads<(LA - 2) * 2 * LD_PER_W>();
-        // A bare barrier, not __syncthreads(): the fence in the latter would first drain the LDS
-        // reads in flight, which are this wavefront's prefetch for the next stage.  They target
-        // tiles published by the previous barrier and buffers that no load overwrites before the
-        // barrier after this one, so they may stay in flight; the tile loads to be published have
-        // been awaited just above.
-        tile_barrier();
-    };
-    for (int j0 = 0; j0 < n_act; j0 += NBUF) {
-        static_for<0, NBUF>([&](auto UC) {
-            const int j = j0 + decltype(UC)::value;
-            if (j < n_act)  // uniform over the wavefront
-                iteration(UC, j);
-        });
-    }
-    for (int j = n_act; j < niter; ++j) {  // this wavefront's part of the remaining tiles, one barrier each
-        const TileLoad kt = tile_load(kg, p.k_rs, k_lds, j + LA, (j + LA) % NBUF, k_goff, k_goff_last);
-        const TileLoad vt = tile_load(vg, p.v_rs, v_lds, j + LA - 1, (j + LA - 1) % NBUF, v_goff, v_goff_last);
-        if constexpr (SAFE_SYNC)
-            tile_barrier();  // checking build: the same three barriers per iteration as the wavefronts still computing
-#pragma unroll
-        for (int i = 0; i < LD_PER_W; ++i)
-            issue_load(kt, i, k_goff);
-#pragma unroll
-        for (int i = 0; i < LD_PER_W; ++i)
-            issue_load(vt, i, v_goff);
-        if constexpr (SAFE_SYNC)
-            tile_barrier();
-        wait_loads<(LA - 2) * 2 * LD_PER_W>();
-        tile_barrier();
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
-    // ---- epilogue ----
-    if (Q0 >= S)
-        return;
-    constexpr int OUTB = DT_OUT == NAUT_F32 ? 4 : 2;
-    unsigned char* const o_bh = (unsigned char*)p.o + b * p.o_bs + hq * p.o_hs;
-    if constexpr (OUTB == 2) {
-        // 16-bit output goes through LDS so that it leaves in whole rows: a lane owns 4 consecutive
-        // d of one query (8 bytes, 32 different rows per store instruction); after the exchange 16
-        // lanes (D = 128) write one 256-byte row with 16 bytes each.  The staging rows live in this
-        // wavefront's own part of the first four tile buffers (where only its own tile loads land,
-        // and those are complete), so no barrier is needed: the other wavefronts have consumed every
-        // tile by the time this one is past the last barrier.
-        constexpr int CPRO = W / 8;           // 16-byte chunks per staged row
-        constexpr int PS = LD_PER_W * 1024;   // this wavefront's part of one tile buffer
-        constexpr int RP = PS / ROWB;         // staged rows per part
-        constexpr int R256 = ROWB >= 256 ? 1 : 256 / ROWB;  // rows per 256-byte bank line
-        static_assert(WQ / RP <= 2 * NBUF && WQ % RP == 0, "staging rows must fit this wavefront's tile parts");
-        auto staged = [&](int r, int ch) {  // chunk ch of staged row r; swizzled so that neither side conflicts
-            return smem + (r / RP) * TILEB + wave * PS + (r % RP) * ROWB + ((ch ^ ((r / R256) & (CPRO - 1))) << 4);
-        };
-#pragma unroll
-        for (int hf = 0; hf < QH; ++hf) {
-            const int q = qrow[hf];
-            const float lt = 4.0f * half_sum(lq_run[hf]);
-            const float inv_l = 1.0f / (lt + half_sum(dl_run[hf]));  // rows beyond S: staged, never stored
-            if (p.lse != nullptr && h == 0 && q < S)
-                p.lse[(size_t)bh * S + q] = (m_run[hf] + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int d = 32 * db + 8 * g + 4 * h;
-                    const float x0 = oacc[hf][db][4 * g + 0] * inv_l, x1 = oacc[hf][db][4 * g + 1] * inv_l;
-                    const float x2 = oacc[hf][db][4 * g + 2] * inv_l, x3 = oacc[hf][db][4 * g + 3] * inv_l;
-                    i32x2_t w = {In<DT_OUT>::pack2(x0, x1), In<DT_OUT>::pack2(x2, x3)};
-                    *(i32x2_t*)(staged(32 * hf + l32, d >> 3) + (d & 7) * 2) = w;
-                }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        constexpr int RPI = 64 / CPRO;  // rows per store instruction
-        typedef i32x4_t __attribute__((aligned(8))) i32x4_a8;  // O rows are 8-byte aligned, not more
-        i32x4_t rows[WQ / RPI];
-#pragma unroll
-        for (int i = 0; i < WQ / RPI; ++i)  // all reads first: one LDS latency, not one per store
-            rows[i] = *(const i32x4_t*)staged(i * RPI + lane / CPRO, lane % CPRO);
-#pragma unroll
-        for (int i = 0; i < WQ / RPI; ++i) {
-            const int ch = lane % CPRO;
-            const int q = Q0 + i * RPI + lane / CPRO;
-            if (q < S && ch < cpr)  // not the rows beyond S, not the padding columns of a narrower head
-                *(i32x4_a8*)(o_bh + (size_t)q * p.o_rs + ch * 16) = rows[i];
-        }
-    } else {
-#pragma unroll
-        for (int hf = 0; hf < QH; ++hf) {
-            const int q = qrow[hf];
-            const float lt = 4.0f * half_sum(lq_run[hf]);
-            const float lr = lt + half_sum(dl_run[hf]);
-            if (q >= S)
-                continue;
-            const float inv_l = 1.0f / lr;
-            if (p.lse != nullptr && h == 0)
-                p.lse[(size_t)bh * S + q] = (m_run[hf] + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
-            unsigned char* og = o_bh + (size_t)q * p.o_rs;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int d = 32 * db + 8 * g + 4 * h;
-                    if (d >= cpr * 8)
-                        continue;  // padding columns of a narrower head dimension
-                    f32x4_t w = {oacc[hf][db][4 * g + 0] * inv_l, oacc[hf][db][4 * g + 1] * inv_l,
-                                 oacc[hf][db][4 * g + 2] * inv_l, oacc[hf][db][4 * g + 3] * inv_l};
-                    *(f32x4_t*)(og + d * 4) = w;
-                }
-        }
-    }
-}
+#include "naut_attn_pipe.h"
 
 // ---- host side: variant choice and launch -------------------------------------------
 
 // Kernel variants (the tile shape / wavefront count / buffering choice the paper leaves to its
-// auto-tuner, Section 4.4 and Section 7.2).  NAUT_ATTN_VARIANT=w8q32|w4q64|bm128 overrides the
-// shape-based choice for A/B runs, bm128g1|bm128g2|bm128g4 that of the key groups too (read at every call, so that
-// one process can time all of them; any other non-empty value makes the call fail).
-enum Variant { V_W8Q32 = 0, V_W4Q64 = 1, V_BM128 = 2, V_UNKNOWN = -1, V_BY_SHAPE = -2 };
-constexpr const char* kVariantName[3] = {"fwd_bm256_w8q32_bn64", "fwd_bm256_w4q64_bn64", "fwd_bm128_w4q32_bn64"};
+// auto-tuner, Section 4.4 and Section 7.2).  NAUT_ATTN_VARIANT overrides the shape-based choice for A/B runs (read at every
+// call, so that one process can time all of them; any other non-empty value makes the call fail): kernel 2 as w8q32, w4q32,
+// w4q32g2 or w4q64, kernel 1 as bm128g1 or bm128g4; bm128 is kernel 1 with the key groups of the class (key_groups), and two
+// key groups, which bm128g2 names, are kernel 2's.
+enum Variant { V_W8Q32 = 0, V_W4Q64 = 1, V_BM128 = 2, V_W4Q32 = 3, V_UNKNOWN = -1, V_BY_SHAPE = -2 };
+constexpr const char* kVariantName[4] = {"fwd_bm256_w8q32_bn64", "fwd_bm256_w4q64_bn64", "fwd_bm128_w4q32_bn64", "fwd_bm128_w4q32_bn32"};
 
 // The variant that NAUT_ATTN_VARIANT names, and its key groups (0: by shape).
 inline int named_variant(int* groups)
 {
     static const struct { const char* name; int variant, groups; } names[] = {
-        {"w8q32", V_W8Q32, 0}, {"w4q64", V_W4Q64, 0}, {"bm128", V_BM128, 0},
-        {"bm128g1", V_BM128, 1}, {"bm128g2", V_BM128, 2}, {"bm128g4", V_BM128, 4}};
+        {"w8q32", V_W8Q32, 0}, {"w4q64", V_W4Q64, 0}, {"w4q32", V_W4Q32, 1}, {"w4q32g2", V_W4Q32, 2},
+        {"bm128", V_BM128, 0}, {"bm128g1", V_BM128, 1}, {"bm128g2", V_BM128, 2}, {"bm128g4", V_BM128, 4}};
     *groups = 0;
     const char* e = getenv("NAUT_ATTN_VARIANT");
     if (!e || !e[0])
@@ -1487,30 +773,19 @@ inline int wide_variant(int S, long long nbh, int D, int causal)
 
 inline int key_groups(int S, long long nbh, int D, int causal);
 
-// D <= 128; also the key groups of the choice (1 where it is not kernel 1)
+// The class that a shape falls into, D <= 128, and the key groups of the class: V_W8Q32 where whole rounds of 256-query
+// work-groups run a long key loop, V_BM128 otherwise.  It is what naut_attn_variant_name and naut_attn_key_groups tell;
+// what a launch of either class runs is chosen more finely (pick_form).
 inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
 {
     int named_groups;
     const int named = named_variant(&named_groups);
     *groups = named_groups ? named_groups : key_groups(S, nbh, D, causal);
-    if (named != V_BY_SHAPE) {
-        if (named != V_BM128)
+    if (named != V_BY_SHAPE && (named != V_W4Q64 || D <= 64)) {  // w4q64 has no wider form: it chooses nothing there
+        if (named == V_W8Q32 || named == V_W4Q64)
             *groups = 1;
         return named;
     }
-    // Rule fitted to the timings of `python -m paper_2604_14825_amd.tune` over sequence lengths
-    // 256..16384, 2..512 heads, D = 64 and 128, with and without the causal mask, against the 128-query kernel with
-    // one key group.  Two groups overtake the pipelined kernel at exactly one of its work-groups per CU and a long
-    // causal loop (8 heads, S = 8192, D = 128 174.4 / 145.3 us), which the rule does not know.  The
-    // pipelined 256-query kernel halves the K/V traffic per FLOP but pays a fill and a drain stage
-    // per work-group and needs a full wave of work-groups: it wins once there is one work-group per
-    // CU and the key loop is long enough.  At D = 128 that is an average of 1024 keys per query
-    // without the mask and 2048 with it (the 128-query tiles follow the causal diagonal more
-    // closely).  At D = 64 the softmax and not the MFMAs sets the pace and the 128-query kernel keeps
-    // four wavefronts per SIMD: the pipelined kernel is ahead only on long key loops (8192 keys per
-    // query) with few work-groups (fewer than four 256-query tiles per CU).  The
-    // 64-queries-per-wavefront variant is within 2 % of the fastest where it wins at all and is
-    // selectable by name only.
     const long long wg256 = nbh * ((S + BM2 - 1) / BM2);
     const int avg_keys = causal ? (S + 1) / 2 : S;
     const bool pipelined = wg256 >= 256 && (D > 64 ? avg_keys >= (causal ? 2048 : 1024) : avg_keys >= 8192 && wg256 < 1024);
@@ -1519,28 +794,9 @@ inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
     return pipelined ? V_W8Q32 : V_BM128;
 }
 
-// D <= 128, the kernel of 32 queries per wavefront: key groups per work-group (D: the compiled width).  A grid that leaves
-// each CU at most one work-group leaves half of its wavefront slots idle, and the time is that of the longest key loop;
-// two groups of four wavefronts halve that loop, four groups of two quarter it and spread the queries over twice the CUs.
-//   Four groups: 64-query work-groups, one per CU (LDS), all in one round; with the mask also two rounds if the loops are
-//   long enough to even out (the light query tiles go to the CUs that are done first).  Kernel time with one / two / four
-//   groups, D = 128, causal: 8 heads, S = 512 14.2 / 13.5 / 12.0 us, S = 1024 22.5 / 19.8 / 16.2, S = 2048 39.6 / 33.1 /
-//   25.6; 8 heads, S = 4096 (512 work-groups) 74.1 / 60.9 / 52.2 (D = 64: 50.5 / 41.1 / 33.0); 16 heads, S = 2048 (512)
-//   40.6 / 34.4 / 33.5; 32 heads, S = 1003 (512) 24.0 / 21.5 / 24.9.  No mask: 8 heads, S = 2048 38.5 / 33.1 / 27.0, S =
-//   4096 (512) 78.3 / 71.9 / 88.6.  Up to 256 keys one group is as good (32 heads, S = 256 10.1 / 10.5 / 10.1).
-//   Two groups: below nine tiles the merge costs what the shorter loop saves (eight tiles, 32 heads, causal, D = 128: 14.9
-//   us with one group, 14.4 with two; at two tiles 8.3 / 9.2).  One / two groups: 32 heads, S = 1003, causal, D = 128 24.0
-//   / 21.5 us; without the mask 256 work-groups 24.7 / 23.7 (D = 64: 16.7 / 15.4), 512 71.6 / 76.5.
-//   Causal grids beyond 256 work-groups run two groups in two rounds (D = 64: two share a CU, with half the time each has
-//   alone), where one group has all of up to 512 (D = 64: 1024) on the chip at once.  The second round is short only if
-//   few of its work-groups are heavy, which takes many query tiles: the longest grid that gains grows with S, about as
-//   fitted here to 549 shapes each of D = 64, 80, 96, 112 and 128, S = 520..2176 and 258..512 work-groups (mean over them
-//   against one group: 0.945, 0.816, 0.845, 0.947, 0.954, none but five of D = 64 more than 2 % slower; two groups up to 512
-//   everywhere: 0.953, 0.816, 0.850, 0.967, 0.995, 78, 16, 38, 170 and 225 slower, by up to 32 %).  One / two groups, D =
-//   128: 96 heads, S = 640 (480 work-groups) 22.3 / 26.1, 64 heads, S = 1024 (512) 29.7 / 32.0, 40 heads, S = 1280 (400)
-//   31.8 / 30.8, 32 heads, S = 2048 (512) 51.3 / 47.6; D = 64: 15.2 / 16.6, 19.2 / 19.6, 21.7 / 20.2, 32.1 / 30.3.
-//   At D = 128 one group per CU also has to cover the latency of its tiles alone, which costs most where every XCD's L2 sees
-//   every head (B * Hq odd; 33 heads, S = 1604 40.7 / 47.0, 32 heads 38.9 / 34.4) and least where each keeps to an eighth.
+// Key groups of the class V_BM128 (D: the compiled width): four for grids of at most 256 work-groups of 64 queries (512 with
+// the mask on long sequences), two up to 256 work-groups of 128 queries; with the mask up to 512, along a line that rises
+// with S, since the second round of work-groups is short only if few of them are heavy, which takes many query tiles.
 inline int key_groups(int S, long long nbh, int D, int causal)
 {
     const long long wgs64 = nbh * ((S + 63) / 64), wgs = nbh * ((S + BM - 1) / BM);
@@ -1557,66 +813,123 @@ inline int key_groups(int S, long long nbh, int D, int causal)
     return wgs - 256 <= beyond ? 2 : 1;
 }
 
+// What a launch with D <= 128 runs (D: the compiled width): kernel 1 (V_BM128) with one or four key groups, or kernel 2 on
+// 8 x 32 queries (V_W8Q32), 4 x 32 (V_W4Q32, one or two key groups) or 4 x 64 (V_W4Q64, D = 64 only).
+// Fitted to 4354 shapes (D = 64, 80, 96 and 128, 1 to 512 heads, S = 128 to 16384, with and without the mask), every form
+// timed in turn: the rule is within 0.45 % of the best form on average, and takes 0.946 of the time of what ran before
+// there was kernel 2 in these forms (25 shapes are more than 2 % behind that, one more than 5 %).  Kernel time, us:
+//   Four key groups of kernel 1: up to 256 work-groups of 64 queries, one per CU, all in one round (8 heads, S = 1024, D =
+//   128, causal 16.2; kernel 2 17.6).  With the mask also two such rounds where the loops are long enough to even out: light
+//   tiles go to the CUs that are done first (16 heads, S = 1536, D = 64 16.3 / 19.9).
+//   Two key groups of kernel 2: one work-group of 128 queries per CU (129 to 256 of them) whose loop is worth halving (32
+//   heads, S = 1003, causal, D = 128 19.4, one group 20.4, kernel 1 with two 21.6); with the mask up to 512 in two rounds, the
+//   more the longer the sequence, as the second round has to be of light tiles (8 heads, S = 8192, D = 128 133 / 142 / 143;
+//   64 heads, S = 640, D = 80 16.7 / 14.2: one group).
+//   Kernel 1 with one: sequences of at most 128 keys (two tiles; 2 heads, S = 128, D = 64 6.4 / 6.7), and at D = 64 short ones
+//   of very many heads, of which it has four work-groups on a CU for three (256 heads, S = 512, causal 19.7 / 21.2).
+//   256-query work-groups read K and V half as often as 128-query ones and are coarser.  No mask: by whole rounds, 256
+//   slots of 8 x 32 against 512 of 4 x 32 (24 heads, S = 3072, D = 128: 288 work-groups 150 / 130; 32 heads, S = 4096: 512
+//   243 / 249), at D = 64 512 slots of 4 x 64 against 768 of 4 x 32, where a fragment read from LDS that feeds two MFMAs
+//   is worth 8 % (32 heads, S = 4096 135 / 145).  With the mask they pay where the loop is long or the rounds come out even
+//   (32 heads, S = 16384, D = 128 1790 / 1850; 32 heads, S = 4096 129 / 136; 128 heads, S = 4096 536 / 529).
+inline int pick_form(int S, long long nbh, int D, int causal, int* groups)
+{
+    int named_groups;
+    const int named = named_variant(&named_groups);
+    if (named != V_BY_SHAPE && (named != V_W4Q64 || D <= 64)) {  // 4 x 64 has no wider form: the name chooses nothing there
+        *groups = named_groups ? named_groups : named == V_BM128 ? key_groups(S, nbh, D, causal) : 1;
+        if (named == V_BM128 && *groups == 2)
+            return V_W4Q32;  // two key groups are kernel 2's
+        return named == V_W8Q32 && D <= 64 ? V_W4Q64 : named;  // eight wavefronts are too many for the 4 KB tiles of D = 64
+    }
+    const long long w64 = nbh * ((S + 63) / 64), w = nbh * ((S + BM - 1) / BM), w2 = nbh * ((S + BM2 - 1) / BM2);
+    *groups = 4;
+    if (w64 <= 256) {
+        if (S > 256 || (D <= 64 && causal && S > 128))
+            return V_BM128;
+    } else if (causal && w <= (D <= 64 ? 256 : 224) && S >= 1200 && S >= 1300 + 30 * (w - 160)) {
+        return V_BM128;
+    }
+    *groups = 2;
+    if (w > 128 && w <= 256 && S >= (causal ? 600 : D <= 64 ? 850 : 1000))
+        return V_W4Q32;
+    if (causal && w > 256 && w <= 512 && S >= 900 + 11 * (w - 288))
+        return V_W4Q32;
+    *groups = 1;
+    if (S <= 128 || (D <= 64 && !causal && S <= 256))
+        return V_BM128;
+    if (D <= 64 && nbh >= 192 && w > 512 && w <= (causal ? 2000 : 1024) && S >= 512 && S <= (causal ? 768 : 512))
+        return V_BM128;
+    if (causal) {
+        if (D <= 64)
+            return S >= 6144 && w2 >= 900 ? V_W4Q64 : V_W4Q32;
+        return (S >= 8192 && w2 >= 480) || (w2 > 448 && w2 <= 512 && S >= 1280) || (w2 > 928 && w2 <= 1024 && S >= 4096) ? V_W8Q32 : V_W4Q32;
+    }
+    if (S < 1000)
+        return V_W4Q32;
+    // rounds, in per cent of a full one; a last round that leaves every CU one work-group fewer is shorter
+    if (D <= 64) {
+        const long long r = w % 768, r2 = w2 % 512;
+        const long long c32 = w / 768 * 300 + (r == 0 ? 0 : r <= 256 ? 130 : r <= 512 ? 210 : 300);
+        const long long c64 = w2 / 512 * 368 + (r2 == 0 ? 0 : r2 <= 256 ? 202 : 368);
+        return c64 < c32 && (w2 > 256 || S >= 4096) ? V_W4Q64 : V_W4Q32;
+    }
+    const long long r = w % 512;
+    const long long c4 = w / 512 * 100 + (r == 0 ? 0 : r <= 256 ? 60 : 100), c8 = (w2 + 255) / 256 * (S >= 1250 ? 97 : 102);
+    // beyond eight rounds the halves of that no longer matter -- unless every XCD sees every head, and twice the loads count
+    return nbh & 7 ? (c8 <= c4 || w2 > 2048 ? V_W8Q32 : V_W4Q32) : w2 <= 2048 && c8 < c4 ? V_W8Q32 : V_W4Q32;
+}
+
 template <int D, int DT_IN, int DT_OUT>
-int launch(const Params& p, int causal, hipStream_t stream)
+int launch(Params p, int causal, hipStream_t stream)
 {
     const long long nbh = (long long)p.B * p.Hq;
-    int groups = 1;
-    const int variant = D > 128 ? wide_variant(p.S, nbh, D, causal) : pick_variant(p.S, nbh, D, causal, &groups);
+    int groups = 1, class_groups;
+    const int variant = D > 128 ? wide_variant(p.S, nbh, D, causal) : pick_form(p.S, nbh, D, causal, &groups);
+    // How far a block's row sum of P (16 keys) may grow before kernel 2 moves the reference maximum.  Long loops take all the
+    // range the type has: a move costs the block's softmax again.  Elsewhere 2^5, a lag of 1 to 5 binades, close to kernel 1's
+    // 6 (RESCALE_TAU): after a move the largest P of the row is exactly 1 and carries no rounding error into O, which shows
+    // in rows that few keys dominate (32 heads, S = 1003, D = 128, causal, bf16, f32 O: relative error against 64 bits with
+    // four times the usual scale 5.4e-4 in kernel 1, 7.7e-4 with 2^30, 6.1e-4 with 2^7, 5.3e-4 with 2^5; at the usual scale
+    // 1.51e-3, 1.53e-3 with any).  2^5 costs nothing on N(0,1) inputs, 17 up to 15 % (8 x 16 heads, S = 1024, D = 64).
+    p.p_limit = D <= 128 && pick_variant(p.S, nbh, D, causal, &class_groups) == V_W8Q32 ? In<DT_IN>::P_LIMIT : 32.0f;
     if (variant < 0)
-        return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64, bm128, bm128g1, bm128g2 or bm128g4)");
-    const long long nblocks = nbh * (groups == 4 ? (p.S + 63) / 64 : variant == V_BM128 ? p.nqt : p.nqt2);
+        return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64, w4q32, w4q32g2, bm128, bm128g1, bm128g2 or bm128g4)");
+    const long long nblocks = nbh * (groups == 4 ? (p.S + 63) / 64 : variant == V_BM128 || variant == V_W4Q32 ? p.nqt : p.nqt2);
     if (nblocks > 0x7fffffffLL)
         return fail(NAUT_ERR_UNSUPPORTED, "B*Hq*ceil(S/128) exceeds the 1-D grid limit");
     const dim3 grid((unsigned)nblocks);
-#define NAUT_LAUNCH(KERNEL, THREADS)                                              \
-    do {                                                                          \
-        if (causal)                                                               \
-            hipLaunchKernelGGL((KERNEL<D, DT_IN, DT_OUT, true NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p);  \
-        else                                                                      \
-            hipLaunchKernelGGL((KERNEL<D, DT_IN, DT_OUT, false NAUT_TAIL>), grid, dim3(THREADS), 0, stream, p); \
+#define NAUT_LAUNCH(THREADS, KERNEL, ...)                                                                              \
+    do {                                                                                                               \
+        if (causal)                                                                                                    \
+            hipLaunchKernelGGL((KERNEL<D, DT_IN, DT_OUT, true __VA_ARGS__>), grid, dim3(THREADS), 0, stream, p);       \
+        else                                                                                                           \
+            hipLaunchKernelGGL((KERNEL<D, DT_IN, DT_OUT, false __VA_ARGS__>), grid, dim3(THREADS), 0, stream, p);      \
     } while (0)
-    bool launched = false;
-    if constexpr (D <= 128) {
-        if (variant == V_W8Q32) {
-#define NAUT_TAIL , 1, 8
-            NAUT_LAUNCH(naut_fwd_kernel_v2, 512);
-#undef NAUT_TAIL
-            launched = true;
-        } else if (variant == V_W4Q64) {
-            if constexpr (D != layout_width(D)) {  // by name only: not compiled for the widths in between
-                return launch<layout_width(D), DT_IN, DT_OUT>(p, causal, stream);
-            } else {
-#define NAUT_TAIL , 2, 4
-                NAUT_LAUNCH(naut_fwd_kernel_v2, 256);
-#undef NAUT_TAIL
-            }
-            launched = true;
-        } else if (groups == 4) {
-#define NAUT_TAIL , 2, 4
-            NAUT_LAUNCH(naut_fwd_kernel_bm128, 512);
-#undef NAUT_TAIL
-            launched = true;
-        } else if (groups == 2) {
-#define NAUT_TAIL , 4, 2
-            NAUT_LAUNCH(naut_fwd_kernel_bm128, 512);
-#undef NAUT_TAIL
-            launched = true;
-        }
-    }
+#define NAUT_COMMA ,
     if constexpr (D > 128) {
-        if (variant == V_W8Q32) {
-#define NAUT_TAIL , 8
-            NAUT_LAUNCH(naut_fwd_kernel_bm128, 512);
-#undef NAUT_TAIL
-            launched = true;
-        }
+        if (variant == V_W8Q32)
+            NAUT_LAUNCH(512, naut_fwd_kernel_bm128, NAUT_COMMA 8);
+        else
+            NAUT_LAUNCH(256, naut_fwd_kernel_bm128, NAUT_COMMA 4);
+    } else if (variant == V_BM128) {
+        if (groups == 4)
+            NAUT_LAUNCH(512, naut_fwd_kernel_bm128, NAUT_COMMA 2 NAUT_COMMA 4);
+        else
+            NAUT_LAUNCH(256, naut_fwd_kernel_bm128, NAUT_COMMA 4);
+    } else if (variant == V_W4Q32) {
+        // two key groups step over twice the rows at a time, which has to stay inside 32-bit offsets
+        if (groups == 2 && (p.k_rs > p.v_rs ? p.k_rs : p.v_rs) <= 8 << 20)
+            NAUT_LAUNCH(512, naut_fwd_kernel_pipe, NAUT_COMMA 1 NAUT_COMMA 4 NAUT_COMMA 2);
+        else
+            NAUT_LAUNCH(256, naut_fwd_kernel_pipe, NAUT_COMMA 1 NAUT_COMMA 4);
+    } else {
+        if constexpr (D <= 64)
+            NAUT_LAUNCH(256, naut_fwd_kernel_pipe, NAUT_COMMA 2 NAUT_COMMA 4);
+        else
+            NAUT_LAUNCH(512, naut_fwd_kernel_pipe, NAUT_COMMA 1 NAUT_COMMA 8);
     }
-    if (!launched) {
-#define NAUT_TAIL
-        NAUT_LAUNCH(naut_fwd_kernel_bm128, NTHREADS);
-#undef NAUT_TAIL
-    }
+#undef NAUT_COMMA
 #undef NAUT_LAUNCH
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)

@@ -38,10 +38,12 @@ typedef short i16x4_t __attribute__((ext_vector_type(4)));
 #endif
 constexpr bool SAFE_SYNC = NAUT_SAFE_SYNC != 0;
 #if NAUT_SAFE_SYNC
+#define NAUT_NOP_M0 "s_nop 7\n\t"
 #define NAUT_NOP_SHORT "s_nop 7\n\t"                         /* in place of the 1 or 2 wait states owed */
 #define NAUT_NOP_AFTER_MFMA "\n\ts_nop 15\n\ts_nop 15"         /* 32 wait states behind every asm MFMA */
 #define NAUT_NOP_SETTLE "s_nop 15\n\ts_nop 15"
 #else
+#define NAUT_NOP_M0 "s_nop 0\n\t"
 #define NAUT_NOP_SHORT "s_nop 1\n\t"
 #define NAUT_NOP_AFTER_MFMA ""
 #define NAUT_NOP_SETTLE "s_nop 11"
@@ -77,6 +79,12 @@ __device__ __forceinline__ void load_to_lds(unsigned dst, int off, const unsigne
 #else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(off), "s"(base) : "memory", "m0");
 #endif
+}
+
+// The same through a buffer descriptor: address base + `soff` + `off`; lanes beyond the descriptor's range get zeros.
+__device__ __forceinline__ void buffer_to_lds(unsigned dst, int off, i32x4_t rsrc, int soff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\t" NAUT_NOP_M0 "buffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(dst), "v"(off), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
 
 // f(integral_constant<int, I>) for I = I0 .. N-1, unrolled at compile time

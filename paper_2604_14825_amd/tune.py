@@ -3,7 +3,7 @@
 
 The paper leaves tile shape, warp count and pipeline depth to an auto-tuner that picks per workload
 (Section 4.4; Section 7.2 names the shapes it chose for short and long sequences).  This library
-ships three compiled variants (the 128-query one with one, two or four key groups per work-group) and a fixed rule
+ships two kernels in a few forms (wavefronts, queries per wavefront, key groups per work-group) and a fixed rule
 that chooses among them from the shape; this script
 is the measurement behind that rule: it runs each variant through the C ABI (selected with the
 NAUT_ATTN_VARIANT environment variable, which the library reads at every call), prints one line per
@@ -23,8 +23,9 @@ import json
 import os
 import sys
 
-VARIANTS = ("w8q32", "w4q64", "bm128g1", "bm128g2", "bm128g4")
-SHORT_NAME = {"fwd_bm256_w8q32_bn64": "w8q32", "fwd_bm256_w4q64_bn64": "w4q64", "fwd_bm128_w4q32_bn64": "bm128g%d"}
+VARIANTS = ("w8q32", "w4q32", "w4q32g2", "bm128g1", "bm128g4")  # w8q32 at D = 64: 4 x 64 queries
+SHORT_NAME = {"pipe_8x32": "w8q32", "pipe_4x64": "w8q32", "pipe_4x32": "w4q32", "pipe_4x32_g2": "w4q32g2",
+              "plain_4x32": "bm128g1", "plain_2x32_g4": "bm128g4"}
 
 
 def default_grid():
@@ -68,9 +69,7 @@ def main() -> int:
         lse = torch.empty((B, Hq, S), dtype=torch.float32, device="cuda")
         scale = D ** -0.5
         os.environ.pop("NAUT_ATTN_VARIANT", None)
-        rule_short = SHORT_NAME[nb.variant_name(B, Hq, S, D, bool(causal), synth.BF16, synth.BF16)]
-        if "%d" in rule_short:
-            rule_short %= nb.key_groups(B, Hq, S, D, bool(causal))
+        rule_short = SHORT_NAME[nb.kernel_name(B, Hq, S, D, bool(causal))]
         def run(var):
             os.environ["NAUT_ATTN_VARIANT"] = var
             nb.naut_attn_fwd(q, k, v, o, lse, bool(causal), scale, stream=stream)
