@@ -2,8 +2,8 @@
 // against a long key/value cache (the paper's second workload, "DC", Section 6).
 //
 // The work is bound by reading K and V once from HBM, not by the matrix pipes, so the key axis is
-// split across work-groups (and again across the four wavefronts of a work-group): every wavefront
-// streams its own 32-key blocks of K and V through a private double buffer in LDS with direct
+// split across work-groups (and again across the eight wavefronts of a work-group): every wavefront
+// streams its own 32-key blocks of K and V through a private buffer of each in LDS with direct
 // global->LDS loads (no work-group barrier in the loop), runs the same transposed MFMA formulation
 // as the prefill kernels on them (S^T = K.Q^T, online softmax with a lazily moved reference maximum,
 // O^T += V^T.P^T), and the partial (O, m, l) triples are merged with the split-merge identity of
@@ -27,11 +27,7 @@ namespace {
 
 using namespace naut;
 
-#ifndef NAUT_DEC_WAVES
-#define NAUT_DEC_WAVES 4
-#endif
-constexpr int DEC_WAVES = NAUT_DEC_WAVES;  // wavefronts of the split kernel, each with a private 4-block LDS region
-constexpr int DEC_THREADS = DEC_WAVES * 64;
+constexpr int DEC_WAVES = 8;               // wavefronts of a split kernel, each with LDS for a block of K and one of V
 constexpr int MRG_WAVES = 4;               // wavefronts of the merge kernel
 constexpr int MRG_THREADS = MRG_WAVES * 64;
 constexpr int DEC_ROWS = 32;               // query rows per work-group (one MFMA tile)
@@ -45,7 +41,7 @@ constexpr float DEC_M_INIT = -1.0e30f;     // finite stand-in for "no maximum ye
 #ifndef NAUT_DEC_TARGET
 #define NAUT_DEC_TARGET 256
 #endif
-constexpr int DEC_TARGET_WGS = NAUT_DEC_TARGET;  // work-groups of a round: one per CU (LDS; the 64 KB of D = 64 would let two share one)
+constexpr int DEC_TARGET_WGS = NAUT_DEC_TARGET;  // work-groups of a round: one per CU (LDS; the 66 KB of D = 64 let two share one)
 
 struct DecodeParams {
     const void* q;
@@ -58,7 +54,7 @@ struct DecodeParams {
     int R;         // query rows per (batch, K/V head) = Hq/Hkv * Sq
     int nchunks;   // ceil(R / 32)
     int nsplit;    // splits of the key axis
-    int bps;       // 32-key blocks per split (a multiple of 4)
+    int bps;       // blocks per split (a multiple of half the wavefronts)
     int causal;
     float c;       // scale * log2(e) (FP8: times descale_q * descale_k), > 0
     float dv;      // factor on O: 1 (16-bit inputs) or descale_v (FP8)
@@ -79,126 +75,139 @@ __device__ __forceinline__ float half_sum_f(float x)
     return a + b;
 }
 
-// Tail of a split kernel: the four wavefronts' partial (O, m, l) are merged through LDS (each wavefront
+// Tail of a split kernel: the wavefronts' partial (O, m, l) are merged through LDS (each wavefront
 // reuses its own, now idle, region of REGION bytes) and the work-group's partial goes to the workspace.
 // m is the reference maximum the wavefront's l and O are relative to (log2 units).
 // With a single split that partial is the result: it is divided by l and stored as O right here, and there is no merge
 // kernel (32/8 heads, D = 128, 512 keys, B = 40, the same single split: 27.9 -> 24.5 us).
 template <int D, int REGION, int NW, int DT_IN>
-__device__ __forceinline__ void merge_wavefronts(unsigned char* smem, const f32x16_t (&oacc)[D / 32], float m_run,
-                                                 float l_run, const DecodeParams& p, int bhk, int chunk, int split)
+__device__ __forceinline__ void merge_wavefronts(unsigned char* smem, float (&ml_lds)[NW][2 * DEC_ROWS], const f32x16_t (&oacc)[D / 32],
+                                                 float m_run, float l_run, const DecodeParams& p, int bhk, int chunk, int split)
 {
     constexpr int DB = D / 32;
-    constexpr int OSTRIDE = D + 4;  // floats per row of the partial O in LDS (padded against bank conflicts)
-    static_assert(DEC_ROWS * OSTRIDE * 4 + 2 * DEC_ROWS * 4 <= REGION, "the wavefront's partial fits its LDS region");
+    constexpr int Q4 = D / 4;  // 16-byte pieces of a row of O
+    static_assert(DEC_ROWS * D * 4 <= REGION, "the wavefront's partial fits its LDS region");
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31;
     const int h = lane >> 5;
-    unsigned char* my_lds = smem + wave * REGION;
-    // ---- merge the four wavefronts through LDS (each reuses its own, now idle, region) ----
-    float* my_o = (float*)my_lds;                          // [32][OSTRIDE]
-    float* my_ml = my_o + DEC_ROWS * OSTRIDE;              // m[32], l[32]
+    const int rows = p.R - chunk * DEC_ROWS < DEC_ROWS ? p.R - chunk * DEC_ROWS : DEC_ROWS;  // the rest is padding
+    // ---- merge the wavefronts through LDS (each reuses its own, now idle, region) ----
+    // piece q4 of row r; the position is XOR-ed with the row, so that neither side conflicts
+    auto piece = [&](int w, int r, int q4) { return (f32x4_t*)(smem + w * REGION) + r * Q4 + (q4 ^ (r & 7)); };
     const float l_tot = half_sum_f(l_run);
+    if (l32 < rows) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            const int d = 32 * db + 8 * gq + 4 * h;
-            const f32x4_t w = {oacc[db][4 * gq + 0], oacc[db][4 * gq + 1], oacc[db][4 * gq + 2], oacc[db][4 * gq + 3]};
-            *(f32x4_t*)(my_o + l32 * OSTRIDE + d) = w;
-        }
+            for (int gq = 0; gq < 4; ++gq)
+                *piece(wave, l32, 8 * db + 2 * gq + h) =
+                    f32x4_t{oacc[db][4 * gq + 0], oacc[db][4 * gq + 1], oacc[db][4 * gq + 2], oacc[db][4 * gq + 3]};
+    }
     if (h == 0) {
-        my_ml[l32] = m_run;
-        my_ml[DEC_ROWS + l32] = l_tot;
+        ml_lds[wave][l32] = m_run;
+        ml_lds[wave][DEC_ROWS + l32] = l_tot;
     }
     __syncthreads();
 
-    // (row, D/8 consecutive d) items, dealt to the threads; partial written to the workspace
-    constexpr int DPT = D / 8;  // floats per item: 32 (D = 256), 16 (D = 128) or 8 (D = 64)
+    // (row, M pieces Q4 / M apart) items, dealt to the threads; partial written to the workspace
     const size_t nparts = (size_t)p.B * p.Hkv * p.nchunks * p.nsplit;
     const size_t part = ((size_t)bhk * p.nchunks + chunk) * p.nsplit + split;
+    auto merge = [&](auto PIECES) {
+        constexpr int M = decltype(PIECES)::value, G = Q4 / M;
+        for (int item = tid; item < rows * G; item += NW * 64) {
+            const int r_out = item / G, g = item % G;
+            float mw[NW], lw[NW];
+            f32x4_t x[NW][M];
+            float m = DEC_M_INIT;
 #pragma unroll
-    for (int item = tid; item < DEC_ROWS * 8; item += NW * 64) {
-    const int r_out = item >> 3, d0 = (item & 7) * DPT;
-    float mw[NW], lw[NW];
-    float M = DEC_M_INIT;
+            for (int w = 0; w < NW; ++w) {
+                mw[w] = ml_lds[w][r_out];
+                lw[w] = ml_lds[w][DEC_ROWS + r_out];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const float* ml = (const float*)(smem + w * REGION) + DEC_ROWS * OSTRIDE;
-        mw[w] = ml[r_out];
-        lw[w] = ml[DEC_ROWS + r_out];
-        M = fmaxf(M, mw[w]);
-    }
-    float L = 0.f;
-    f32x4_t acc[DPT / 4];
+                for (int i = 0; i < M; ++i)
+                    x[w][i] = *piece(w, r_out, g + i * G);
+                m = fmaxf(m, mw[w]);
+            }
+            float l = 0.f;
+            f32x4_t acc[M];
 #pragma unroll
-    for (int i = 0; i < DPT / 4; ++i)
-        acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < M; ++i)
+                acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const float f = __builtin_amdgcn_exp2f(mw[w] - M);
-        L += f * lw[w];
-        const float* ow = (const float*)(smem + w * REGION) + r_out * OSTRIDE + d0;
+            for (int w = 0; w < NW; ++w) {
+                const float f = __builtin_amdgcn_exp2f(mw[w] - m);
+                l += f * lw[w];
 #pragma unroll
-        for (int i = 0; i < DPT / 4; ++i) {
-            const f32x4_t x = *(const f32x4_t*)(ow + 4 * i);
-            acc[i] += x * f;
+                for (int i = 0; i < M; ++i)
+                    acc[i] += x[w][i] * f;
+            }
+            if (p.nsplit == 1) {
+                const int r = chunk * DEC_ROWS + r_out;
+                const float inv_l = p.dv / l;
+                // lse is dense [B][Hq][Sq]: the R rows of (batch, K/V head) bhk are contiguous there
+                if (p.lse != nullptr && g == 0)
+                    p.lse[(size_t)bhk * p.R + r] = (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+                const int b = bhk / p.Hkv, hk = bhk % p.Hkv;
+                const int head = hk * (p.Hq / p.Hkv) + r / p.Sq, pos = r % p.Sq;
+                unsigned char* orow = (unsigned char*)p.o + b * p.o_bs + head * p.o_hs + (long long)pos * p.o_rs;
+#pragma unroll
+                for (int i = 0; i < M; ++i) {
+                    const int d = 4 * (g + i * G);
+                    if (d >= p.cpr * 8)
+                        break;  // padding columns of a narrower head dimension
+                    const f32x4_t y = acc[i] * inv_l;
+                    if (p.out_f32)
+                        *(f32x4_t*)(orow + d * 4) = y;
+                    else
+                        *(i32x2_t*)(orow + d * 2) = i32x2_t{In<DT_IN>::pack2(y.x, y.y), In<DT_IN>::pack2(y.z, y.w)};
+                }
+                continue;
+            }
+#pragma unroll
+            for (int i = 0; i < M; ++i)
+                *(f32x4_t*)(p.ws + (part * DEC_ROWS + r_out) * D + 4 * (g + i * G)) = acc[i];
+            if (g == 0) {
+                float* ws_m = p.ws + nparts * DEC_ROWS * D;
+                float* ws_l = ws_m + nparts * DEC_ROWS;
+                ws_m[part * DEC_ROWS + r_out] = m;
+                ws_l[part * DEC_ROWS + r_out] = l;
+            }
         }
-    }
-    if (chunk * DEC_ROWS + r_out >= p.R)
-        continue;  // rows past the last one are padding: nobody reads their partials
-    if (p.nsplit == 1) {
-        const int r = chunk * DEC_ROWS + r_out;
-        const float inv_l = p.dv / L;
-        // lse is dense [B][Hq][Sq]: the R rows of (batch, K/V head) bhk are contiguous there
-        if (p.lse != nullptr && (item & 7) == 0)
-            p.lse[(size_t)bhk * p.R + r] = (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
-        const int b = bhk / p.Hkv, hk = bhk % p.Hkv;
-        const int head = hk * (p.Hq / p.Hkv) + r / p.Sq, pos = r % p.Sq;
-        unsigned char* orow = (unsigned char*)p.o + b * p.o_bs + head * p.o_hs + (long long)pos * p.o_rs;
-#pragma unroll
-        for (int i = 0; i < DPT / 4; ++i) {
-            const int d = d0 + 4 * i;
-            if (d >= p.cpr * 8)
-                break;  // padding columns of a narrower head dimension
-            const f32x4_t y = acc[i] * inv_l;
-            if (p.out_f32)
-                *(f32x4_t*)(orow + d * 4) = y;
-            else
-                *(i32x2_t*)(orow + d * 2) = i32x2_t{In<DT_IN>::pack2(y.x, y.y), In<DT_IN>::pack2(y.z, y.w)};
-        }
-        continue;
-    }
-    float* ws_o = p.ws + (part * DEC_ROWS + r_out) * D + d0;
-#pragma unroll
-    for (int i = 0; i < DPT / 4; ++i)
-        *(f32x4_t*)(ws_o + 4 * i) = acc[i];
-    if ((item & 7) == 0) {
-        float* ws_m = p.ws + nparts * DEC_ROWS * D;
-        float* ws_l = ws_m + nparts * DEC_ROWS;
-        ws_m[part * DEC_ROWS + r_out] = M;
-        ws_l[part * DEC_ROWS + r_out] = L;
-    }
-    }
+    };
+    // as few pieces per thread as take the rows in one pass, so that few threads are idle (a row's exponentials and latency
+    // are shared by its pieces); at most four
+    constexpr int FULL = DEC_ROWS * Q4 / (NW * 64);
+    if (FULL == 1 || rows * Q4 <= NW * 64)
+        merge(std::integral_constant<int, 1>{});
+    else if (FULL == 2 || rows * Q4 <= 2 * NW * 64)
+        merge(std::integral_constant<int, 2>{});
+    else
+        merge(std::integral_constant<int, 4>{});
 }
 
-// wavefronts of the 16-bit split kernel: the four LDS blocks of a wavefront are 64 KB at D = 256
-constexpr int dec_waves(int D) { return D > 128 ? 2 : DEC_WAVES; }
+// wavefronts of the split kernel (or half as many: see half_waves); the two LDS blocks of one are 32 KB at D = 256
+constexpr int dec_waves(int D) { return D > 128 ? DEC_WAVES / 2 : DEC_WAVES; }
 
-template <int D, int DT_IN>
-__global__ __launch_bounds__(dec_waves(D) * 64, 1) void naut_decode_split_kernel(const DecodeParams p)
+// A wavefront has one buffer for K and one for V: the next block's K is requested when this block's K fragments are in
+// registers, its V when the V fragments are.  Twice as many wavefronts as with two buffers of each keep as many bytes in
+// flight (128 KB per CU), and cover a block's scores, softmax and P.V with each other's loads; the first block's loads
+// are out before Q's.  Against four wavefronts with two buffers (us a call, 32/8 heads, D = 128): 20 caches of 2000 keys 34.1 ->
+// 31.0, 40 of 500 24.9 -> 22.1, 8 of 16384 94.4 -> 93.8; D = 256, 16/8 heads, 256 keys 11.6 -> 10.7.
+template <int D, int DT_IN, int NW>
+__global__ __launch_bounds__(NW * 64, 1) void naut_decode_split_kernel(const DecodeParams p)
 {
     using T = In<DT_IN>;
-    constexpr int NW = dec_waves(D);
+    constexpr int REGION = 2 * DEC_BLK * D * 2;  // LDS of a wavefront
     constexpr int ROWB = D * 2;
     constexpr int BLKB = DEC_BLK * ROWB;   // one 32-key block of K or V
     constexpr int KS = D / 16;
     constexpr int DB = D / 32;
     constexpr int NLD = BLKB / 1024;       // direct loads (1 KB each) per block and operand
 
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * 4 * BLKB];  // per wavefront: K0 V0 K1 V1
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * REGION];  // per wavefront: K, V
+    __shared__ float ml_lds[NW][2 * DEC_ROWS];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -223,15 +232,16 @@ __global__ __launch_bounds__(dec_waves(D) * 64, 1) void naut_decode_split_kernel
     const int lim = p.causal ? Sk - p.Sq + (row_ld % p.Sq) : Sk - 1;
 
     i32x4_t qf[KS];
+    auto load_q = [&]() {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        qf[ks] = ks * 2 + h < p.cpr
-                     ? *(const i32x4_t*)(qg + (row_ld / p.Sq) * p.q_hs + (long long)(row_ld % p.Sq) * p.q_rs + ks * 32 + h * 16)
-                     : i32x4_t{0, 0, 0, 0};
+        for (int ks = 0; ks < KS; ++ks)
+            qf[ks] = ks * 2 + h < p.cpr
+                         ? *(const i32x4_t*)(qg + (row_ld / p.Sq) * p.q_hs + (long long)(row_ld % p.Sq) * p.q_rs + ks * 32 + h * 16)
+                         : i32x4_t{0, 0, 0, 0};
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        asm volatile("" : "+v"(qf[ks]));
-
+        for (int ks = 0; ks < KS; ++ks)
+            asm volatile("" : "+v"(qf[ks]));
+    };
     // Direct global->LDS loads: instruction n fills physical chunks 64n..64n+63 of the block, lane i
     // the chunk 64n+i, so the lane fetches the logical chunk that the swizzle maps there.
     // (row of the block, byte inside the row) of that logical chunk:
@@ -259,30 +269,30 @@ __global__ __launch_bounds__(dec_waves(D) * 64, 1) void naut_decode_split_kernel
             v_col[n] = (vc < p.cpr ? vc : p.cpr - 1) * 16;
         }
     }
-    const unsigned lds0 = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem + (unsigned)(wave * 4 * BLKB);
-    unsigned char* my_lds = smem + wave * 4 * BLKB;
+    const unsigned lds0 = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem + (unsigned)(wave * REGION);
+    unsigned char* my_lds = smem + wave * REGION;
 
     const int nblk = (Sk + DEC_BLK - 1) / DEC_BLK;
     const int blk_begin = split * p.bps;
     const int blk_end = blk_begin + p.bps < nblk ? blk_begin + p.bps : nblk;
 
-    auto issue = [&](int blk, int buf) {
-        const unsigned char* kp = kg + (size_t)blk * DEC_BLK * p.k_rs;
-        const unsigned char* vp = vg + (size_t)blk * DEC_BLK * p.v_rs;
+    // K (OP = 0) or V (OP = 1) of a block into its buffer
+    auto issue = [&](auto OP, int blk) {
+        constexpr bool V = decltype(OP)::value != 0;
+        const int rs = V ? p.v_rs : p.k_rs;
+        const unsigned char* const base = (V ? vg : kg) + (size_t)blk * DEC_BLK * rs;
         const int rows_left = Sk - blk * DEC_BLK;  // >= 1
-        const unsigned dst = lds0 + (unsigned)(buf * 2 * BLKB);
+        const unsigned dst = lds0 + (V ? BLKB : 0);
 #pragma unroll
         for (int n = 0; n < NLD; ++n) {
-            int kr = k_row[n], vr = v_row[n];
-            if (rows_left < DEC_BLK) {  // ragged last block: re-read the last row instead of running past the end
-                kr = kr < rows_left ? kr : rows_left - 1;
-                vr = vr < rows_left ? vr : rows_left - 1;
-            }
-            const int ko = kr * p.k_rs + k_col[n], vo = vr * p.v_rs + v_col[n];
-            load_to_lds(dst + n * 1024, ko, kp);
-            load_to_lds(dst + BLKB + n * 1024, vo, vp);
+            int r = V ? v_row[n] : k_row[n];
+            if (rows_left < DEC_BLK)  // ragged last block: re-read the last row instead of running past the end
+                r = r < rows_left ? r : rows_left - 1;
+            load_to_lds(dst + n * 1024, r * rs + (V ? v_col[n] : k_col[n]), base);
         }
     };
+    constexpr std::integral_constant<int, 0> OPK{};
+    constexpr std::integral_constant<int, 1> OPV{};
 
     f32x16_t oacc[DB];
 #pragma unroll
@@ -293,21 +303,18 @@ __global__ __launch_bounds__(dec_waves(D) * 64, 1) void naut_decode_split_kernel
     float m_run = DEC_M_INIT;  // reference maximum, log2 units (already times c)
     float l_run = 0.f;         // this lane's share of the running sum (its 16 of every 32 keys)
 
-    // This wavefront's blocks: blk_begin + wave, + NW, ...  Block n+1 is in flight while block n is used.
+    // This wavefront's blocks: blk_begin + wave, + NW, ...
     static_assert(2 * NLD < 64, "vmcnt field");
     int blk = blk_begin + wave;
-    if (blk < blk_end)
-        issue(blk, 0);
-    for (int it = 0; blk < blk_end; blk += NW, ++it) {
-        const int buf = it & 1;
+    if (blk < blk_end) {
+        issue(OPK, blk);
+        issue(OPV, blk);
+    }
+    load_q();
+    for (; blk < blk_end; blk += NW) {
         const bool more = blk + NW < blk_end;
-        if (more) {
-            issue(blk + NW, buf ^ 1);
-            wait_loads<2 * NLD>();
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
-        const unsigned char* kt = my_lds + buf * 2 * BLKB;
+        wait_loads<NLD>();  // this block's K; its V may still be on its way
+        const unsigned char* kt = my_lds;
         const unsigned char* vt = kt + BLKB;
 
         f32x16_t s_;
@@ -318,6 +325,10 @@ __global__ __launch_bounds__(dec_waves(D) * 64, 1) void naut_decode_split_kernel
         for (int ks = 0; ks < KS; ++ks) {
             const i32x4_t kf = *(const i32x4_t*)(kt + k_off<D>(l32, ks * 2 + h));
             s_ = T::mfma(kf, qf[ks], s_);
+        }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the K fragments are in registers
+            issue(OPK, blk + NW);
         }
         const int key0 = blk * DEC_BLK;
         if (key0 + DEC_BLK - 1 > Sk - p.Sq || key0 + DEC_BLK > Sk) {  // some row's limit may fall inside the block
@@ -351,6 +362,10 @@ __global__ __launch_bounds__(dec_waves(D) * 64, 1) void naut_decode_split_kernel
             psum = r == 0 ? s_[r] : psum + s_[r];
         }
         l_run += psum;
+        if (more)
+            wait_loads<NLD>();  // this block's V; the next one's K may still be on its way
+        else
+            wait_loads<0>();
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const int r0 = t * 8;
@@ -362,9 +377,13 @@ __global__ __launch_bounds__(dec_waves(D) * 64, 1) void naut_decode_split_kernel
                 oacc[db] = T::mfma(vf, pb, oacc[db]);
             }
         }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the V fragments too
+            issue(OPV, blk + NW);
+        }
     }
 
-    merge_wavefronts<D, 4 * BLKB, NW, DT_IN>(smem, oacc, m_run, l_run, p, bhk, chunk, split);
+    merge_wavefronts<D, REGION, NW, DT_IN>(smem, ml_lds, oacc, m_run, l_run, p, bhk, chunk, split);
 }
 
 // The same split kernel on FP8 (E4M3) Q, K and V: 64-key blocks (one 32x32x64 MFMA covers 64 keys of
@@ -377,16 +396,18 @@ constexpr int DEC8_BLK = 64;
 constexpr float DEC8_TAU = 1.0f;      // P * 2^7 <= 2^(1+7) = 256 < 448, the largest E4M3 value
 constexpr float DEC8_P_SHIFT = 7.0f;
 
-template <int D>
-__global__ __launch_bounds__(DEC_THREADS, 1) void naut_decode_split_fp8_kernel(const DecodeParams p)
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 1) void naut_decode_split_fp8_kernel(const DecodeParams p)
 {
     constexpr int BLKB = DEC8_BLK * D;     // bytes of one 64-key block of K or V
+    constexpr int REGION = 2 * BLKB;
     constexpr int KS = D / 64;
     constexpr int DB = D / 32;
     constexpr int CPR = D / 16;            // 16-byte chunks per row
     constexpr int NLD = BLKB / 1024;       // direct loads (1 KB each) per block and operand
 
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[DEC_WAVES * 4 * BLKB];  // per wavefront: K0 V0 K1 V1
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * REGION];  // per wavefront: K, V
+    __shared__ float ml_lds[NW][2 * DEC_ROWS];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -412,18 +433,19 @@ __global__ __launch_bounds__(DEC_THREADS, 1) void naut_decode_split_fp8_kernel(c
 
     // Q^T fragments (MFMA B operand): lane holds q[row][64*ks + 32*h .. +32]
     i32x8_t qf[KS];
+    auto load_q = [&]() {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const unsigned char* qrow = qg + (row_ld / p.Sq) * p.q_hs + (long long)(row_ld % p.Sq) * p.q_rs;
-        const int c0 = ks * 4 + h * 2;  // this lane's two 16-byte chunks of the row
-        const i32x4_t lo = c0 < cpr16 ? *(const i32x4_t*)(qrow + c0 * 16) : i32x4_t{0, 0, 0, 0};
-        const i32x4_t hi = c0 + 1 < cpr16 ? *(const i32x4_t*)(qrow + c0 * 16 + 16) : i32x4_t{0, 0, 0, 0};
-        qf[ks] = i32x8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    }
+        for (int ks = 0; ks < KS; ++ks) {
+            const unsigned char* qrow = qg + (row_ld / p.Sq) * p.q_hs + (long long)(row_ld % p.Sq) * p.q_rs;
+            const int c0 = ks * 4 + h * 2;  // this lane's two 16-byte chunks of the row
+            const i32x4_t lo = c0 < cpr16 ? *(const i32x4_t*)(qrow + c0 * 16) : i32x4_t{0, 0, 0, 0};
+            const i32x4_t hi = c0 + 1 < cpr16 ? *(const i32x4_t*)(qrow + c0 * 16 + 16) : i32x4_t{0, 0, 0, 0};
+            qf[ks] = i32x8_t{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        }
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        asm volatile("" : "+v"(qf[ks]));
-
+        for (int ks = 0; ks < KS; ++ks)
+            asm volatile("" : "+v"(qf[ks]));
+    };
     // Direct global->LDS loads: instruction n fills physical 16-byte chunks 64n..64n+63 of the block, lane i
     // the chunk 64n+i, so the lane fetches the logical chunk that k8_off / v8_off place there.
     int k_row[NLD], k_col[NLD], v_row[NLD], v_col[NLD];
@@ -439,30 +461,30 @@ __global__ __launch_bounds__(DEC_THREADS, 1) void naut_decode_split_fp8_kernel(c
         const int vc = (((pc >> 1) ^ key) << 1) + (pc & 1);  // likewise for v8_off (32-byte chunks, two halves)
         v_col[n] = (vc < cpr16 ? vc : cpr16 - 1) * 16;
     }
-    const unsigned lds0 = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem + (unsigned)(wave * 4 * BLKB);
-    unsigned char* my_lds = smem + wave * 4 * BLKB;
+    const unsigned lds0 = (unsigned)(uintptr_t)(NAUT_LDS unsigned char*)smem + (unsigned)(wave * REGION);
+    unsigned char* my_lds = smem + wave * REGION;
 
     const int nblk = (Sk + DEC8_BLK - 1) / DEC8_BLK;
     const int blk_begin = split * p.bps;
     const int blk_end = blk_begin + p.bps < nblk ? blk_begin + p.bps : nblk;
 
-    auto issue = [&](int blk, int buf) {
-        const unsigned char* kp = kg + (size_t)blk * DEC8_BLK * p.k_rs;
-        const unsigned char* vp = vg + (size_t)blk * DEC8_BLK * p.v_rs;
+    // K (OP = 0) or V (OP = 1) of a block into its buffer
+    auto issue = [&](auto OP, int blk) {
+        constexpr bool V = decltype(OP)::value != 0;
+        const int rs = V ? p.v_rs : p.k_rs;
+        const unsigned char* const base = (V ? vg : kg) + (size_t)blk * DEC8_BLK * rs;
         const int rows_left = Sk - blk * DEC8_BLK;  // >= 1
-        const unsigned dst = lds0 + (unsigned)(buf * 2 * BLKB);
+        const unsigned dst = lds0 + (V ? BLKB : 0);
 #pragma unroll
         for (int n = 0; n < NLD; ++n) {
-            int kr = k_row[n], vr = v_row[n];
-            if (rows_left < DEC8_BLK) {  // ragged last block: re-read the last row instead of running past the end
-                kr = kr < rows_left ? kr : rows_left - 1;
-                vr = vr < rows_left ? vr : rows_left - 1;
-            }
-            const int ko = kr * p.k_rs + k_col[n], vo = vr * p.v_rs + v_col[n];
-            load_to_lds(dst + n * 1024, ko, kp);
-            load_to_lds(dst + BLKB + n * 1024, vo, vp);
+            int r = V ? v_row[n] : k_row[n];
+            if (rows_left < DEC8_BLK)  // ragged last block: re-read the last row instead of running past the end
+                r = r < rows_left ? r : rows_left - 1;
+            load_to_lds(dst + n * 1024, r * rs + (V ? v_col[n] : k_col[n]), base);
         }
     };
+    constexpr std::integral_constant<int, 0> OPK{};
+    constexpr std::integral_constant<int, 1> OPV{};
 
     // lane-constant parts of the transposed V reads (as in the FP8 prefill kernel)
     const int i16 = lane & 15;
@@ -482,18 +504,15 @@ __global__ __launch_bounds__(DEC_THREADS, 1) void naut_decode_split_fp8_kernel(c
 
     static_assert(2 * NLD < 64, "vmcnt field");
     int blk = blk_begin + wave;
-    if (blk < blk_end)
-        issue(blk, 0);
-    for (int it = 0; blk < blk_end; blk += DEC_WAVES, ++it) {
-        const int buf = it & 1;
-        const bool more = blk + DEC_WAVES < blk_end;
-        if (more) {
-            issue(blk + DEC_WAVES, buf ^ 1);
-            wait_loads<2 * NLD>();
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        }
-        const unsigned char* kt = my_lds + buf * 2 * BLKB;
+    if (blk < blk_end) {
+        issue(OPK, blk);
+        issue(OPV, blk);
+    }
+    load_q();
+    for (; blk < blk_end; blk += NW) {
+        const bool more = blk + NW < blk_end;
+        wait_loads<NLD>();  // this block's K; its V may still be on its way
+        const unsigned char* kt = my_lds;
         const unsigned char* vt = kt + BLKB;
 
         f32x16_t sacc[2];
@@ -510,6 +529,10 @@ __global__ __launch_bounds__(DEC_THREADS, 1) void naut_decode_split_fp8_kernel(c
                 const i32x8_t kf = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
                 sacc[kb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kf, qf[ks], sacc[kb], 0, 0, 0, 0, 0, 0);
             }
+        }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the K fragments are in registers
+            issue(OPK, blk + NW);
         }
         const int key0 = blk * DEC8_BLK;
         if (key0 + DEC8_BLK - 1 > Sk - p.Sq || key0 + DEC8_BLK > Sk) {  // some row's limit may fall inside the block
@@ -551,6 +574,10 @@ __global__ __launch_bounds__(DEC_THREADS, 1) void naut_decode_split_fp8_kernel(c
                 psum = (kb | r) == 0 ? pv : psum + pv;
             }
         l_run += psum;
+        if (more)
+            wait_loads<NLD>();  // this block's V; the next one's K may still be on its way
+        else
+            wait_loads<0>();
 #pragma unroll
         for (int w = 0; w < 8; ++w) {
             const int kb = w >> 2, r0 = (w & 3) * 4;
@@ -569,8 +596,12 @@ __global__ __launch_bounds__(DEC_THREADS, 1) void naut_decode_split_fp8_kernel(c
             }
             oacc[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vf, pb, oacc[db], 0, 0, 0, 0, 0, 0);
         }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the V fragments too
+            issue(OPV, blk + NW);
+        }
     }
-    merge_wavefronts<D, 4 * BLKB, DEC_WAVES, NAUT_BF16>(smem, oacc, m_run - DEC8_P_SHIFT, l_run, p, bhk, chunk, split);
+    merge_wavefronts<D, REGION, NW, NAUT_BF16>(smem, ml_lds, oacc, m_run - DEC8_P_SHIFT, l_run, p, bhk, chunk, split);
 }
 
 // One work-group (four wavefronts) per query row: merges the nsplit > 1 partials of the row, divides by l
@@ -742,33 +773,40 @@ void* static_scratch(int* err)
 // count that reaches 256 work-groups, as it was / the one picked here (us a call, 32/8 heads, one position, D = 128):
 // 4096 keys, B = 9 42.7 / 33.6, B = 12 52.0 / 43.2, B = 20 77.0 / 63.8, B = 33 133 / 113, B = 40 139 / 124.
 // The first count stands, and nothing is priced, where it fills whole rounds (base divides 256) and where a fuller split would
-// leave a wavefront less than two blocks (short caches; a single split, which needs no merge, is not considered there:
-// B = 12, 512 keys runs two splits in 14.6 us, one would take 12.2).
+// leave a wavefront without a block.
+//
+// A cache of at most DEC_ONE_BYTES per K/V head is one split, however few work-groups that makes: a second 128 KB takes one
+// CU about 2.5 us, the merge kernel 7 us where the host paces the calls and 3 us on a stream that runs behind it.  Two splits
+// as it was / one (us a call, D = 128, 32/8 heads, one position): 512 keys 10.7 / 8.4 (from a graph 9.2 / 8.1), 12 caches of
+// 512 keys 11.9 / 10.1; D = 64, 16/4 heads, 1000 keys, four splits, 10.9 / 8.2 (7.1 / 7.1).  At 768 keys one split is no
+// faster where a graph holds the calls (9.4 / 9.2) and slower with more of them (8 caches 11.6 / 12.4).
 //
 // The workspace must hold the least count's partials (the first count that reaches 256 work-groups); with less room than
 // the picked count needs, the best candidate that fits is taken.  No count takes more than DEC_MAX_PARTS partials unless
-// the least does, so the 16 MiB static scratch holds the picked count wherever it holds the least (D <= 128).
+// the least does, so the 16 MiB static scratch holds the picked count wherever it holds the least (D <= 128).  Both sizes
+// are those of the counts above also where one split is taken and nothing is written there.
 constexpr unsigned DEC_MAX_PARTS = 960;
+constexpr size_t DEC_ONE_BYTES = 256u << 10;  // K and V of 512 keys at D = 128 in 16 bits
 
 bool make_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int block_bytes, size_t room, Plan* pl)
 {
-    const unsigned W = dec_waves(D);  // 2 or 4
+    const unsigned W = dec_waves(D), G = W / 2;  // 8 or 4; a split is a multiple of G blocks
     const long long R = (long long)(Hq / Hkv) * Sq;
     const long long nchunks = (R + DEC_ROWS - 1) / DEC_ROWS;
     if (nchunks > 65535 || (long long)B * Hkv > 65535 || R > 0x7fffffffLL)
         return false;
     const unsigned nblk = ((unsigned)Sk + DEC_BLK - 1) / DEC_BLK;
     const unsigned base = (unsigned)B * Hkv * (unsigned)nchunks;
-    const unsigned max_split = (nblk + 2 * W - 1) / (2 * W);  // at least two blocks per wavefront
+    const unsigned max_split = (nblk + W - 1) / W;  // a block per wavefront
     const unsigned part_bytes = DEC_ROWS * (D + 2) * sizeof(float);
     // a count without empty splits, and its blocks per split
     auto settle = [&](unsigned n, unsigned* bps) {
         n = n > max_split ? max_split : n < 1 ? 1 : n;
         if (n == 1) {
-            *bps = (nblk + W - 1) / W * W;
+            *bps = (nblk + G - 1) / G * G;
             return 1u;
         }
-        *bps = ((nblk + n - 1) / n + W - 1) / W * W;
+        *bps = ((nblk + n - 1) / n + G - 1) / G * G;
         return (nblk + *bps - 1) / *bps;
     };
     unsigned bps;
@@ -779,11 +817,19 @@ bool make_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int block_bytes, s
     pl->nsplit = (int)least;
     pl->bps = (int)bps;
     pl->ws_least = pl->ws_bytes = (size_t)parts * part_bytes;
-    // No other candidate: a fuller split would leave a wavefront less than two blocks, or the least fills whole rounds.
-    if (first >= max_split || first * base == DEC_TARGET_WGS || room < pl->ws_least)
+    if (room < pl->ws_least)
+        return true;  // the caller refuses it
+    const bool one = (size_t)nblk * block_bytes <= DEC_ONE_BYTES;
+    if (one) {
+        pl->nsplit = 1;
+        pl->bps = (int)((nblk + G - 1) / G * G);
+    }
+    // No other candidate: a fuller split would leave a wavefront without a block, or the least fills whole rounds.
+    if (first >= max_split || first * base == DEC_TARGET_WGS)
         return true;
     const unsigned most = parts > DEC_MAX_PARTS ? parts : DEC_MAX_PARTS;
     const double block_us = block_bytes * (2.9 / 65536.0);  // a block per CU while the whole chip streams
+    unsigned picked = least, picked_bps = bps;
     double best = 0.0;
     for (unsigned rounds = 1; rounds <= 4; ++rounds) {
         unsigned b;
@@ -794,26 +840,51 @@ bool make_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int block_bytes, s
         const double turn = b * block_us, share = rest * (1.0 / DEC_TARGET_WGS);
         const double us = full * (turn + 2.0) + (rest ? turn * (share > 0.45 ? share : 0.45) + 2.0 : 0.0) + (n > 1 ? 7.0 : 0.0);
         if (rounds == 1 || us < best) {
-            pl->nsplit = (int)n;
-            pl->bps = (int)b;
+            picked = n;
+            picked_bps = b;
             best = us;
         }
         if (n >= max_split)
             break;
     }
-    if ((unsigned)pl->nsplit > least)
-        pl->ws_bytes = (size_t)base * pl->nsplit * part_bytes;
+    if (picked > least)
+        pl->ws_bytes = (size_t)base * picked * part_bytes;
+    if (!one) {
+        pl->nsplit = (int)picked;
+        pl->bps = (int)picked_bps;
+    }
     return true;
 }
 
 constexpr int dec_width(int D) { return D <= 64 ? 64 : D <= 128 ? 128 : 256; }
 constexpr int block_bytes16(int D) { return 2 * DEC_BLK * D * 2; }  // K and V of one block
 
+// Whether the split kernel runs on half of its wavefronts, which lets two work-groups (D = 64: four) share a CU:
+// - where the others would have no block, and at D <= 128 up to twice that (a block or two per wavefront: the merge of four
+//   partials is shorter than that of eight by what the second block costs, and short caches fill the chip with twice the
+//   work-groups; us a call before / all / half: 30 caches of 16 heads, 128 keys 15.0 / 13.2 / 10.1, 5 caches of 1326
+//   keys, 2 heads, 32 rows 10.5 / 10.7 / 10.5; D = 256, 512 keys, 8 heads 11.8 / 10.9 / 12.5);
+// - in 16 bits at D > 64 where there are more work-groups than CUs: the second one's loads fill the gaps of the first and the last
+//   round is shorter (320 of 512 keys 25.0 / 22.1 / 19.6, D = 256 49.1 / 42.6 / 37.5; 288 of 3000 87.5 / 83.9 / 81.1).
+//   FP8 gains nothing (320 of 1000 keys 24.8 / 21.9 / 23.5), and at D = 64 two of all fit anyway (264 of 9000 keys
+//   117.6 / 114.6 / 117.5).
+template <int D, bool FP8>
+bool half_waves(const DecodeParams& p)
+{
+    constexpr int W = dec_waves(D);
+    return p.bps <= (D > 128 ? W / 2 : W) ||
+           (!FP8 && D > 64 && (long long)p.nsplit * p.nchunks * p.B * p.Hkv > DEC_TARGET_WGS);
+}
+
 template <int D, int DT_IN, int DT_OUT>
 int launch_decode(const DecodeParams& p, hipStream_t stream)
 {
     const dim3 g1((unsigned)p.nsplit, (unsigned)p.nchunks, (unsigned)(p.B * p.Hkv));
-    hipLaunchKernelGGL((naut_decode_split_kernel<D, DT_IN>), g1, dim3(dec_waves(D) * 64), 0, stream, p);
+    constexpr int W = dec_waves(D);
+    if (half_waves<D, false>(p))
+        hipLaunchKernelGGL((naut_decode_split_kernel<D, DT_IN, W / 2>), g1, dim3(W / 2 * 64), 0, stream, p);
+    else
+        hipLaunchKernelGGL((naut_decode_split_kernel<D, DT_IN, W>), g1, dim3(W * 64), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_launch(e);
@@ -1073,10 +1144,16 @@ int naut_attn_decode_fp8_strided(const void* q, const void* k, const void* v, vo
     p.cpr = D / 8;
     hipStream_t hs = (hipStream_t)stream;
     const dim3 g1((unsigned)p.nsplit, (unsigned)p.nchunks, (unsigned)(p.B * p.Hkv));
-    if (DK == 128)
-        hipLaunchKernelGGL((naut_decode_split_fp8_kernel<128>), g1, dim3(DEC_THREADS), 0, hs, p);
+    constexpr int W = DEC_WAVES;
+    const bool half = half_waves<128, true>(p);  // D = 64 has the same rule
+    if (DK == 128 && half)
+        hipLaunchKernelGGL((naut_decode_split_fp8_kernel<128, W / 2>), g1, dim3(W / 2 * 64), 0, hs, p);
+    else if (DK == 128)
+        hipLaunchKernelGGL((naut_decode_split_fp8_kernel<128, W>), g1, dim3(W * 64), 0, hs, p);
+    else if (half)
+        hipLaunchKernelGGL((naut_decode_split_fp8_kernel<64, W / 2>), g1, dim3(W / 2 * 64), 0, hs, p);
     else
-        hipLaunchKernelGGL((naut_decode_split_fp8_kernel<64>), g1, dim3(DEC_THREADS), 0, hs, p);
+        hipLaunchKernelGGL((naut_decode_split_fp8_kernel<64, W>), g1, dim3(W * 64), 0, hs, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail_launch(e);
