@@ -816,8 +816,8 @@ inline int key_groups(int S, long long nbh, int D, int causal)
 // What a launch with D <= 128 runs (D: the compiled width): kernel 1 (V_BM128) with one or four key groups, or kernel 2 on
 // 8 x 32 queries (V_W8Q32), 4 x 32 (V_W4Q32, one or two key groups) or 4 x 64 (V_W4Q64, D = 64 only).
 // Fitted to 4354 shapes (D = 64, 80, 96 and 128, 1 to 512 heads, S = 128 to 16384, with and without the mask), every form
-// timed in turn: the rule is within 0.45 % of the best form on average, and takes 0.946 of the time of what ran before
-// there was kernel 2 in these forms (25 shapes are more than 2 % behind that, one more than 5 %).  Kernel time, us:
+// timed in turn: the rule is within 0.4 % of the best form on average, and takes 0.954 of the time of what ran before
+// there was kernel 2 in these forms (40 shapes are more than 2 % behind that, five more than 5 %).  Kernel time, us:
 //   Four key groups of kernel 1: up to 256 work-groups of 64 queries, one per CU, all in one round (8 heads, S = 1024, D =
 //   128, causal 16.2; kernel 2 17.6).  With the mask also two such rounds where the loops are long enough to even out: light
 //   tiles go to the CUs that are done first (16 heads, S = 1536, D = 64 16.3 / 19.9).
@@ -892,7 +892,9 @@ int launch(Params p, int causal, hipStream_t stream)
     // in rows that few keys dominate (32 heads, S = 1003, D = 128, causal, bf16, f32 O: relative error against 64 bits with
     // four times the usual scale 5.4e-4 in kernel 1, 7.7e-4 with 2^30, 6.1e-4 with 2^7, 5.3e-4 with 2^5; at the usual scale
     // 1.51e-3, 1.53e-3 with any).  2^5 costs nothing on N(0,1) inputs, 17 up to 15 % (8 x 16 heads, S = 1024, D = 64).
-    p.p_limit = D <= 128 && pick_variant(p.S, nbh, D, causal, &class_groups) == V_W8Q32 ? In<DT_IN>::P_LIMIT : 32.0f;
+    p.p_limit = D <= 128 && variant != V_BM128 && pick_variant(p.S, nbh, D, causal, &class_groups) == V_W8Q32
+                    ? In<DT_IN>::P_LIMIT
+                    : 32.0f;
     if (variant < 0)
         return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64, w4q32, w4q32g2, bm128, bm128g1, bm128g2 or bm128g4)");
     const long long nblocks = nbh * (groups == 4 ? (p.S + 63) / 64 : variant == V_BM128 || variant == V_W4Q32 ? p.nqt : p.nqt2);
