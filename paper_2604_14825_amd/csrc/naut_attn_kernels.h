@@ -887,14 +887,14 @@ int launch(Params p, int causal, hipStream_t stream)
     int groups = 1, class_groups;
     const int variant = D > 128 ? wide_variant(p.S, nbh, D, causal) : pick_form(p.S, nbh, D, causal, &groups);
     // How far a block's row sum of P (16 keys) may grow before kernel 2 moves the reference maximum.  Long loops take all the
-    // range the type has: a move costs the block's softmax again.  Elsewhere 2^5, a lag of 1 to 5 binades, close to kernel 1's
-    // 6 (RESCALE_TAU): after a move the largest P of the row is exactly 1 and carries no rounding error into O, which shows
-    // in rows that few keys dominate (32 heads, S = 1003, D = 128, causal, bf16, f32 O: relative error against 64 bits with
-    // four times the usual scale 5.4e-4 in kernel 1, 7.7e-4 with 2^30, 6.1e-4 with 2^7, 5.3e-4 with 2^5; at the usual scale
-    // 1.51e-3, 1.53e-3 with any).  2^5 costs nothing on N(0,1) inputs, 17 up to 15 % (8 x 16 heads, S = 1024, D = 64).
+    // range the type has: a move costs the block's softmax again.  Elsewhere 24, a lag of 1 to 4.6 binades for kernel 1's 6
+    // (RESCALE_TAU): after a move the largest P of the row is exactly 1 and carries no rounding error into O, which shows in
+    // rows that few keys dominate.  Relative error against 64 bits over that of kernel 1 with as many key groups (bf16, f32
+    // O, 256 shapes) with limits of 32, 24 and 16: four times the usual scale 0.99, 0.94, 0.92; twice 0.97, 0.95, 0.91; usual
+    // 0.997, 0.997, 0.996.  24 costs 0.1 % of the time on N(0,1) inputs, 16 1.2 %, 8 up to 13 %.
     p.p_limit = D <= 128 && variant != V_BM128 && pick_variant(p.S, nbh, D, causal, &class_groups) == V_W8Q32
                     ? In<DT_IN>::P_LIMIT
-                    : 32.0f;
+                    : 24.0f;
     if (variant < 0)
         return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64, w4q32, w4q32g2, bm128, bm128g1, bm128g2 or bm128g4)");
     const long long nblocks = nbh * (groups == 4 ? (p.S + 63) / 64 : variant == V_BM128 || variant == V_W4Q32 ? p.nqt : p.nqt2);
