@@ -771,6 +771,14 @@ inline int wide_variant(int S, long long nbh, int D, int causal)
     return 4 * r4 <= 5 * r8 || (r4 == 4 && r8 == 3 && D == 256 && S >= 1024) ? V_BM128 : V_W8Q32;
 }
 
+// Whether a shape of D <= 128 runs long key loops with whole rounds of 256-query work-groups.
+inline bool long_loops(int S, long long nbh, int D, int causal)
+{
+    const long long wg256 = nbh * ((S + BM2 - 1) / BM2);
+    const int avg_keys = causal ? (S + 1) / 2 : S;
+    return wg256 >= 256 && (D > 64 ? avg_keys >= (causal ? 2048 : 1024) : avg_keys >= 8192 && wg256 < 1024);
+}
+
 inline int key_groups(int S, long long nbh, int D, int causal);
 
 // The class that a shape falls into, D <= 128, and the key groups of the class: V_W8Q32 where whole rounds of 256-query
@@ -786,12 +794,10 @@ inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
             *groups = 1;
         return named;
     }
-    const long long wg256 = nbh * ((S + BM2 - 1) / BM2);
-    const int avg_keys = causal ? (S + 1) / 2 : S;
-    const bool pipelined = wg256 >= 256 && (D > 64 ? avg_keys >= (causal ? 2048 : 1024) : avg_keys >= 8192 && wg256 < 1024);
-    if (pipelined)
-        *groups = 1;
-    return pipelined ? V_W8Q32 : V_BM128;
+    if (!long_loops(S, nbh, D, causal))
+        return V_BM128;
+    *groups = 1;
+    return V_W8Q32;
 }
 
 // Key groups of the class V_BM128 (D: the compiled width): four for grids of at most 256 work-groups of 64 queries (512 with
@@ -884,7 +890,7 @@ template <int D, int DT_IN, int DT_OUT>
 int launch(Params p, int causal, hipStream_t stream)
 {
     const long long nbh = (long long)p.B * p.Hq;
-    int groups = 1, class_groups;
+    int groups = 1;
     const int variant = D > 128 ? wide_variant(p.S, nbh, D, causal) : pick_form(p.S, nbh, D, causal, &groups);
     // How far a block's row sum of P (16 keys) may grow before kernel 2 moves the reference maximum.  Long loops take all the
     // range the type has: a move costs the block's softmax again.  Elsewhere 24, a lag of 1 to 4.6 binades for kernel 1's 6
@@ -892,9 +898,7 @@ int launch(Params p, int causal, hipStream_t stream)
     // rows that few keys dominate.  Relative error against 64 bits over that of kernel 1 with as many key groups (bf16, f32
     // O, 256 shapes) with limits of 32, 24 and 16: four times the usual scale 0.99, 0.94, 0.92; twice 0.97, 0.95, 0.91; usual
     // 0.997, 0.997, 0.996.  24 costs 0.1 % of the time on N(0,1) inputs, 16 1.2 %, 8 up to 13 %.
-    p.p_limit = D <= 128 && variant != V_BM128 && pick_variant(p.S, nbh, D, causal, &class_groups) == V_W8Q32
-                    ? In<DT_IN>::P_LIMIT
-                    : 24.0f;
+    p.p_limit = long_loops(p.S, nbh, D, causal) ? In<DT_IN>::P_LIMIT : 24.0f;  // by shape, whatever form is named
     if (variant < 0)
         return fail(NAUT_ERR_UNSUPPORTED, "NAUT_ATTN_VARIANT names no kernel variant (w8q32, w4q64, w4q32, w4q32g2, bm128, bm128g1, bm128g2 or bm128g4)");
     const long long nblocks = nbh * (groups == 4 ? (p.S + 63) / 64 : variant == V_BM128 || variant == V_W4Q32 ? p.nqt : p.nqt2);

@@ -160,3 +160,25 @@ def test_error_is_that_of_the_plain_kernel(D, variant, S, causal, monkeypatch):
             err[name] = ((o.double() - ref).norm() / ref.norm()).item()
         print("error", D, S, causal, hot, variant, "%.4e of %.4e: %.4f" % (err[variant], err["bm128g1"], err[variant] / err["bm128g1"]), flush=True)
         assert err[variant] <= 1.01 * err["bm128g1"]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,S,D,causal", [(16, 4096, 128, True), (16, 4096, 96, False), (4, 16384, 64, False), (48, 640, 128, True), (24, 1500, 128, False)])
+def test_a_named_form_is_the_form_of_the_rule(H, S, D, causal, monkeypatch):
+    """Naming the form that the shape runs anyway changes nothing, bit for bit, also on long loops, where the reference
+    maximum may lag further: comparisons by name time and test what runs."""
+    monkeypatch.delenv("NAUT_ATTN_VARIANT", raising=False)
+    form = nb.kernel_name(1, H, S, D, causal)
+    name = {"pipe_8x32": "w8q32", "pipe_4x64": "w8q32", "pipe_4x32": "w4q32", "pipe_4x32_g2": "w4q32g2"}[form]
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(1, H, S, D, device="cuda", generator=g).to(torch.bfloat16) for _ in range(3))
+    k[:, :, :: S // 40] *= 4  # the maximum grows along the sequence
+    res = []
+    for e in ("", name):
+        monkeypatch.setenv("NAUT_ATTN_VARIANT", e)
+        print("named", H, S, D, causal, form, e, flush=True)
+        o, lse = torch.full(q.shape, math.nan, device="cuda"), torch.full((1, H, S), math.nan, device="cuda")
+        nb.naut_attn_fwd_strided(q, k, v, o, lse, causal, 1.0 / math.sqrt(D))
+        torch.cuda.synchronize()
+        res.append((o, lse))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
