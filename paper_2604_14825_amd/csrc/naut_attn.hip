@@ -195,7 +195,7 @@ const char* naut_attn_fwd_kernel_name(int B, int Hq, int S, int D, int causal)
     case V_W8Q32: return "pipe_8x32";
     case V_W4Q64: return "pipe_4x64";
     case V_W4Q32: return groups == 2 ? "pipe_4x32_g2" : "pipe_4x32";
-    case V_BM128: return groups == 4 ? "plain_2x32_g4" : "plain_4x32";
+    case V_BM128: return groups == 4 ? "plain_2x32_g4" : groups == 2 ? "plain_4x32_g2" : "plain_4x32";
     default: return nullptr;
     }
 }

@@ -169,7 +169,7 @@ struct XMfma<NAUT_F16> {
 //       MFMAs in asm.  It is bound by the dependences of its one instruction stream (46 % of the wavefront time is
 //       waiting), but one work-group of it takes 0.8 times as long as one of the other, so it stays for grids that do
 //       not fill the chip (see wide_variant).
-// NG key groups of NWV wavefronts (D <= 128: four of two; see pick_form): group g takes key tiles g, g + NG, ... through tile
+// NG key groups of NWV wavefronts (D <= 128: two of four or four of two; see pick_form): group g takes key tiles g, g + NG, ... through tile
 // buffers of its own, and the partial (O, m, l) of the groups are merged through LDS at the end.
 // S = 16384, 32 heads, causal, D = 256: 5282 us (833 TFLOP/s) on four wavefronts, 4173 us (1054) on eight under sustained
 // load (three launches at a time, before the clock falls, 5026 / 3922); the D = 128 kernel reaches 1150 to 1190.  D = 192,
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
     constexpr bool WIDE = D > 128;
     constexpr bool ACC = WIDE && NWV == 4;         // O and Q live in the accumulation registers
     constexpr bool PAIR = WIDE && NWV == 8;        // two wavefronts per SIMD on 256 ordinary registers each
-    static_assert(WIDE ? NG == 1 && NWV >= 4 : (NWV == 4 && NG == 1) || (NWV == 2 && NG == 4), "the shapes that are launched");
+    static_assert(WIDE ? NG == 1 && NWV >= 4 : (NWV == 4 && NG <= 2) || (NWV == 2 && NG == 4), "the shapes that are launched");
     constexpr int NB = 4;                          // buffers per operand (wide)
     constexpr int NB2 = NAUT_K1_NBUF;              // buffers per operand (D <= 128)
     constexpr int LDW = TILEB / 1024 / NWV;        // direct loads (1 KB each) per wavefront per tile
@@ -726,8 +726,7 @@ __global__ __launch_bounds__(NWV * NG * 64, D > 128 ? 1 : 2) void naut_fwd_kerne
 // Kernel variants (the tile shape / wavefront count / buffering choice the paper leaves to its
 // auto-tuner, Section 4.4 and Section 7.2).  NAUT_ATTN_VARIANT overrides the shape-based choice for A/B runs (read at every
 // call, so that one process can time all of them; any other non-empty value makes the call fail): kernel 2 as w8q32, w4q32,
-// w4q32g2 or w4q64, kernel 1 as bm128g1 or bm128g4; bm128 is kernel 1 with the key groups of the class (key_groups), and two
-// key groups, which bm128g2 names, are kernel 2's.
+// w4q32g2 or w4q64, kernel 1 as bm128g1, bm128g2 or bm128g4; bm128 is kernel 1 with the key groups of the class (key_groups).
 enum Variant { V_W8Q32 = 0, V_W4Q64 = 1, V_BM128 = 2, V_W4Q32 = 3, V_UNKNOWN = -1, V_BY_SHAPE = -2 };
 constexpr const char* kVariantName[4] = {"fwd_bm256_w8q32_bn64", "fwd_bm256_w4q64_bn64", "fwd_bm128_w4q32_bn64", "fwd_bm128_w4q32_bn32"};
 
@@ -779,30 +778,11 @@ inline bool long_loops(int S, long long nbh, int D, int causal)
     return wg256 >= 256 && (D > 64 ? avg_keys >= (causal ? 2048 : 1024) : avg_keys >= 8192 && wg256 < 1024);
 }
 
-inline int key_groups(int S, long long nbh, int D, int causal);
-
-// The class that a shape falls into, D <= 128, and the key groups of the class: V_W8Q32 where whole rounds of 256-query
-// work-groups run a long key loop, V_BM128 otherwise.  It is what naut_attn_variant_name and naut_attn_key_groups tell;
-// what a launch of either class runs is chosen more finely (pick_form).
-inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
-{
-    int named_groups;
-    const int named = named_variant(&named_groups);
-    *groups = named_groups ? named_groups : key_groups(S, nbh, D, causal);
-    if (named != V_BY_SHAPE && (named != V_W4Q64 || D <= 64)) {  // w4q64 has no wider form: it chooses nothing there
-        if (named == V_W8Q32 || named == V_W4Q64)
-            *groups = 1;
-        return named;
-    }
-    if (!long_loops(S, nbh, D, causal))
-        return V_BM128;
-    *groups = 1;
-    return V_W8Q32;
-}
-
-// Key groups of the class V_BM128 (D: the compiled width): four for grids of at most 256 work-groups of 64 queries (512 with
-// the mask on long sequences), two up to 256 work-groups of 128 queries; with the mask up to 512, along a line that rises
-// with S, since the second round of work-groups is short only if few of them are heavy, which takes many query tiles.
+// Key groups of the shapes without long loops (D: the compiled width): four for grids of at most 256 work-groups of 64
+// queries (512 with the mask on long sequences), two up to 256 work-groups of 128 queries; with the mask up to 512, along a
+// line that rises with S, since the second round of work-groups is short only if few of them are heavy, which takes many
+// query tiles.  A launch has at least these: every group has a reference maximum of its own, and the more keys there are
+// whose P is exactly 1, the smaller the error of O (see pick_form).
 inline int key_groups(int S, long long nbh, int D, int causal)
 {
     const long long wgs64 = nbh * ((S + 63) / 64), wgs = nbh * ((S + BM - 1) / BM);
@@ -819,18 +799,40 @@ inline int key_groups(int S, long long nbh, int D, int causal)
     return wgs - 256 <= beyond ? 2 : 1;
 }
 
-// What a launch with D <= 128 runs (D: the compiled width): kernel 1 (V_BM128) with one or four key groups, or kernel 2 on
-// 8 x 32 queries (V_W8Q32), 4 x 32 (V_W4Q32, one or two key groups) or 4 x 64 (V_W4Q64, D = 64 only).
-// Fitted to 4354 shapes (D = 64, 80, 96 and 128, 1 to 512 heads, S = 128 to 16384, with and without the mask), every form
-// timed in turn: the rule is within 0.4 % of the best form on average, and takes 0.954 of the time of what ran before
-// there was kernel 2 in these forms (40 shapes are more than 2 % behind that, five more than 5 %).  Kernel time, us:
-//   Four key groups of kernel 1: up to 256 work-groups of 64 queries, one per CU, all in one round (8 heads, S = 1024, D =
-//   128, causal 16.2; kernel 2 17.6).  With the mask also two such rounds where the loops are long enough to even out: light
-//   tiles go to the CUs that are done first (16 heads, S = 1536, D = 64 16.3 / 19.9).
-//   Two key groups of kernel 2: one work-group of 128 queries per CU (129 to 256 of them) whose loop is worth halving (32
-//   heads, S = 1003, causal, D = 128 19.4, one group 20.4, kernel 1 with two 21.6); with the mask up to 512 in two rounds, the
-//   more the longer the sequence, as the second round has to be of light tiles (8 heads, S = 8192, D = 128 133 / 142 / 143;
-//   64 heads, S = 640, D = 80 16.7 / 14.2: one group).
+// The class that a shape falls into, D <= 128, and the key groups of the class: V_W8Q32 for long loops, V_BM128 otherwise.
+// It is what naut_attn_variant_name and naut_attn_key_groups tell; the kernel that a launch of either class runs is
+// pick_form's choice.
+inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
+{
+    int named_groups;
+    const int named = named_variant(&named_groups);
+    *groups = named_groups ? named_groups : key_groups(S, nbh, D, causal);
+    if (named != V_BY_SHAPE && (named != V_W4Q64 || D <= 64)) {  // w4q64 has no wider form: it chooses nothing there
+        if (named == V_W8Q32 || named == V_W4Q64)
+            *groups = 1;
+        return named;
+    }
+    if (!long_loops(S, nbh, D, causal))
+        return V_BM128;
+    *groups = 1;
+    return V_W8Q32;
+}
+
+// What a launch with D <= 128 runs (D: the compiled width): kernel 1 (V_BM128) with one, two or four key groups, or kernel 2
+// on 8 x 32 queries (V_W8Q32), 4 x 32 (V_W4Q32, one or two key groups) or 4 x 64 (V_W4Q64, D = 64 only).
+// Fitted to timings of every form in turn over some 4500 shapes (D = 64, 80, 96 and 128, 1 to 512 heads, S = 128 to 16384,
+// with and without the mask).  Kernel time, us:
+//   Four key groups of kernel 1: where key_groups says four, and on a little shorter and larger grids: up to 256 work-groups
+//   of 64 queries, one per CU, all in one round (8 heads, S = 1024, D = 128, causal 16.2; kernel 2 17.6).  With the mask also
+//   two such rounds where the loops are long enough to even out: light tiles go to the CUs that are done first (16 heads, S =
+//   1536, D = 64 16.3 / 19.9).  Fewer groups there would be as fast (causal, 22 shapes 0.96 of the time), but less accurate:
+//   relative error against 64 bits of two for four 1.02 at the usual scale, up to 1.4 on keys with outliers.
+//   Two key groups of kernel 2: where key_groups says two (fewer: error 1.04, up to 1.4 on keys with outliers), and: one
+//   work-group of 128 queries per CU (129 to 256 of them) whose loop is worth halving (32 heads, S = 1003, causal, D = 128
+//   19.4, one group 20.4, kernel 1 with two 21.6); with the mask up to 512 in two rounds, the more the longer the sequence, as
+//   the second round has to be of light tiles (8 heads, S = 8192, D = 128 133 / 142 / 143).
+//   Two key groups of kernel 1: with the mask, beyond one round, short: the second round's few light tiles are over sooner
+//   (56 heads, S = 640, D = 128 17.5, kernel 2 19.2; D = 80 14.0 / 15.3; 64 heads, S = 640, D = 64 13.3 / 13.8).
 //   Kernel 1 with one: sequences of at most 128 keys (two tiles; 2 heads, S = 128, D = 64 6.4 / 6.7), and at D = 64 short ones
 //   of very many heads, of which it has four work-groups on a CU for three (256 heads, S = 512, causal 19.7 / 21.2).
 //   256-query work-groups read K and V half as often as 128-query ones and are coarser.  No mask: by whole rounds, 256
@@ -844,22 +846,19 @@ inline int pick_form(int S, long long nbh, int D, int causal, int* groups)
     const int named = named_variant(&named_groups);
     if (named != V_BY_SHAPE && (named != V_W4Q64 || D <= 64)) {  // 4 x 64 has no wider form: the name chooses nothing there
         *groups = named_groups ? named_groups : named == V_BM128 ? key_groups(S, nbh, D, causal) : 1;
-        if (named == V_BM128 && *groups == 2)
-            return V_W4Q32;  // two key groups are kernel 2's
         return named == V_W8Q32 && D <= 64 ? V_W4Q64 : named;  // eight wavefronts are too many for the 4 KB tiles of D = 64
     }
+    const int least = long_loops(S, nbh, D, causal) ? 1 : key_groups(S, nbh, D, causal);
     const long long w64 = nbh * ((S + 63) / 64), w = nbh * ((S + BM - 1) / BM), w2 = nbh * ((S + BM2 - 1) / BM2);
     *groups = 4;
-    if (w64 <= 256) {
-        if (S > 256 || (D <= 64 && causal && S > 128))
-            return V_BM128;
-    } else if (causal && w <= (D <= 64 ? 256 : 224) && S >= 1200 && S >= 1300 + 30 * (w - 160)) {
+    if (least == 4 || (w64 <= 256 && D <= 64 && causal && S > 128) ||
+        (causal && w <= (D <= 64 ? 256 : 224) && S >= 1200 && S >= 1300 + 30 * (w - 160)))
         return V_BM128;
-    }
     *groups = 2;
-    if (w > 128 && w <= 256 && S >= (causal ? 600 : D <= 64 ? 850 : 1000))
-        return V_W4Q32;
-    if (causal && w > 256 && w <= 512 && S >= 900 + 11 * (w - 288))
+    if (least == 2 && causal && w > 256 && (D > 64 ? S < 850 : S <= 600 || (S < 1150 && 5 * (w - 290) >= S - 640)))
+        return V_BM128;
+    if (least == 2 || (w > 128 && w <= 256 && S >= (causal ? 600 : D <= 64 ? 850 : 1000)) ||
+        (causal && w > 256 && w <= 512 && S >= 900 + 11 * (w - 288)))
         return V_W4Q32;
     *groups = 1;
     if (S <= 128 || (D <= 64 && !causal && S <= 256))
@@ -921,6 +920,8 @@ int launch(Params p, int causal, hipStream_t stream)
     } else if (variant == V_BM128) {
         if (groups == 4)
             NAUT_LAUNCH(512, naut_fwd_kernel_bm128, NAUT_COMMA 2 NAUT_COMMA 4);
+        else if (groups == 2)
+            NAUT_LAUNCH(512, naut_fwd_kernel_bm128, NAUT_COMMA 4 NAUT_COMMA 2);
         else
             NAUT_LAUNCH(256, naut_fwd_kernel_bm128, NAUT_COMMA 4);
     } else if (variant == V_W4Q32) {

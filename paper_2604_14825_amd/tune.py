@@ -23,9 +23,9 @@ import json
 import os
 import sys
 
-VARIANTS = ("w8q32", "w4q32", "w4q32g2", "bm128g1", "bm128g4")  # w8q32 at D = 64: 4 x 64 queries
+VARIANTS = ("w8q32", "w4q32", "w4q32g2", "bm128g1", "bm128g2", "bm128g4")  # w8q32 at D = 64: 4 x 64 queries
 SHORT_NAME = {"pipe_8x32": "w8q32", "pipe_4x64": "w8q32", "pipe_4x32": "w4q32", "pipe_4x32_g2": "w4q32g2",
-              "plain_4x32": "bm128g1", "plain_2x32_g4": "bm128g4"}
+              "plain_4x32": "bm128g1", "plain_4x32_g2": "bm128g2", "plain_2x32_g4": "bm128g4"}
 
 
 def default_grid():

@@ -131,7 +131,7 @@ def test_kernel_names(monkeypatch):
         assert nb.kernel_name(*args) == want, args
     for name, at64, at128 in (("w8q32", "pipe_4x64", "pipe_8x32"), ("w4q64", "pipe_4x64", "plain_4x32"), ("w4q32", "pipe_4x32", "pipe_4x32"),
                               ("w4q32g2", "pipe_4x32_g2", "pipe_4x32_g2"), ("bm128g1", "plain_4x32", "plain_4x32"),
-                              ("bm128g2", "pipe_4x32_g2", "pipe_4x32_g2"), ("bm128g4", "plain_2x32_g4", "plain_2x32_g4"), ("no", None, None)):
+                              ("bm128g2", "plain_4x32_g2", "plain_4x32_g2"), ("bm128g4", "plain_2x32_g4", "plain_2x32_g4"), ("no", None, None)):
         monkeypatch.setenv("NAUT_ATTN_VARIANT", name)
         assert nb.kernel_name(1, 2, 128, 64, False) == at64 and nb.kernel_name(1, 2, 128, 128, False) == at128, name
 
@@ -182,3 +182,16 @@ def test_a_named_form_is_the_form_of_the_rule(H, S, D, causal, monkeypatch):
         torch.cuda.synchronize()
         res.append((o, lse))
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+def test_launches_have_the_key_groups_of_their_class(monkeypatch):
+    """Every key group has a reference maximum of its own: with fewer than key_groups() of them fewer keys' P are exactly 1,
+    and O is less accurate (up to 1.4 times the error on keys with outliers)."""
+    monkeypatch.delenv("NAUT_ATTN_VARIANT", raising=False)
+    for D in (64, 72, 80, 96, 128):
+        for causal in (True, False):
+            for H in (1, 3, 8, 12, 16, 25, 32, 48, 63, 64, 80, 96, 100, 128, 256):
+                for S in (1, 129, 257, 300, 511, 513, 640, 768, 900, 1003, 1280, 1536, 2048, 2560, 4096, 8192, 16384):
+                    name = nb.kernel_name(1, H, S, D, causal)
+                    groups = int(name.split("_g")[1]) if "_g" in name else 1
+                    assert groups >= nb.key_groups(1, H, S, D, causal), (H, S, D, causal, name)
