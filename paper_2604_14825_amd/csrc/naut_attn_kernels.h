@@ -820,7 +820,7 @@ inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
 
 // What a launch with D <= 128 runs (D: the compiled width): kernel 1 (V_BM128) with one, two or four key groups, or kernel 2
 // on 8 x 32 queries (V_W8Q32), 4 x 32 (V_W4Q32, one or two key groups) or 4 x 64 (V_W4Q64, D = 64 only).
-// Fitted to timings of every form in turn over some 4500 shapes (D = 64, 80, 96 and 128, 1 to 512 heads, S = 128 to 16384,
+// Fitted to timings of every form in turn over some 7000 shapes (D = 64, 80, 96 and 128, 1 to 768 heads, S = 128 to 16384,
 // with and without the mask).  Kernel time, us:
 //   Four key groups of kernel 1: where key_groups says four, and on a little shorter and larger grids: up to 256 work-groups
 //   of 64 queries, one per CU, all in one round (8 heads, S = 1024, D = 128, causal 16.2; kernel 2 17.6).  With the mask also
@@ -833,13 +833,21 @@ inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
 //   the second round has to be of light tiles (8 heads, S = 8192, D = 128 133 / 142 / 143).
 //   Two key groups of kernel 1: with the mask, beyond one round, short: the second round's few light tiles are over sooner
 //   (56 heads, S = 640, D = 128 17.5, kernel 2 19.2; D = 80 14.0 / 15.3; 64 heads, S = 640, D = 64 13.3 / 13.8).
-//   Kernel 1 with one: sequences of at most 128 keys (two tiles; 2 heads, S = 128, D = 64 6.4 / 6.7), and at D = 64 short ones
-//   of very many heads, of which it has four work-groups on a CU for three (256 heads, S = 512, causal 19.7 / 21.2).
+//   Kernel 1 with one: sequences of at most 128 keys (two tiles; 2 heads, S = 128, D = 64 6.4 / 6.7), and short ones of very
+//   many heads: at D = 64, of which it has four work-groups on a CU for three, between two rounds of the latter and two of the
+//   former where the last query tile is more than half full (256 heads, S = 512, causal 19.7 / 21.2, 512 heads, S = 256 17.8
+//   / 18.8); at D > 64, with the mask, the first work-groups beyond one round (144 heads, S = 512, D = 128 1.05 of its time
+//   on kernel 2, 192 heads, S = 384 1.05).
 //   256-query work-groups read K and V half as often as 128-query ones and are coarser.  No mask: by whole rounds, 256
 //   slots of 8 x 32 against 512 of 4 x 32 (24 heads, S = 3072, D = 128: 288 work-groups 150 / 130; 32 heads, S = 4096: 512
 //   243 / 249), at D = 64 512 slots of 4 x 64 against 768 of 4 x 32, where a fragment read from LDS that feeds two MFMAs
 //   is worth 8 % (32 heads, S = 4096 135 / 145).  With the mask they pay where the loop is long or the rounds come out even
 //   (32 heads, S = 16384, D = 128 1790 / 1850; 32 heads, S = 4096 129 / 136; 128 heads, S = 4096 536 / 529).
+//   Where eight does not divide the heads, XCDs share them, and K and V pass through several L2s: an XCD sees
+//   an eighth of 8 k heads, a quarter of 4 k, half of 2 k and all of an odd count.  Time of 4 x 32 over 8 x
+//   32 queries at equal rounds (D = 128 / 96 / 80, more than two rounds): odd counts 1.22 / 1.09 / 1.00, 2 k 1.17 / 1.05 /
+//   0.98, 4 k 1.07 / 1.00 / 0.97.  At D = 64 kernel 1 is the better one on odd counts with the mask (63 heads, S = 2700 84.8,
+//   4 x 32 89.6, 93 heads, S = 1700 57.9 / 62.1).
 inline int pick_form(int S, long long nbh, int D, int causal, int* groups)
 {
     int named_groups;
@@ -851,25 +859,33 @@ inline int pick_form(int S, long long nbh, int D, int causal, int* groups)
     const int least = long_loops(S, nbh, D, causal) ? 1 : key_groups(S, nbh, D, causal);
     const long long w64 = nbh * ((S + 63) / 64), w = nbh * ((S + BM - 1) / BM), w2 = nbh * ((S + BM2 - 1) / BM2);
     *groups = 4;
-    if (least == 4 || (w64 <= 256 && D <= 64 && causal && S > 128) ||
+    if (least == 4 || (w64 <= 256 && D <= 64 && causal && S > 192) ||
         (causal && w <= (D <= 64 ? 256 : 224) && S >= 1200 && S >= 1300 + 30 * (w - 160)))
         return V_BM128;
     *groups = 2;
-    if (least == 2 && causal && w > 256 && (D > 64 ? S < 850 : S <= 600 || (S < 1150 && 5 * (w - 290) >= S - 640)))
+    if (least == 2 && causal && w > 256 && (D > 64 ? S < 850 || (S <= 1024 && w > 296 && w <= 352) : S <= 600 || (S < 1150 && 5 * (w - 290) >= S - 640)))
         return V_BM128;
     if (least == 2 || (w > 128 && w <= 256 && S >= (causal ? 600 : D <= 64 ? 850 : 1000)) ||
         (causal && w > 256 && w <= 512 && S >= 900 + 11 * (w - 288)))
         return V_W4Q32;
     *groups = 1;
-    if (S <= 128 || (D <= 64 && !causal && S <= 256))
-        return V_BM128;
-    if (D <= 64 && nbh >= 192 && w > 512 && w <= (causal ? 2000 : 1024) && S >= 512 && S <= (causal ? 768 : 512))
+    if (S <= 128 || (D <= 64 && !causal && S <= 256) || (causal && w <= 256 && S <= (D <= 64 ? 192 : 144)))
         return V_BM128;
     if (causal) {
+        if (D <= 64 && w > 780 && w <= 2000 && S <= 768 && (S <= 640 || w >= 1500) && (S - 1) % BM >= BM / 2)
+            return V_BM128;
+        if (D > 64 && w > 512 && S > 224 && S <= 640 && w <= (S % BM == 0 && S <= 512 ? 768 : 600))
+            return V_BM128;
+        if (D <= 64 && nbh % 2 && w >= 900 && S >= 750 && S < 6144)
+            return V_BM128;
         if (D <= 64)
             return S >= 6144 && w2 >= 900 ? V_W4Q64 : V_W4Q32;
+        if (D > 80 && S >= 1000 && w2 >= (nbh % 2 ? (D > 96 ? 270 : 480) : nbh % 4 ? (D > 96 ? 480 : 1000) : nbh % 8 && D > 96 ? 1000 : w2 + 1))
+            return V_W8Q32;
         return (S >= 8192 && w2 >= 480) || (w2 > 448 && w2 <= 512 && S >= 1280) || (w2 > 928 && w2 <= 1024 && S >= 4096) ? V_W8Q32 : V_W4Q32;
     }
+    if (D <= 64 ? nbh >= 192 && w > 512 && w <= 1024 && S == 512 : S == 256 && w > 416 && w <= 704)
+        return V_BM128;
     if (S < 1000)
         return V_W4Q32;
     // rounds, in per cent of a full one; a last round that leaves every CU one work-group fewer is shorter
@@ -879,9 +895,11 @@ inline int pick_form(int S, long long nbh, int D, int causal, int* groups)
         const long long c64 = w2 / 512 * 368 + (r2 == 0 ? 0 : r2 <= 256 ? 202 : 368);
         return c64 < c32 && (w2 > 256 || S >= 4096) ? V_W4Q64 : V_W4Q32;
     }
+    const int dear = nbh % 2 || (nbh % 4 && w2 >= 600) ? 4 * (D - 72) : nbh % 4 ? 2 * (D - 72) : nbh % 8 && D > 96 && w2 >= 1000 ? 80 : 0;
     const long long r = w % 512;
-    const long long c4 = w / 512 * 100 + (r == 0 ? 0 : r <= 256 ? 60 : 100), c8 = (w2 + 255) / 256 * (S >= 1250 ? 97 : 102);
-    // beyond eight rounds the halves of that no longer matter -- unless every XCD sees every head, and twice the loads count
+    const long long c4 = (w / 512 * 100 + (r == 0 ? 0 : r <= 256 ? 60 : 100)) * (1000 + dear) / 1000;
+    const long long c8 = (w2 + 255) / 256 * (S >= 1250 ? 97 : 102);
+    // beyond eight rounds the halves of that no longer matter -- unless XCDs share heads, and twice the loads count
     return nbh & 7 ? (c8 <= c4 || w2 > 2048 ? V_W8Q32 : V_W4Q32) : w2 <= 2048 && c8 < c4 ? V_W8Q32 : V_W4Q32;
 }
 

@@ -195,3 +195,15 @@ def test_launches_have_the_key_groups_of_their_class(monkeypatch):
                     name = nb.kernel_name(1, H, S, D, causal)
                     groups = int(name.split("_g")[1]) if "_g" in name else 1
                     assert groups >= nb.key_groups(1, H, S, D, causal), (H, S, D, causal, name)
+
+
+def test_kernel_names_of_grids_that_eight_does_not_divide_and_of_short_ones(monkeypatch):
+    """Where 4 x 32 queries of the pipelined kernel would take longer than what ran before it, by 3 to 20 %: XCDs that share
+    heads, short sequences of many heads just beyond one round, sequences of two to three tiles."""
+    monkeypatch.delenv("NAUT_ATTN_VARIANT", raising=False)
+    for args, want in (((1, 63, 2304, 128, False), "pipe_8x32"), ((1, 73, 3000, 128, False), "pipe_8x32"), ((1, 43, 3000, 128, True), "pipe_8x32"),
+                       ((1, 150, 2100, 128, False), "pipe_8x32"), ((1, 40, 2048, 128, False), "pipe_4x32"), ((1, 63, 2304, 80, True), "pipe_4x32"),
+                       ((1, 63, 2700, 64, True), "plain_4x32"), ((1, 192, 384, 128, True), "plain_4x32"), ((1, 144, 512, 96, True), "plain_4x32"),
+                       ((1, 256, 256, 128, False), "plain_4x32"), ((1, 512, 256, 64, True), "plain_4x32"), ((1, 512, 288, 64, True), "pipe_4x32"),
+                       ((1, 16, 160, 64, True), "plain_4x32"), ((1, 16, 200, 64, True), "plain_2x32_g4"), ((1, 16, 140, 128, True), "plain_4x32")):
+        assert nb.kernel_name(*args) == want, args
