@@ -190,13 +190,18 @@ __device__ __forceinline__ void merge_wavefronts(unsigned char* smem, float (&ml
 // wavefronts of the split kernel (or half as many: see half_waves); the two LDS blocks of one are 32 KB at D = 256
 constexpr int dec_waves(int D) { return D > 128 ? DEC_WAVES / 2 : DEC_WAVES; }
 
+// Wavefronts per SIMD that a split kernel has to leave registers for: two work-groups of half the wavefronts share a CU (D =
+// 64: four, D > 128: of two wavefronts each).  Left to itself the compiler took 260 registers for FP8 at D = 128, one
+// work-group, and 136 and 144 at D = 64, three; with the bound 168, 113 and 112, none spilled.
+constexpr int dec_waves_per_simd(int D) { return D > 128 ? 1 : D > 64 ? 2 : 4; }
+
 // A wavefront has one buffer for K and one for V: the next block's K is requested when this block's K fragments are in
 // registers, its V when the V fragments are.  Twice as many wavefronts as with two buffers of each keep as many bytes in
 // flight (128 KB per CU), and cover a block's scores, softmax and P.V with each other's loads; the first block's loads
 // are out before Q's.  Against four wavefronts with two buffers (us a call, 32/8 heads, D = 128): 20 caches of 2000 keys 34.1 ->
 // 31.0, 40 of 500 24.9 -> 22.1, 8 of 16384 94.4 -> 93.8; D = 256, 16/8 heads, 256 keys 11.6 -> 10.7.
 template <int D, int DT_IN, int NW>
-__global__ __launch_bounds__(NW * 64, 1) void naut_decode_split_kernel(const DecodeParams p)
+__global__ __launch_bounds__(NW * 64, (dec_waves_per_simd(D))) void naut_decode_split_kernel(const DecodeParams p)
 {
     using T = In<DT_IN>;
     constexpr int REGION = 2 * DEC_BLK * D * 2;  // LDS of a wavefront
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(NW * 64, 1) void naut_decode_split_kernel(const Dec
 
 // The same split kernel on FP8 (E4M3) Q, K and V: 64-key blocks (one 32x32x64 MFMA covers 64 keys of
 // P.V), the LDS layouts, transposed byte reads and the 2^7 scaling of P of the FP8 prefill kernel, the
-// blocks dealt to the wavefronts and double-buffered in LDS exactly as above; strides and narrower heads
+// blocks dealt to the wavefronts and one buffer of K and V each, exactly as above; strides and narrower heads
 // as above too, in 16-byte chunks of 16 values (p.cpr counts 8 values: two per chunk here).
 // bps counts 64-key blocks here.  The partial's reference maximum is stored as m - 7, which makes its l
 // and O (both carry the factor 2^7) relative to it in the plain sense the merge kernel expects.
@@ -397,7 +402,7 @@ constexpr float DEC8_TAU = 1.0f;      // P * 2^7 <= 2^(1+7) = 256 < 448, the lar
 constexpr float DEC8_P_SHIFT = 7.0f;
 
 template <int D, int NW>
-__global__ __launch_bounds__(NW * 64, 1) void naut_decode_split_fp8_kernel(const DecodeParams p)
+__global__ __launch_bounds__(NW * 64, (dec_waves_per_simd(D))) void naut_decode_split_fp8_kernel(const DecodeParams p)
 {
     constexpr int BLKB = DEC8_BLK * D;     // bytes of one 64-key block of K or V
     constexpr int REGION = 2 * BLKB;
@@ -864,16 +869,15 @@ constexpr int block_bytes16(int D) { return 2 * DEC_BLK * D * 2; }  // K and V o
 //   partials is shorter than that of eight by what the second block costs, and short caches fill the chip with twice the
 //   work-groups; us a call before / all / half: 30 caches of 16 heads, 128 keys 15.0 / 13.2 / 10.1, 5 caches of 1326
 //   keys, 2 heads, 32 rows 10.5 / 10.7 / 10.5; D = 256, 512 keys, 8 heads 11.8 / 10.9 / 12.5);
-// - in 16 bits at D > 64 where there are more work-groups than CUs: the second one's loads fill the gaps of the first and the last
-//   round is shorter (320 of 512 keys 25.0 / 22.1 / 19.6, D = 256 49.1 / 42.6 / 37.5; 288 of 3000 87.5 / 83.9 / 81.1).
-//   FP8 gains nothing (320 of 1000 keys 24.8 / 21.9 / 23.5), and at D = 64 two of all fit anyway (264 of 9000 keys
-//   117.6 / 114.6 / 117.5).
-template <int D, bool FP8>
+// - where there are more work-groups than CUs: the second one's loads fill the gaps of the first and the last round is
+//   shorter (320 of 512 keys 25.0 / 22.1 / 19.6, D = 256 49.1 / 42.6 / 37.5; 288 of 3000 87.5 / 83.9 / 81.1).  Half / all
+//   over grids of more than 256, kernel time: FP8, D = 128, 640 to 1000 keys 0.84 to 0.89, 1300 to 3000 0.91 to 0.97; FP8,
+//   D = 64 0.92 to 0.98; 16 bits, D = 64 0.95 to 1.00 (16384 keys 1.008).
+template <int D>
 bool half_waves(const DecodeParams& p)
 {
     constexpr int W = dec_waves(D);
-    return p.bps <= (D > 128 ? W / 2 : W) ||
-           (!FP8 && D > 64 && (long long)p.nsplit * p.nchunks * p.B * p.Hkv > DEC_TARGET_WGS);
+    return p.bps <= (D > 128 ? W / 2 : W) || (long long)p.nsplit * p.nchunks * p.B * p.Hkv > DEC_TARGET_WGS;
 }
 
 template <int D, int DT_IN, int DT_OUT>
@@ -881,7 +885,7 @@ int launch_decode(const DecodeParams& p, hipStream_t stream)
 {
     const dim3 g1((unsigned)p.nsplit, (unsigned)p.nchunks, (unsigned)(p.B * p.Hkv));
     constexpr int W = dec_waves(D);
-    if (half_waves<D, false>(p))
+    if (half_waves<D>(p))
         hipLaunchKernelGGL((naut_decode_split_kernel<D, DT_IN, W / 2>), g1, dim3(W / 2 * 64), 0, stream, p);
     else
         hipLaunchKernelGGL((naut_decode_split_kernel<D, DT_IN, W>), g1, dim3(W * 64), 0, stream, p);
@@ -1145,7 +1149,7 @@ int naut_attn_decode_fp8_strided(const void* q, const void* k, const void* v, vo
     hipStream_t hs = (hipStream_t)stream;
     const dim3 g1((unsigned)p.nsplit, (unsigned)p.nchunks, (unsigned)(p.B * p.Hkv));
     constexpr int W = DEC_WAVES;
-    const bool half = half_waves<128, true>(p);  // D = 64 has the same rule
+    const bool half = half_waves<128>(p);  // D = 64 has the same rule
     if (DK == 128 && half)
         hipLaunchKernelGGL((naut_decode_split_fp8_kernel<128, W / 2>), g1, dim3(W / 2 * 64), 0, hs, p);
     else if (DK == 128)
