@@ -780,18 +780,20 @@ void* static_scratch(int* err)
 // The first count stands, and nothing is priced, where it fills whole rounds (base divides 256) and where a fuller split would
 // leave a wavefront without a block.
 //
-// A cache of at most DEC_ONE_BYTES per K/V head is one split, however few work-groups that makes: a second 128 KB takes one
-// CU about 2.5 us, the merge kernel 7 us where the host paces the calls and 3 us on a stream that runs behind it.  Two splits
-// as it was / one (us a call, D = 128, 32/8 heads, one position): 512 keys 10.7 / 8.4 (from a graph 9.2 / 8.1), 12 caches of
-// 512 keys 11.9 / 10.1; D = 64, 16/4 heads, 1000 keys, four splits, 10.9 / 8.2 (7.1 / 7.1).  At 768 keys one split is no
-// faster where a graph holds the calls (9.4 / 9.2) and slower with more of them (8 caches 11.6 / 12.4).
+// A cache of at most two blocks for each of all wavefronts is one split, however few work-groups that makes: a second 128 KB
+// takes one CU about 2.5 us, the merge kernel 7 us where the host paces the calls and 3 us on a stream that runs behind it.
+// Two splits as it was / one (us a call, D = 128, 32/8 heads, one position): 512 keys 10.7 / 8.4 (from a graph 9.2 / 8.1), 12
+// caches of 512 keys 11.9 / 10.1.  At 768 keys one split is no faster where a graph holds the calls (9.4 / 9.2) and slower
+// with more of them (8 caches 11.6 / 12.4).  At D = 64 four blocks a wavefront would be as many bytes, but they are fewer
+// partials than four splits of four wavefronts have, and every partial has a reference maximum of its own, whose key's P is
+// exactly 1: error against 64 bits 1.06 of that of four splits at 1000 keys, 1.1 to 1.3 at four times the usual scale
+// (kernel time 0.94 to 0.98 of it; FP8 at 2000 keys 1.08).
 //
 // The workspace must hold the least count's partials (the first count that reaches 256 work-groups); with less room than
 // the picked count needs, the best candidate that fits is taken.  No count takes more than DEC_MAX_PARTS partials unless
 // the least does, so the 16 MiB static scratch holds the picked count wherever it holds the least (D <= 128).  Both sizes
 // are those of the counts above also where one split is taken and nothing is written there.
 constexpr unsigned DEC_MAX_PARTS = 960;
-constexpr size_t DEC_ONE_BYTES = 256u << 10;  // K and V of 512 keys at D = 128 in 16 bits
 
 bool make_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int block_bytes, size_t room, Plan* pl)
 {
@@ -824,7 +826,7 @@ bool make_plan(int B, int Hq, int Hkv, int Sq, int Sk, int D, int block_bytes, s
     pl->ws_least = pl->ws_bytes = (size_t)parts * part_bytes;
     if (room < pl->ws_least)
         return true;  // the caller refuses it
-    const bool one = (size_t)nblk * block_bytes <= DEC_ONE_BYTES;
+    const bool one = nblk <= 2 * W;
     if (one) {
         pl->nsplit = 1;
         pl->bps = (int)((nblk + G - 1) / G * G);

@@ -90,3 +90,22 @@ def test_block_and_split_edges_fp8(D, Hkv, g, Sq, B):
             assert (lse.double() - rl).abs().max().item() <= 2e-4, (D, Hkv, g, Sq, B, Sk)
             again = run(*(x.view(torch.uint8) for x in (q, k, v)), scale, (1.0, 1.0, 1.0))
             assert torch.equal(o, again[0]) and torch.equal(lse, again[1]), (D, Hkv, g, Sq, B, Sk)
+
+
+@pytest.mark.parametrize("D,fp8", [(64, False), (64, True), (128, False), (128, True), (256, False)])
+def test_one_split_is_two_blocks_a_wavefront(D, fp8):
+    """Up to two blocks for each wavefront one split stores O itself and leaves the workspace alone; from there on there are
+    several, at every width: fewer partials than that are fewer keys whose P is exactly 1."""
+    limit = 2 * (4 if D > 128 else 8) * (64 if fp8 else 32)
+    L = binding.lib()
+    for Sk in (limit - 1, limit, limit + 1, 2 * limit):
+        x = [torch.randn(1, h, s, D, device="cuda") for h, s in ((4, 1), (2, Sk), (2, Sk))]
+        q, k, v = (t.to(torch.float8_e4m3fn).view(torch.uint8) if fp8 else t.bfloat16() for t in x)
+        o, lse = torch.empty(1, 4, 1, D, device="cuda", dtype=torch.bfloat16), torch.empty(1, 4, 1, device="cuda")
+        ws = torch.full((L.naut_attn_decode_workspace_bytes(1, 4, 2, 1, Sk, D),), 0xA5, device="cuda", dtype=torch.uint8)
+        if fp8:
+            binding.naut_attn_decode_fp8(q, k, v, o, lse, True, 0.1, 1.0, 1.0, 1.0, ws)
+        else:
+            binding.naut_attn_decode_strided(q, k, v, o, lse, True, 0.1, ws)
+        torch.cuda.synchronize()
+        assert bool((ws == 0xA5).all()) == (Sk <= limit), (D, fp8, Sk)
