@@ -875,11 +875,19 @@ constexpr int block_bytes16(int D) { return 2 * DEC_BLK * D * 2; }  // K and V o
 //   shorter (320 of 512 keys 25.0 / 22.1 / 19.6, D = 256 49.1 / 42.6 / 37.5; 288 of 3000 87.5 / 83.9 / 81.1).  Half / all
 //   over grids of more than 256, kernel time: FP8, D = 128, 640 to 1000 keys 0.84 to 0.89, 1300 to 3000 0.91 to 0.97; FP8,
 //   D = 64 0.92 to 0.98; 16 bits, D = 64 0.95 to 1.00 (16384 keys 1.008).
+// D > 128, where half is two wavefronts:
+// - a last round of at most one work-group a CU runs with half the bytes in flight, so it has to be another one (40 caches of
+//   8 heads, 4096 keys, 640 work-groups: four wavefronts each before there was half 250, half 269; 33 caches, 792: 226 / 204);
+// - the few threads take their time to merge and store many rows (64 keys, 16 rows 8.1 / 8.7, 32 rows 9.3 / 9.9).
 template <int D>
 bool half_waves(const DecodeParams& p)
 {
     constexpr int W = dec_waves(D);
-    return p.bps <= (D > 128 ? W / 2 : W) || (long long)p.nsplit * p.nchunks * p.B * p.Hkv > DEC_TARGET_WGS;
+    const long long wgs = (long long)p.nsplit * p.nchunks * p.B * p.Hkv;
+    if (D <= 128)
+        return p.bps <= W || wgs > DEC_TARGET_WGS;
+    const long long rest = wgs % (2 * DEC_TARGET_WGS);
+    return (p.bps <= W / 2 && p.R < 8) || (wgs > DEC_TARGET_WGS && (rest == 0 || rest > DEC_TARGET_WGS));
 }
 
 template <int D, int DT_IN, int DT_OUT>
