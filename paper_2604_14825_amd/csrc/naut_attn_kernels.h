@@ -943,7 +943,8 @@ int launch(Params p, int causal, hipStream_t stream)
         else
             NAUT_LAUNCH(256, naut_fwd_kernel_bm128, NAUT_COMMA 4);
     } else if (variant == V_W4Q32) {
-        // two key groups step over twice the rows at a time, which has to stay inside 32-bit offsets
+        // two key groups step over twice the rows at a time: with rows of at most 8 MiB that is at most 2^29 bytes, as the
+        // 32-bit offsets between two moves of the base need it (see rebase in the kernel)
         if (groups == 2 && (p.k_rs > p.v_rs ? p.k_rs : p.v_rs) <= 8 << 20)
             NAUT_LAUNCH(512, naut_fwd_kernel_pipe, NAUT_COMMA 1 NAUT_COMMA 4 NAUT_COMMA 2);
         else

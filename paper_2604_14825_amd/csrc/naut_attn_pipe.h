@@ -217,7 +217,8 @@ __global__ __launch_bounds__(NWV * NG * 64, (pipe_waves_per_simd<D, QH, NWV, NG>
         return t;
     };
     auto advance = [&](Tiles& t, unsigned step) { t.off = t.off + step < t.end ? t.off + step : t.end; };  // the last tile again past the end
-    // Offsets stay below 2^32 (a step is at most 2^29 bytes, with two key groups 2^30): called every few steps, it moves the base past 2^30.
+    // Offsets stay below 2^32: a step is at most 2^29 bytes (32 rows of 16 MiB; 64 of 8 MiB, beyond which launch() does not
+    // run two key groups), and this, called every four steps and first after five, moves the base past 2^30.
     auto rebase = [&](Tiles& t) {
         if (t.off >> 30) {
             const uint64_t a = ((uint64_t)(unsigned)t.rsrc.y << 32 | (unsigned)t.rsrc.x) + t.off;

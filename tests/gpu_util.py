@@ -13,6 +13,24 @@ TORCH_DT = {synth.BF16: torch.bfloat16, synth.F16: torch.float16, synth.F32: tor
 TOL_MAX, TOL_MEAN, TOL_LSE = 2e-2, 2e-3, 1e-3
 
 
+# The kernel that a NAUT_ATTN_VARIANT name runs at head dimensions up to 64, to 128 and beyond (None: the name chooses nothing
+# there, and a test that passes it would run what another name does).
+FORMS = {"w8q32": ("pipe_4x64", "pipe_8x32", "plain_8x32"), "w4q64": ("pipe_4x64", None, None), "w4q32": ("pipe_4x32", "pipe_4x32", None),
+         "w4q32g2": ("pipe_4x32_g2", "pipe_4x32_g2", None), "bm128g1": ("plain_4x32", "plain_4x32", "plain_4x32"),
+         "bm128g2": ("plain_4x32_g2", "plain_4x32_g2", None), "bm128g4": ("plain_2x32_g4", "plain_2x32_g4", None)}
+
+
+def use_form(monkeypatch, variant, B, Hq, S, D, causal):
+    """Name the variant for the calls to come and see that it is what they run ("bm128": kernel 1 with its own key groups)."""
+    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
+    got = nb.kernel_name(B, Hq, S, D, causal)
+    if variant == "bm128":
+        assert got.startswith("plain_"), got
+    else:
+        want = FORMS[variant][0 if D <= 64 else 1 if D <= 128 else 2]
+        assert want is not None and got == want, (variant, D, got)
+
+
 def to_device(bits: np.ndarray, dtype: int) -> torch.Tensor:
     return torch.from_numpy(bits.view(np.int16)).cuda().view(TORCH_DT[dtype])
 

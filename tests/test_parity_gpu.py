@@ -66,13 +66,15 @@ def _key_profile(kind, S):
     raise ValueError(kind)
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])   # bm128: four key groups here
+# bm128: four key groups here; w8q32 at D = 64: 64 queries per wavefront in two halves, whose reference moves together
+@pytest.mark.parametrize("variant,D", [("w8q32", 128), ("w4q32", 128), ("w4q32g2", 128), ("w8q32", 64), ("w4q32", 64), ("w4q32g2", 64),
+                                       ("bm128", 128), ("bm128g1", 128), ("bm128g2", 128)])
 @pytest.mark.parametrize("kind", ["ascending", "descending", "late_spike"])
-def test_moving_reference_maximum(kind, variant, monkeypatch):
+def test_moving_reference_maximum(kind, variant, D, monkeypatch):
     """Score profiles that exercise the repair path of the online softmax: a maximum that keeps growing,
     one that is met in the first block, and a single late key far above the rest (near one-hot rows)."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
-    B, Hq, Hkv, S, D, causal, idt, odt = 1, 4, 2, 700, 128, True, synth.BF16, synth.F32
+    B, Hq, Hkv, S, causal, idt, odt = 1, 4, 2, 700, True, synth.BF16, synth.F32
+    gu.use_form(monkeypatch, variant, B, Hq, S, D, causal)
     seed = 4242
     q = synth.fill(B, Hq, S, D, seed, synth.TAG_Q, idt)
     k = synth.fill(B, Hkv, S, D, seed, synth.TAG_K, idt)
@@ -80,7 +82,7 @@ def test_moving_reference_maximum(kind, variant, monkeypatch):
     kf = _bits_to_f32(k, idt) * _key_profile(kind, S)[None, None, :, None]
     k = synth.round16(kf, idt)
     scale = 1.0 / math.sqrt(D)
-    print("case", kind, variant, flush=True)
+    print("case", kind, variant, D, flush=True)
     o, lse = gu.run_hip(q, k, v, idt, odt, causal, scale)
     o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, scale)
     gu.check(o, lse, o_ref, lse_ref, kind + "/" + variant)
@@ -90,16 +92,17 @@ def test_moving_reference_maximum(kind, variant, monkeypatch):
         gu.check(o, lse, o_ref, lse_ref, kind + "/" + variant + "/hot")
 
 
-@pytest.mark.parametrize("variant,D", [("w8q32", 128), ("w4q64", 128), ("bm128", 128), ("bm128", 64), ("bm128", 256),
-                                       ("bm128g1", 128), ("bm128g2", 128), ("bm128g1", 64), ("bm128g2", 64), ("w8q32", 256)])
+@pytest.mark.parametrize("variant,D", [("w8q32", 128), ("w4q64", 64), ("bm128", 128), ("bm128", 64), ("bm128", 256),
+                                       ("bm128g1", 128), ("bm128g2", 128), ("bm128g1", 64), ("bm128g2", 64), ("w8q32", 256),
+                                       ("w4q32", 128), ("w4q32g2", 128), ("w4q32", 64), ("w4q32g2", 64)])
 def test_dominant_key_behind_a_lagging_reference(variant, D, monkeypatch):
     """The last key of every fourth row (its diagonal, under the causal mask) dominates the row by a few binades --
     too few to make a kernel move its reference maximum -- and carries values of magnitude 4 to 5.5, where one
     bf16 step of O is 3e-2.  The largest P of such a row is an arbitrary number, not 1; unless O is divided by the sum of the
     P that went into it, the rounding of that P (up to 2^-8) is an error of 2^-8 |v| on top of the rounding of O, and
     the 2e-2 bar is missed."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)   # bm128, D <= 128: four key groups at this size
     B, H, S, idt, odt = 1, 4, 1500, synth.BF16, synth.BF16
+    gu.use_form(monkeypatch, variant, B, H, S, D, True)   # bm128, D <= 128: four key groups at this size
     seed = 4545 + D
     q = synth.fill(B, H, S, D, seed, synth.TAG_Q, idt)
     k = synth.fill(B, H, S, D, seed, synth.TAG_K, idt)
@@ -153,17 +156,17 @@ def test_moving_reference_maximum_wide(kind, variant, monkeypatch):
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("variant", ["w8q32", "bm128", "bm128g1", "bm128g2", "bm128g4"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q32", "w4q32g2", "bm128", "bm128g1", "bm128g2", "bm128g4"])
 def test_every_tile_count(variant, causal, monkeypatch):
     """Sequence lengths just below, at and just above every multiple of 64 up to 704: every residue of the key-tile
-    count modulo the unrolled loops' period (4 LDS buffers in the 256-query kernel; in the 128-query one 2 times its key
-    groups, whose tiles are 32 keys where there are four), with and without a ragged last tile, and every position of
+    count modulo the unrolled loops' period (4 LDS buffers times the key groups in the pipelined kernel; in the plain one 2
+    times them, with tiles of 32 keys where there are four), with and without a ragged last tile, and every position of
     the causal diagonal inside a 256-query work-group."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     B, Hq, Hkv, D, idt, odt = 1, 2, 1, 128, synth.BF16, synth.F32
     scale = 1.0 / math.sqrt(D)
     for t in range(1, 12):
         for S in (64 * t - 1, 64 * t, 64 * t + 1):
+            gu.use_form(monkeypatch, variant, B, Hq, S, D, causal)
             q = synth.fill(B, Hq, S, D, 6000 + S, synth.TAG_Q, idt)
             k = synth.fill(B, Hkv, S, D, 6000 + S, synth.TAG_K, idt, S // 50, 8.0)
             v = synth.fill(B, Hkv, S, D, 6000 + S, synth.TAG_V, idt)
@@ -209,11 +212,13 @@ VARIANT_SHAPES = [
 ]
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2", "bm128g4"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "w4q32", "w4q32g2", "bm128", "bm128g1", "bm128g2", "bm128g4"])
 def test_every_kernel_variant(variant, monkeypatch):
     """Each tile shape / wavefront layout the library can choose gives the same attention."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     for B, Hq, Hkv, S, D, causal, idt, odt in VARIANT_SHAPES:
+        if variant == "w4q64" and D > 64:
+            continue
+        gu.use_form(monkeypatch, variant, B, Hq, S, D, causal)
         seed = 2000 + S + D
         q = synth.fill(B, Hq, S, D, seed, synth.TAG_Q, idt)
         k = synth.fill(B, Hkv, S, D, seed, synth.TAG_K, idt, S // 40, 8.0)
@@ -225,10 +230,10 @@ def test_every_kernel_variant(variant, monkeypatch):
         gu.check(o, lse, o_ref, lse_ref, variant)
 
 
-@pytest.mark.parametrize("variant", ["w4q64", "bm128"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q32g2", "bm128"])  # (by shape it is w4q32)
 def test_variants_on_prefill_sampled_rows(variant, monkeypatch):
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     w = synth.WORKLOADS["prefill"]
+    gu.use_form(monkeypatch, variant, w.B, w.Hq, w.S, w.D, w.causal)
     q, k, v = synth.make_inputs(w)
     o, lse = gu.run_hip(q, k, v, w.in_dtype, w.out_dtype, w.causal, w.scale)
     rows = gu.sample_rows(w, 1024, seed=23, bm=256)

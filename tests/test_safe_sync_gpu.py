@@ -61,16 +61,16 @@ SMALL = [
 ]
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2", "bm128g4"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q32", "w4q32g2", "bm128", "bm128g1", "bm128g2", "bm128g4"])
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,causal,idt,odt", SMALL)
 def test_small_shapes_bit_identical(B, Hq, Hkv, S, D, causal, idt, odt, variant, monkeypatch):
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
+    gu.use_form(monkeypatch, variant, B, Hq, S, D, causal)
     q, k, v = make(B, Hq, Hkv, S, D, idt, 21000 + S + D)
     print("safe-sync small", variant, B, Hq, Hkv, S, D, causal, flush=True)
     both_prefill(q, k, v, idt, odt, causal, 1.0 / math.sqrt(D), "small/%s" % variant)
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "bm128", "bm128g1", "bm128g2", "bm128g4"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q32", "w4q32g2", "bm128", "bm128g1", "bm128g2", "bm128g4"])
 @pytest.mark.parametrize("causal", [True, False])
 def test_every_tile_count_bit_identical(variant, causal, monkeypatch):
     """S = 64 t - 1, 64 t and 64 t + 1 for t = 1 .. 9: every phase of the four-buffer rotation, with and without a ragged tail."""
@@ -82,12 +82,13 @@ def test_every_tile_count_bit_identical(variant, causal, monkeypatch):
             both_prefill(q, k, v, synth.BF16, synth.BF16, causal, 1.0 / math.sqrt(128), "tiles S=%d/%s" % (S, variant))
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
+@pytest.mark.parametrize("variant,D", [("w8q32", 128), ("w4q32", 128), ("w4q32g2", 128), ("w8q32", 64), ("w4q32", 64), ("w4q32g2", 64),
+                                       ("bm128", 128), ("bm128g1", 128), ("bm128g2", 128)])
 @pytest.mark.parametrize("kind", ["ascending", "descending", "late_spike"])
-def test_moving_reference_bit_identical(kind, variant, monkeypatch):
+def test_moving_reference_bit_identical(kind, variant, D, monkeypatch):
     """The score profiles that drive the rare blocks (reference moves, heavy blocks) of the online softmax."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
-    B, Hq, Hkv, S, D, idt = 1, 4, 2, 700, 128, synth.BF16
+    B, Hq, Hkv, S, idt = 1, 4, 2, 700, synth.BF16
+    gu.use_form(monkeypatch, variant, B, Hq, S, D, True)
     q = synth.fill(B, Hq, S, D, 4242, synth.TAG_Q, idt)
     k = synth.fill(B, Hkv, S, D, 4242, synth.TAG_K, idt)
     v = synth.fill(B, Hkv, S, D, 4242, synth.TAG_V, idt)
@@ -96,7 +97,7 @@ def test_moving_reference_bit_identical(kind, variant, monkeypatch):
             "late_spike": np.where(j == (3 * S) // 4, 60.0, 1.0).astype(np.float32)}[kind]
     kf = (k.astype(np.uint32) << 16).view(np.float32) * prof[None, None, :, None]
     k = synth.round16(kf, idt)
-    print("safe-sync profile", kind, variant, flush=True)
+    print("safe-sync profile", kind, variant, D, flush=True)
     for causal, sc in ((True, 1.0), (False, 4.0)):
         both_prefill(q, k, v, idt, synth.F32, causal, sc / math.sqrt(D), "%s/%s" % (kind, variant))
 
@@ -200,7 +201,7 @@ def test_long_sequence_bit_identical():
 @pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,D", [(1, 4, 4, 1, 100, 128), (2, 8, 2, 1, 777, 128), (1, 8, 1, 3, 500, 64),
                                             (1, 16, 2, 5, 300, 128), (2, 32, 8, 1, 16384, 128)])
 def test_decode_bit_identical(B, Hq, Hkv, Sq, Sk, D):
-    """The decode split kernel counts its own loads over a private double buffer per wavefront."""
+    """The decode split kernel counts its own loads over a private buffer each of K and V per wavefront."""
     q = synth.fill(B, Hq, Sq, D, 25000 + Sk, synth.TAG_Q, synth.BF16)
     k = synth.fill(B, Hkv, Sk, D, 25000 + Sk, synth.TAG_K, synth.BF16, Sk // 50, 8.0)
     v = synth.fill(B, Hkv, Sk, D, 25000 + Sk, synth.TAG_V, synth.BF16)

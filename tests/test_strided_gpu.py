@@ -29,12 +29,12 @@ def run_strided(qd, kd, vd, od, causal, scale, want_lse=True):
     return od.double().cpu().numpy(), (lse.double().cpu().numpy() if want_lse else None)
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q32", "w4q32g2", "bm128", "bm128g1", "bm128g2"])
 @pytest.mark.parametrize("D", [8, 32, 40, 64, 80, 96, 112, 128])
 def test_head_dimensions(D, variant, monkeypatch):
     """Every multiple of 8 runs on the next of the 64-, 80-, 96- and 128-wide kernels; contiguous layout."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     B, Hq, Hkv, S, causal, idt, odt = 1, 4, 2, 333, True, synth.BF16, synth.F32
+    gu.use_form(monkeypatch, variant, B, Hq, S, D, causal)
     q, k, v = make(B, Hq, Hkv, S, D, idt, 9000 + D)
     scale = 1.0 / math.sqrt(D)
     print("head dim", D, variant, flush=True)
@@ -45,13 +45,13 @@ def test_head_dimensions(D, variant, monkeypatch):
     gu.check(o, lse, o_ref, lse_ref, "D=%d %s" % (D, variant))
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q32", "w4q32g2", "bm128", "bm128g1", "bm128g2"])
 @pytest.mark.parametrize("D,causal,idt,odt", [(128, True, synth.BF16, synth.BF16), (64, False, synth.F16, synth.F16),
                                              (96, True, synth.BF16, synth.BF16)])
 def test_bshd_layout(D, causal, idt, odt, variant, monkeypatch):
     """Tensors stored [B][S][H][D] (sequence-major), passed as transposed views; O written in the same layout."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     B, Hq, Hkv, S = 2, 6, 2, 300
+    gu.use_form(monkeypatch, variant, B, Hq, S, D, causal)
     q, k, v = make(B, Hq, Hkv, S, D, idt, 9100 + D)
     scale = 1.0 / math.sqrt(D)
     bshd = lambda a: gu.to_device(np.ascontiguousarray(a.transpose(0, 2, 1, 3)), idt)   # memory [B][S][H][D]
@@ -85,14 +85,14 @@ def test_padded_rows_and_untouched_gaps():
     assert torch.all(o_buf[..., D:] == 7.0).item(), "the gaps between O rows were written"
 
 
-@pytest.mark.parametrize("variant", ["w8q32", "w4q64", "bm128", "bm128g1", "bm128g2"])
+@pytest.mark.parametrize("variant", ["w8q32", "w4q32", "w4q32g2", "bm128", "bm128g1", "bm128g2"])
 @pytest.mark.parametrize("D,odt", [(128, synth.BF16), (64, synth.F16), (80, synth.BF16)])
 def test_o_rows_aligned_to_8_bytes_only(D, odt, variant, monkeypatch):
     """16-bit O with a row pitch of D + 4 elements: rows start on 8-byte, not 16-byte, boundaries (the least the
     entry point accepts), the S = 333 rows end in a ragged tile, and the 4-element gaps must stay untouched.
     The pipelined kernels write O in 16-byte pieces of whole rows, so this is their unaligned-store case."""
-    monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
     B, Hq, Hkv, S = 2, 4, 2, 333
+    gu.use_form(monkeypatch, variant, B, Hq, S, D, True)
     idt = odt
     q, k, v = make(B, Hq, Hkv, S, D, idt, 9300 + D)
     scale = 1.0 / math.sqrt(D)
@@ -215,17 +215,21 @@ def test_wide_head_groups_of_heads(B, Hq, Hkv, S, monkeypatch):
         gu.check(o.reshape(-1, D)[rows], lse.reshape(-1)[rows], o_ref, lse_ref, "D=256, %d heads" % (B * Hq))
 
 
-@pytest.mark.parametrize("D,variant", [(256, None), (128, "bm128"), (128, "w8q32"), (128, "w4q64"), (64, "bm128"),
-                                       (256, "w8q32"), (128, "bm128g1"), (64, "bm128g1"), (128, "bm128g2")])
-def test_wide_head_row_stride_beyond_32_bits(D, variant, monkeypatch):
-    """K and V rows 16 MiB apart (the largest row stride the entry point admits), on every kernel: S times the
-    stride passes 2^32 bytes, so the tile addresses must be formed in 64 bits, and the last row of a tile (the 64th; the
-    32nd at D = 256 and with the four key groups that bm128 runs at D = 128 here) must fit the 32-bit offsets inside
+@pytest.mark.parametrize("D,variant,mib", [(256, None, 16), (128, "bm128", 16), (128, "w8q32", 16), (64, "w8q32", 16), (64, "bm128", 16),
+                                           (256, "w8q32", 16), (128, "bm128g1", 16), (64, "bm128g1", 16), (128, "bm128g2", 16),
+                                           (128, "w4q32", 16), (64, "w4q32", 16), (128, "w4q32g2", 8), (64, "w4q32g2", 8),
+                                           (128, "w4q32g2", 16)])   # more than 8 MiB: one key group, see launch()
+@pytest.mark.parametrize("causal", [True, False])
+def test_wide_head_row_stride_beyond_32_bits(D, variant, mib, causal, monkeypatch):
+    """K and V rows 16 MiB apart (the largest row stride the entry point admits) or as far as two key groups of the pipelined
+    kernel go, on every kernel: S times the stride passes 2^32 bytes, so the tile addresses must be formed in 64 bits (the
+    pipelined kernel moves its base past 2^30 several times), and the last row of a tile (the 64th; the 32nd at D = 256, in
+    the pipelined kernel and with the four key groups that bm128 runs at D = 128 here) must fit the 32-bit offsets inside
     a tile."""
+    B, H, S, idt = 1, 1, 4800 // mib, synth.BF16
     if variant is not None:
-        monkeypatch.setenv("NAUT_ATTN_VARIANT", variant)
-    B, H, S, idt = 1, 1, 300, synth.BF16
-    stride = 1 << 23  # elements
+        gu.use_form(monkeypatch, variant, B, H, S, D, causal)
+    stride = mib << 19  # elements
     q, k, v = make(B, H, H, S, D, idt, 9700)
     scale = 1.0 / math.sqrt(D)
     qd = gu.to_device(q, idt)
@@ -238,10 +242,10 @@ def test_wide_head_row_stride_beyond_32_bits(D, variant, monkeypatch):
     kd, vd = spread(k), spread(v)
     assert kd.stride(2) == stride and kd.stride(2) * 2 * S > 1 << 32
     od = torch.full((B, H, S, D), float("nan"), dtype=torch.float32, device="cuda")
-    print("16 MiB row stride", D, variant, flush=True)
-    o, lse = run_strided(qd, kd, vd, od, True, scale)
-    o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, True, scale)
-    gu.check(o, lse, o_ref, lse_ref, "D=%d %s, row stride 2^23" % (D, variant))
+    print("row stride of %d MiB" % mib, D, variant, causal, flush=True)
+    o, lse = run_strided(qd, kd, vd, od, causal, scale)
+    o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, scale)
+    gu.check(o, lse, o_ref, lse_ref, "D=%d %s, row stride of %d MiB" % (D, variant, mib))
 
 
 @pytest.mark.parametrize("D,variant", [(72, "w8q32"), (80, "w8q32"), (88, "w8q32"), (96, "w8q32"), (104, "w8q32"),
