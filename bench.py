@@ -175,6 +175,12 @@ def cpu_baseline(total_rows: int, run_rows, flops_of_rows, target_seconds: float
     return rec, (rows, o, lse)
 
 
+def kernel_of(nb, w):
+    """The kernel that a prefill launch of this workload runs, and its key groups."""
+    name = nb.kernel_name(w.B, w.Hq, w.S, w.D, w.causal)
+    return {"kernel": name, "key_groups": int(name.partition("_g")[2] or 1)}
+
+
 def prefill_parity(args, w, synth, np, oracle_rows, flops_of_rows, o_dev, lse_dev, tol, out, tflops):
     """cpu_baseline (unless switched off) and the check of the timed buffers; fills `out`; returns pass/fail."""
     import oracle
@@ -440,7 +446,6 @@ def main() -> int:
     flops = w.flops
     tflops = flops / (t["ms_wall"] * 1e-3) / 1e12
     achieved = flops / (t["ms_median"] * 1e-3) / 1e12  # the median launch, measured on the launch stream
-    variant = nb.variant_name(w.B, w.Hq, w.S, w.D, w.causal, w.in_dtype, w.out_dtype)
     roof = {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS, "traffic": measured_traffic(w.name),
             "algorithmic_hbm_bytes": w.io_bytes}
@@ -451,8 +456,7 @@ def main() -> int:
         "ms_per_step": t["ms_wall"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "bf16" if w.in_dtype == synth.BF16 else "f16", "data": "synthetic",
         "config": {"workload": w.name, "B": w.B, "Hq": w.Hq, "Hkv": w.Hkv, "S": w.S, "D": w.D,
-                   "causal": w.causal, "outlier_k_rows": w.n_outlier, "kernel": variant,
-                   "key_groups": nb.key_groups(w.B, w.Hq, w.S, w.D, w.causal),
+                   "causal": w.causal, "outlier_k_rows": w.n_outlier, **kernel_of(nb, w),
                    "flop_convention": "4*B*Hq*S^2*D, halved for causal",
                    "pct_of_bf16_mfma_peak": 100.0 * tflops / PEAK_BF16_TFLOPS},
         "roofline": roof, "context": PAPER_CONTEXT,

@@ -138,7 +138,8 @@ int naut_version(void);
 
 /*
  * Name of the class of kernel that these sizes fall into (a static string such as "fwd_bm256_w8q32_bn64": 256 queries on a
- * compute unit at a time, in wavefronts of 32 queries, over a long key loop), NULL if unsupported.  The paper's
+ * compute unit at a time, in wavefronts of 32 queries, over a long key loop), NULL if unsupported; the kernel that a launch
+ * runs, its tile and its key groups are naut_attn_fwd_kernel_name's to tell.  The paper's
  * auto-tuner makes this kind of choice per shape (Section 7.2: 64x128 tiles with 4
  * warps on short sequences against 128x128 with 8); here it is a fixed rule on the number of
  * work-groups and the length of the key loop, overridable with the environment variable
@@ -159,7 +160,7 @@ const char* naut_attn_fwd_kernel_name(int B, int Hq, int S, int D, int causal);
 /*
  * Key groups per work-group of the class of these sizes (naut_attn_fwd_fp8_key_groups: of the launch), 0 if they are
  * unsupported: the groups take the key tiles of one query tile in turn, and their partial results are merged inside the
- * work-group.  Every class but "fwd_bm128_w4q32_bn64" has one group.
+ * work-group.  Every class but "fwd_bm128_w4q32_bn64" has one group.  A launch has at least those of its class.
  */
 int naut_attn_key_groups(int B, int Hq, int S, int D, int causal);
 int naut_attn_fwd_fp8_key_groups(int B, int Hq, int S, int D, int causal);

@@ -7,6 +7,7 @@ import re
 import pytest
 
 from paper_2604_14825_amd import binding as nb
+from paper_2604_14825_amd import synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -325,3 +326,11 @@ def test_fp8_argument_checks():
     assert f8s(good[:5] + (D - 16,) + good[6:]) == nb.NAUT_ERR_SHAPE                 # k rows overlap
     assert f8s(good[:8] + (1 << 24,) + good[9:]) == nb.NAUT_ERR_UNSUPPORTED          # v row stride too large
     assert f8s(good[:11] + (0,)) == nb.NAUT_ERR_ALIGN                                # o rows would coincide
+
+
+def test_the_benchmark_names_the_kernel_that_runs(monkeypatch):
+    import bench
+    monkeypatch.delenv("NAUT_ATTN_VARIANT", raising=False)
+    want = {"tiny": ("plain_4x32", 1), "encoder": ("pipe_4x64", 1), "prefill": ("pipe_4x32", 1), "gqa": ("pipe_8x32", 1), "long": ("pipe_8x32", 1)}
+    for name, (kernel, groups) in want.items():
+        assert bench.kernel_of(nb, synth.WORKLOADS[name]) == {"kernel": kernel, "key_groups": groups}, name
