@@ -19,7 +19,6 @@ namespace naut_k {
 #if NAUT_INST_W == 64
 template int launch<64, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
 #elif NAUT_INST_W == 96
-extern template int launch<128, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);  // w4q64
 template int launch<80, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
 template int launch<96, NAUT_INST_IN, NAUT_INST_OUT>(Params, int, hipStream_t);
 #elif NAUT_INST_W == 128

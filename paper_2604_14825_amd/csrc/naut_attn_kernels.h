@@ -31,8 +31,8 @@
 //
 // K and V tiles are multi-buffered in LDS, one barrier per tile, and go straight from
 // global memory into LDS (the swizzle applied to the source
-// address): one tile ahead over two buffers in kernel 1, two over four
-// buffers in kernel 2, three over four for heads wider than 128.
+// address): one tile ahead over two buffers in kernel 1, three over four
+// buffers in kernel 2 and for heads wider than 128.
 #ifndef NAUT_ATTN_KERNELS_H
 #define NAUT_ATTN_KERNELS_H
 #include <cfloat>

@@ -8,7 +8,8 @@
 // so the MFMAs of a stage never depend on its vector work.  A stage is laid out as a sequence of slots, one MFMA each,
 // followed by a few vector instructions: the matrix pipe hides about six ordinary vector instructions per MFMA and no
 // more, so the softmax is cut into pieces of that size.  K and V tiles are 32 keys, one barrier per stage, in four LDS
-// buffers per operand, filled by direct global->LDS loads two stages ahead.
+// buffers per operand, filled by direct global->LDS loads that are requested three stages before the one that
+// reads them.
 //
 // What a wavefront owns (QH x 32 queries) and how many share a tile (NWV), with two wavefronts per SIMD throughout (three
 // at D = 64, QH = 1):
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(NWV * NG * 64, (pipe_waves_per_simd<D, QH, NWV, NG>
     constexpr int BM = NWV * WQ;               // queries per work-group
     constexpr int BN = 32;                     // keys per tile and stage
     constexpr int NBUF = 4;                    // LDS buffers per operand
-    constexpr int LA = NBUF - 1;               // K tiles are requested this many stages ahead, V tiles two fewer
+    constexpr int LA = NBUF - 1;               // stage j requests K tile j + LA and V tile j + LA - 2 (read in stage j + LA)
     constexpr int W = layout_width(D);         // row width of the LDS layouts
     constexpr int ROWB = W * 2;
     constexpr int TILEB = BN * ROWB;           // one 32-key K or V tile

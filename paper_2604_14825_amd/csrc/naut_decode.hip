@@ -199,7 +199,7 @@ constexpr int dec_waves_per_simd(int D) { return D > 128 ? 1 : D > 64 ? 2 : 4; }
 // registers, its V when the V fragments are.  Twice as many wavefronts as with two buffers of each keep as many bytes in
 // flight (128 KB per CU), and cover a block's scores, softmax and P.V with each other's loads; the first block's loads
 // are out before Q's.  Against four wavefronts with two buffers (us a call, 32/8 heads, D = 128): 20 caches of 2000 keys 34.1 ->
-// 31.0, 40 of 500 24.9 -> 22.1, 8 of 16384 94.4 -> 93.8; D = 256, 16/8 heads, 256 keys 11.6 -> 10.7.
+// 31.0, 40 of 500 24.9 -> 22.1; D = 256, 16/8 heads, 256 keys 11.6 -> 10.7.  Long caches gain nothing (8 of 16384 94.2 / 94.1).
 template <int D, int DT_IN, int NW>
 __global__ __launch_bounds__(NW * 64, (dec_waves_per_simd(D))) void naut_decode_split_kernel(const DecodeParams p)
 {
