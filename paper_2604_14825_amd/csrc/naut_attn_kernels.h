@@ -820,7 +820,7 @@ inline int pick_variant(int S, long long nbh, int D, int causal, int* groups)
 
 // What a launch with D <= 128 runs (D: the compiled width): kernel 1 (V_BM128) with one, two or four key groups, or kernel 2
 // on 8 x 32 queries (V_W8Q32), 4 x 32 (V_W4Q32, one or two key groups) or 4 x 64 (V_W4Q64, D = 64 only).
-// Fitted to timings of every form in turn over some 7000 shapes (D = 64, 80, 96 and 128, 1 to 768 heads, S = 128 to 16384,
+// Fitted to timings of every form in turn over some 9500 shapes (D = 64, 80, 96 and 128, 1 to 768 heads, S = 128 to 16384,
 // with and without the mask).  Kernel time, us:
 //   Four key groups of kernel 1: where key_groups says four, and on a little shorter and larger grids: up to 256 work-groups
 //   of 64 queries, one per CU, all in one round (8 heads, S = 1024, D = 128, causal 16.2; kernel 2 17.6).  With the mask also
