@@ -153,7 +153,7 @@ const char* naut_attn_variant_name(int B, int Hq, int S, int D, int causal, int 
  * every one over a grid of shapes (python -m paper_2604_14825_amd.tune prints such a table and flags where the rule loses):
  * "pipe_..." the software-pipelined kernel, "plain_..." the other; then wavefronts x queries of each (of each key group),
  * and the number of key groups if several share a work-group.  NULL if the sizes are unsupported.  Host only.  (Rows of
- * K or V more than 8 MiB apart run pipe_4x32 where this says pipe_4x32_g2.)
+ * K or V more than 8 MiB apart run plain_4x32_g2 where this says pipe_4x32_g2.)
  */
 const char* naut_attn_fwd_kernel_name(int B, int Hq, int S, int D, int causal);
 

@@ -908,7 +908,11 @@ int launch(Params p, int causal, hipStream_t stream)
 {
     const long long nbh = (long long)p.B * p.Hq;
     int groups = 1;
-    const int variant = D > 128 ? wide_variant(p.S, nbh, D, causal) : pick_form(p.S, nbh, D, causal, &groups);
+    int variant = D > 128 ? wide_variant(p.S, nbh, D, causal) : pick_form(p.S, nbh, D, causal, &groups);
+    // Two key groups of kernel 2 step over twice the rows at a time: with rows of at most 8 MiB that is at most 2^29 bytes, as
+    // the 32-bit offsets between two moves of the base need it (see rebase in the kernel).  Farther apart: those of kernel 1.
+    if (D <= 128 && variant == V_W4Q32 && groups == 2 && (p.k_rs > p.v_rs ? p.k_rs : p.v_rs) > 8 << 20)
+        variant = V_BM128;
     // How far a block's row sum of P (16 keys) may grow before kernel 2 moves the reference maximum.  Long loops take all the
     // range the type has: a move costs the block's softmax again.  Elsewhere 24, a lag of 1 to 4.6 binades for kernel 1's 6
     // (RESCALE_TAU): after a move the largest P of the row is exactly 1 and carries no rounding error into O, which shows in
@@ -943,9 +947,7 @@ int launch(Params p, int causal, hipStream_t stream)
         else
             NAUT_LAUNCH(256, naut_fwd_kernel_bm128, NAUT_COMMA 4);
     } else if (variant == V_W4Q32) {
-        // two key groups step over twice the rows at a time: with rows of at most 8 MiB that is at most 2^29 bytes, as the
-        // 32-bit offsets between two moves of the base need it (see rebase in the kernel)
-        if (groups == 2 && (p.k_rs > p.v_rs ? p.k_rs : p.v_rs) <= 8 << 20)
+        if (groups == 2)
             NAUT_LAUNCH(512, naut_fwd_kernel_pipe, NAUT_COMMA 1 NAUT_COMMA 4 NAUT_COMMA 2);
         else
             NAUT_LAUNCH(256, naut_fwd_kernel_pipe, NAUT_COMMA 1 NAUT_COMMA 4);

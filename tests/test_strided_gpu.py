@@ -218,7 +218,7 @@ def test_wide_head_groups_of_heads(B, Hq, Hkv, S, monkeypatch):
 @pytest.mark.parametrize("D,variant,mib", [(256, None, 16), (128, "bm128", 16), (128, "w8q32", 16), (64, "w8q32", 16), (64, "bm128", 16),
                                            (256, "w8q32", 16), (128, "bm128g1", 16), (64, "bm128g1", 16), (128, "bm128g2", 16),
                                            (128, "w4q32", 16), (64, "w4q32", 16), (128, "w4q32g2", 8), (64, "w4q32g2", 8),
-                                           (128, "w4q32g2", 16)])   # more than 8 MiB: one key group, see launch()
+                                           (128, "w4q32g2", 16), (64, "w4q32g2", 16)])   # more than 8 MiB: kernel 1's two groups
 @pytest.mark.parametrize("causal", [True, False])
 def test_wide_head_row_stride_beyond_32_bits(D, variant, mib, causal, monkeypatch):
     """K and V rows 16 MiB apart (the largest row stride the entry point admits) or as far as two key groups of the pipelined
@@ -246,6 +246,10 @@ def test_wide_head_row_stride_beyond_32_bits(D, variant, mib, causal, monkeypatc
     o, lse = run_strided(qd, kd, vd, od, causal, scale)
     o_ref, lse_ref = oracle.attn_rows(q, k, v, idt, causal, scale)
     gu.check(o, lse, o_ref, lse_ref, "D=%d %s, row stride of %d MiB" % (D, variant, mib))
+    if variant == "w4q32g2" and mib > 8:  # still two groups, and their accuracy
+        gu.use_form(monkeypatch, "bm128g2", B, H, S, D, causal)
+        again = run_strided(qd, kd, vd, torch.full_like(od, float("nan")), causal, scale)
+        assert np.array_equal(o, again[0]) and np.array_equal(lse, again[1])
 
 
 @pytest.mark.parametrize("D,variant", [(72, "w8q32"), (80, "w8q32"), (88, "w8q32"), (96, "w8q32"), (104, "w8q32"),
